@@ -183,10 +183,10 @@ mmas_status mmas_construct(mmas_ctx* ctx, uint32_t iteration);
  * where that is one wave with 9 <= cand_len <= 32 and at most as many ants
  * as the GPU has SIMDs, a second wave per ant computes the steps' draws
  * ahead into LDS (a draw helper; at most 8 ants per workgroup then).
- * 1 = the ant's wave alone. Without a candidate list, with the bitmask
- * tabu and n <= 1024, four waves per ant (by default or asked for) form a
- * team that splits every step's keys (one barrier a step). EINVAL for other
- * values. */
+ * 1 = the ant's wave alone. Without a candidate list and with n <= 4096, the
+ * default and four waves per ant take a team that splits every step's keys
+ * by draw blocks (1 to 16 waves by n and the ant count; the tabu is kept in
+ * registers whichever is asked for). EINVAL for other values. */
 mmas_status mmas_set_launch(mmas_ctx* ctx, int32_t ants_per_block, int32_t table_rows, int32_t lanes_per_ant,
                             int32_t waves_per_ant);
 

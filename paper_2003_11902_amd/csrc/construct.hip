@@ -1672,37 +1672,58 @@ __global__ __launch_bounds__(1024) void k_construct_wide(Views vw, Shape s, uint
     construct_lone<kTabu, kPher, kRows, kG, true>(vw, s, it, (int)blockIdx.x, lane, region, tcand, tchc, R, &wl, nw);
 }
 
-// Without candidate lists, for small instances with SIMDs to spare: a team
-// of four waves per ant and no shared tabu. Every step keys all unvisited
-// cities (Alg. 4 over all of them, as the fallback does); the cities are
-// split by their word in the draw block: wave j takes city 4b + j of every
-// block b, so the four waves compute the same Philox blocks (one per lane and
-// round) and each keys one word of them. A wave keeps the visited bits of its
-// cities in a register (bit r of lane l: city 4 (64 r + l) + j; the bitmask
-// tabu held in registers). One barrier a step: each wave posts its best
-// (key code, city), and all four read the four and take the same winner, so
-// each knows the next city without a second exchange. n <= 1024 (at most four
-// rounds of 64 blocks).
-template <int kPher>
-__global__ __launch_bounds__(256) void k_construct_team(Views vw, Shape s, uint32_t it) {
-    __shared__ unsigned long long res[2][4];  // by step parity: each wave's best
+// The two largest of four codes (the second: a lane that holds two near the
+// wave's best has a near tie of its own).
+__device__ __forceinline__ void top_two(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t& m1,
+                                        uint32_t& m2) {
+    const uint32_t h01 = max(c0, c1), l01 = min(c0, c1), h23 = max(c2, c3), l23 = min(c2, c3);
+    m1 = max(h01, h23);
+    m2 = max(max(min(h01, h23), l01), l23);
+}
+
+// Without candidate lists, up to 4096 cities: a team of W waves per ant and no
+// shared tabu. Every step keys all unvisited cities (Alg. 4 over all of them,
+// as the fallback does), by draw blocks: wave w, lane l takes blocks
+// 64 w + l + 64 W r, r < kBlocks (cities 4 b .. 4 b + 3 of block b), keeps
+// their visited bits in a register, computes each block once and keys its
+// four words approximately (device.hpp). With W > 1 each wave posts its best
+// and whether its second best is near it, and after one barrier all waves
+// take the same winner; with one wave there is no exchange. A near tie (about
+// one step in 10^5) is settled by the exact keys. Bound by issue: about 78
+// instructions a block (half of them the Philox rounds) and 90 a step and
+// wave. n = 1002, 1002 ants: 2.55 ms -> 0.95 ms (four waves that all computed
+// every Philox block, exact keys with 25 instructions a logarithm, before);
+// n = 198: 130 -> 79 us; n = 3795, 3795 ants: 71 -> 35 ms.
+// (a row is read four floats at a time: the last block's read may pass the
+// row's end by at most three floats, into the next row or, after the last
+// row, into the padding of the view to 256 bytes, which is at least that long
+// whenever n is not a multiple of 4)
+template <int W, int kBlocks>
+__global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, uint32_t it) {
+    static_assert(kBlocks <= 4, "a city's place in the lane takes four code bits");
+    constexpr uint32_t kId = kBlocks == 1 ? 3u : kBlocks == 2 ? 7u : 15u;  // those low bits
+    __shared__ unsigned long long res[2][W];  // by step parity: each wave's best
+    __shared__ unsigned long long resx[W];    // the exact keys' best
     const int lane = threadIdx.x & 63;
-    const int j = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // word of the block
+    const int wave = W > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     const int ant = blockIdx.x;
     const int n = s.n;
     const uint64_t seed = s.seed;
-    const int rounds = (((n + 3) >> 2) + kWave - 1) / kWave;  // <= 4
-    float tmin_a = 0.0f;
-    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(vw.state->tau_min, s.alpha);
+    const int b0 = kWave * wave + lane;  // this lane's first draw block; the others follow at 64 W
     const uint32_t x0 = draw_block(seed, it, (uint32_t)ant, 0u, 0u).w[0];
     const int start = __builtin_amdgcn_readfirstlane((int)(((uint64_t)x0 * (uint64_t)n) >> 32));
-    // visited bits; cities past n count as visited
-    uint32_t vis = 0u;
+    // bit 4 r + j: city j of block r is live; cities past n count as visited
+    uint32_t live = 0u;
+    uint32_t row_off[kBlocks];  // bytes into the row of factors
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (r >= rounds || 4 * (kWave * r + lane) + j >= n) vis |= 1u << r;
+    for (int r = 0; r < kBlocks; ++r) {
+        const int left = n - 4 * (b0 + kWave * W * r);
+        live |= (left >= 4 ? 0xFu : left > 0 ? (1u << left) - 1u : 0u) << (4 * r);
+        row_off[r] = left > 0 ? 16u * (uint32_t)(b0 + kWave * W * r) : 0u;
+    }
     auto mark = [&](int c) {
-        if ((c & 3) == j && lane == ((c >> 2) & (kWave - 1))) vis |= 1u << (c >> 8);
+        const int cb = c >> 2;
+        live &= ~((cb & (kWave * W - 1)) == b0 ? 1u << (4 * (cb / (kWave * W)) + (c & 3)) : 0u);
     };
     mark(start);
 
@@ -1713,50 +1734,87 @@ __global__ __launch_bounds__(256) void k_construct_team(Views vw, Shape s, uint3
     int64_t len = 0;
     int cur = start;
     for (int k = 1; k < n; ++k) {
-        // the factors and visited bits first, then the draws
-        float f[4];
-        uint32_t v[4];
+        // the factors first, then the draws
+        const uint8_t* row = reinterpret_cast<const uint8_t*>(vw.choice_inv + (size_t)cur * n);
+        float f[kBlocks][4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int c = 4 * (kWave * r + lane) + j;
-            v[r] = c < n ? (uint32_t)c : 0u;
-            if (kPher == MMAS_PHER_DENSE)
-                f[r] = r < rounds ? vw.choice_inv[(size_t)cur * n + v[r]] : 1.0f;
-            else
-                f[r] = r < rounds ? 1.0f / (tmin_a * heur_from_dist(dist[(size_t)cur * n + v[r]], s.beta)) : 1.0f;
-        }
-        uint32_t bcode = 0u, bnode = kNone;
+        for (int r = 0; r < kBlocks; ++r) __builtin_memcpy(f[r], row + row_off[r], sizeof(f[r]));
+        uint32_t m1 = 0u, m2 = 0u;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (r >= rounds) break;
-            const Words4 blk = draw_block(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)(4 * (kWave * r + lane)));
-            const float key = log_u01(u01(pick_word(blk, (uint32_t)j))) * f[r];
-            keep_best(((vis >> r) & 1u) ? 0u : ord_key(key), v[r], bcode, bnode);
+        for (int r = 0; r < kBlocks; ++r) {
+            const Words4 blk =
+                draw_block(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)(4 * (b0 + kWave * W * r)));
+            uint32_t code[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int id = 4 * r + j;
+                const float key = log2_draw(blk.w[j]) * f[r][j];
+                const uint32_t m = (uint32_t)((int)(live << (31 - id)) >> 31);  // ~0 if live
+                code[j] = ((~__float_as_uint(key) & ~kId) | (uint32_t)id) & m;
+            }
+            uint32_t t1, t2;
+            top_two(code[0], code[1], code[2], code[3], t1, t2);
+            m2 = max(max(m2, t2), min(m1, t1));
+            m1 = max(m1, t1);
         }
-        const unsigned long long mine = share_result(bcode, bnode);
-        if (lane == 0) res[k & 1][j] = mine;
-        __syncthreads();
-        // every wave takes the same winner: the largest key code, then the
-        // largest ~city (res[k & 1] is written again two steps later, after
-        // the next barrier)
-        const unsigned long long rr = lane < 4 ? res[k & 1][lane] : 0ull;
-        const uint32_t hi = (uint32_t)(rr >> 32), lo = (uint32_t)rr;
-        const uint32_t mx = wave_max_u32<2>(hi);
-        const uint64_t tied = __ballot(hi == mx && lane < 4);
-        uint32_t best_lo;
-        if (__popcll(tied) == 1)
-            best_lo = (uint32_t)__builtin_amdgcn_readlane((int)lo, __ffsll((unsigned long long)tied) - 1);
-        else
-            best_lo = wave_max_u32<2>(hi == mx ? lo : 0u);
-        const uint32_t next = mx ? ~best_lo : kNone;
+        const uint32_t best = wave_max_bcast(m1);
+        const uint32_t near = near_code(best);
+        const uint64_t tied = __ballot(m1 >= near);
+        const int first = (int)__builtin_ctzll(tied);
+        // (none is near when the wave has no city left: best is 0)
+        bool clear = (__popcll(tied) == 1) & (__ballot(m2 >= near) == 0ull);
+        const uint32_t id = best & kId;
+        uint32_t next = 4u * (uint32_t)(kWave * (W * (int)(id >> 2) + wave) + first) + (id & 3u);
+        if constexpr (W > 1) {
+            if (lane == 0)
+                res[k & 1][wave] = ((unsigned long long)best << 32) | (unsigned long long)(next << 1) |
+                                   (unsigned long long)(clear ? 0u : 1u);
+            __syncthreads();
+            // every wave takes the same winner (res[k & 1] is written again two
+            // steps later, after the next barrier)
+            const unsigned long long rr = res[k & 1][lane < W ? lane : 0];
+            const uint32_t hi = (uint32_t)(rr >> 32), lo = (uint32_t)rr;
+            uint32_t mx = max(hi, dpp<0xB1>(hi));
+            if (W > 2) mx = max(mx, dpp<0x4E>(mx));
+            if (W > 4) mx = max(mx, dpp<0x141>(mx));
+            if (W > 8) mx = max(mx, dpp<0x140>(mx));
+            const uint32_t top = near_code((uint32_t)__builtin_amdgcn_readfirstlane((int)mx));
+            const uint64_t held = __ballot(hi >= top) & ((1ull << W) - 1ull);
+            const uint32_t pick = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)__builtin_ctzll(held));
+            next = pick >> 1;
+            clear = (__popcll(held) == 1) & ((pick & 1u) == 0u);
+        }
+        if (__builtin_expect(!clear, 0)) {
+            // the exact keys (every wave of the team comes here)
+            uint32_t bcode = 0u, bnode = kNone;
+#pragma unroll
+            for (int r = 0; r < kBlocks; ++r) {
+                const uint32_t c = 4u * (uint32_t)(b0 + kWave * W * r);
+                const Words4 blk = draw_block(seed, it, (uint32_t)ant, (uint32_t)k, c);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    keep_best((live >> (4 * r + j)) & 1u ? ord_key(log_u01(u01(blk.w[j])) * f[r][j]) : 0u,
+                              c + (uint32_t)j, bcode, bnode);
+            }
+            unsigned long long r = share_result(bcode, bnode);
+            if constexpr (W > 1) {
+                if (lane == 0) resx[wave] = r;
+                __syncthreads();
+                // (written again after the next step's barrier at the earliest)
+                r = resx[0];
+#pragma unroll
+                for (int w = 1; w < W; ++w) r = resx[w] > r ? resx[w] : r;
+            }
+            next = (uint32_t)__builtin_amdgcn_readfirstlane((int)(r ? ~(uint32_t)r : kNone));
+        }
         if (next >= (uint32_t)n) {
             // unreachable with a validated instance; every wave leaves
-            if (j == 0 && lane == 0) atomicOr(&vw.state->flags, 8u);
+            if (wave == 0 && lane == 0) atomicOr(&vw.state->flags, 8u);
             break;
         }
         mark((int)next);
         cur = (int)next;
-        if (j == 0) {
+        if (wave == 0) {
             const int slot = k & 63;
             if (lane == slot) tbuf = next;
             if (slot == 63 || k == n - 1) {
@@ -1772,7 +1830,7 @@ __global__ __launch_bounds__(256) void k_construct_team(Views vw, Shape s, uint3
             }
         }
     }
-    if (j != 0) return;
+    if (wave != 0) return;
     if (lane == 0) len += dist[(size_t)cur * n + start];  // closing edge
     len = wave_sum_i64(len);
     if (lane == 0) {
@@ -1923,10 +1981,10 @@ hipError_t launch_t(const Views& v, const Shape& s0, uint32_t it, hipStream_t st
 // where the all-city fallback dominates the step, the only part the helper
 // waves share. With n >= 8192 (long fallbacks) and SIMDs to spare: as many
 // as the SIMDs left over by one wave per ant allow, a power of two up to 16.
-// Without a candidate list at n >= 512: four (the bitmask tabu's cities are
-// then gathered by the workgroup, one LDS atomic per wave). Otherwise one:
-// the per-step barriers then cost more than the shared fallbacks save
-// (measured at n = 198, 1002 and 3795 with and without lists).
+// Without a candidate list (past the team kernel's n): four (the bitmask
+// tabu's cities are then gathered by the workgroup, one LDS atomic per wave).
+// Otherwise one: the per-step barriers then cost more than the shared
+// fallbacks save (measured at n = 198, 1002 and 3795 with lists).
 int construct_waves(const Shape& s) {
     if (s.construct_waves > 0) return s.construct_waves;
     if (s.n >= 8192) {
@@ -1936,7 +1994,7 @@ int construct_waves(const Shape& s) {
         while (w < 16 && 2 * w * s.ants <= simds) w *= 2;
         return w;
     }
-    if (s.cl == 0 && s.n >= 512) return 4;
+    if (s.cl == 0) return 4;
     return 1;
 }
 
@@ -1970,24 +2028,49 @@ hipError_t launch_wide(const Views& v, const Shape& s, uint32_t it, int waves, h
     return hipGetLastError();
 }
 
-// The team kernel (four waves per ant, no list, bitmask tabu, n <= 1024):
-// by default, or asked for with four waves per ant. Measured at n = 1002
-// with 1002 ants (four waves per SIMD): 2.55 ms against 2.92 ms with four
-// waves sharing the fallbacks and 3.06 ms with one wave per ant.
+// The team kernel (no list, n <= 4096, whichever tabu: it keeps the visited
+// bits in registers), by default or asked for with four waves per ant.
 bool team_ok(const Shape& s) {
-    if (s.cl != 0 || s.tabu != MMAS_TABU_BITMASK || s.n > 1024 || s.select != MMAS_SELECT_WRS) return false;
+    if (s.cl != 0 || s.n > 4096) return false;
     return s.construct_waves == 0 || s.construct_waves == 4;
 }
 
-template <int kPher>
-hipError_t launch_team(const Views& v, const Shape& s, uint32_t it, hipStream_t st) {
-    k_construct_team<kPher><<<s.ants, 4 * kWave, 0, st>>>(v, s, it);
+// Waves per ant and blocks per lane, by q = ceil(blocks / 64) waves of blocks.
+// While q waves per ant load each SIMD at most twice, one block a lane: the
+// blocks run side by side and the barrier costs less than a second block
+// (n = 1002: 64 to 256 ants 0.56 ms with four waves, 0.90 with one; 512 ants
+// 0.73 and 0.92). Past that the waves share the issue slots and the fewest
+// waves win, whose exchange and selection are paid once per ant (1002 ants:
+// 1.07 ms with four waves, 0.95 with one and no exchange; n = 3795, 3795
+// ants: 62 and 35 ms with sixteen and four). Up to two blocks a lane one wave
+// is as good at any ant count (n = 512: 64 ants 0.28 ms with two waves, 0.29
+// with one; 512 ants 0.36 and 0.31).
+template <int W, int kBlocks>
+hipError_t launch_team_t(const Views& v, const Shape& s, uint32_t it, hipStream_t st) {
+    k_construct_team<W, kBlocks><<<s.ants, kWave * W, 0, st>>>(v, s, it);
     return hipGetLastError();
+}
+
+hipError_t launch_team(const Views& v, const Shape& s, uint32_t it, hipStream_t st) {
+    const int q = (((s.n + 3) >> 2) + kWave - 1) / kWave;
+    if (q <= 1) return launch_team_t<1, 1>(v, s, it, st);
+    if (q <= 2) return launch_team_t<1, 2>(v, s, it, st);
+    const int waves = q <= 4 ? 4 : q <= 8 ? 8 : 16;
+    if ((int64_t)s.ants * waves <= 2 * (int64_t)device_attr(g_simds, hipDeviceAttributeMultiprocessorCount, 4, 0))
+        return waves == 4   ? launch_team_t<4, 1>(v, s, it, st)
+               : waves == 8 ? launch_team_t<8, 1>(v, s, it, st)
+                            : launch_team_t<16, 1>(v, s, it, st);
+    if (q <= 3) return launch_team_t<1, 3>(v, s, it, st);
+    if (q <= 4) return launch_team_t<1, 4>(v, s, it, st);
+    if (q <= 6) return launch_team_t<2, 3>(v, s, it, st);
+    if (q <= 8) return launch_team_t<2, 4>(v, s, it, st);
+    if (q <= 12) return launch_team_t<4, 3>(v, s, it, st);
+    return launch_team_t<4, 4>(v, s, it, st);
 }
 
 template <int kTabu, int kPher>
 hipError_t launch_tp(const Views& v, const Shape& s, uint32_t it, hipStream_t st) {
-    if (kTabu == MMAS_TABU_BITMASK && team_ok(s)) return launch_team<kPher>(v, s, it, st);
+    if (kPher == MMAS_PHER_DENSE && team_ok(s)) return launch_team(v, s, it, st);
     if (pair_ok(s)) return launch_t<kTabu, kPher, true>(v, s, it, st);
     const int waves = construct_waves(s);
     if (waves > 1) return launch_wide<kTabu, kPher>(v, s, it, waves, st);

@@ -282,3 +282,41 @@ def test_team_without_list(gpu, n, pher, ants, waves):
     _, d = I.make_instance("uniform", n, seed=n + 3, side=1e5)
     say(f"team no list n={n} {pher} ants={ants} waves={waves}")
     run_parity(d, 3, ants=ants, cand_len=0, rho=0.1, seed=4, tabu="bitmask", pher=pher, launch=(0, -1, 64, waves))
+
+
+@pytest.mark.parametrize("n,alpha,beta,side,ants", [
+    (1000, 0, 0, 1e4, 128),   # every weight 1: draws that tie, and that nearly tie
+    (300, 8, 8, 1e5, 24),     # weights underflow to denormals and 0: factors up to infinity
+    (260, 1, 8, 1e6, 24),     # denormal weights beside normal ones
+    (40, 8, 0, 2e1, 24),      # coarse distances (long runs of equal weights)
+])
+@pytest.mark.parametrize("cl,launch", [(0, None), (0, (0, -1, 64, 1)), (32, None), (32, (0, -1, 64, 1)), (4, (0, -1, 64, 4)),
+                                       (24, (4, -1, 32, 0))])
+def test_near_ties_and_extreme_weights(gpu, n, alpha, beta, side, ants, cl, launch):
+    """Selections decided by approximate keys fall back to the exact keys
+    where two nearly tie, and where keys leave the range in which the
+    approximation is bounded: tours equal the oracle's for equal weights and
+    for weights at the ends of the FP32 range."""
+    _, d = I.make_instance("uniform", n, seed=n + 1, side=side)
+    say(f"near ties n={n} alpha={alpha} beta={beta} cl={cl} launch={launch}")
+    run_parity(d, 2, ants=ants, cand_len=cl, alpha=alpha, beta=beta, rho=0.1, seed=6, launch=launch)
+
+
+@pytest.mark.parametrize("tabu", ["bitmask", "compact", "list"])
+@pytest.mark.parametrize("n,ants", [(3, 4), (4, 4), (256, 20), (258, 20), (512, 10), (515, 10), (1025, 6), (2048, 3),
+                                    (2051, 3), (4095, 2), (4096, 2), (4097, 2)])
+def test_team_sizes(gpu, n, ants, tabu):
+    """Without a list: one draw block per lane, from one wave per ant to the
+    largest team and just past it; every tabu takes the same launch."""
+    _, d = I.make_instance("uniform", n, seed=n, side=1e5)
+    say(f"team sizes n={n} {tabu}")
+    run_parity(d, 2, ants=ants, cand_len=0, rho=0.1, seed=4, tabu=tabu)
+
+
+@pytest.mark.parametrize("n,ants", [(520, 520), (770, 520), (1026, 260), (1540, 260), (2050, 130), (3080, 130)])
+def test_team_blocks_per_lane(gpu, n, ants):
+    """Without a list and with ants enough to share the SIMDs: two to four
+    draw blocks per lane and fewer waves per ant."""
+    _, d = I.make_instance("uniform", n, seed=n, side=1e5)
+    say(f"team blocks n={n} ants={ants}")
+    run_parity(d, 1, ants=ants, cand_len=0, rho=0.1, seed=4)
