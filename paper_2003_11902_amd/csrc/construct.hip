@@ -30,6 +30,9 @@ template <class T>
 using LdsPtr = __attribute__((address_space(3))) T*;
 template <class T>
 using GlbPtr = __attribute__((address_space(1))) T*;
+// four consecutive row entries, aligned to one
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr size_t kDrawBytes = 4 * kWave * sizeof(float);  // candidate draws of the next steps
 constexpr size_t kScratchBytes = 16;                       // per-ant counter of the fallback list
 
@@ -191,91 +194,12 @@ __device__ __forceinline__ void keep_best(uint32_t code, uint32_t node, uint32_t
     }
 }
 
-// Keys of an all-node fallback over `list` (the L unvisited cities, or a
-// part of them): city v draws slot cl + v. Each lane takes four list entries
-// per round and issues their weight loads before the Philox and logarithm
-// work, so the loads overlap it. Folds the best (code, city) of each lane
-// into bcode / bnode.
-template <class F>
-__device__ __forceinline__ void fallback_keys(const uint16_t* list, int L, const F& factor, int cl, uint64_t seed,
-                                              uint32_t it, uint32_t ant, uint32_t step, int lane, uint32_t& bcode,
-                                              uint32_t& bnode) {
-    for (int base = 0; base < L; base += 4 * kWave) {
-        uint32_t v[4];
-        float f[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + u * kWave + lane;
-            v[u] = i < L ? (uint32_t)list[i] : kNone;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) f[u] = v[u] != kNone ? factor(v[u]) : 1.0f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (v[u] == kNone) continue;
-            const uint32_t slot = (uint32_t)cl + v[u];
-            const Words4 blk = draw_block(seed, it, ant, step, slot);
-            const float key = log_u01(u01(pick_word(blk, slot & 3u))) * f[u];
-            keep_best(ord_key(key), v[u], bcode, bnode);
-        }
-    }
-}
-
-// All-node fallback over a list of the L unvisited cities (the compact tabu's
-// left part).
-template <class F>
-__device__ __forceinline__ uint32_t fallback_list(const uint16_t* list, int L, const F& factor, int cl, uint64_t seed,
-                                                  uint32_t it, uint32_t ant, uint32_t step, int lane) {
-    uint32_t bcode = 0u, bnode = kNone;
-    fallback_keys(list, L, factor, cl, seed, it, ant, step, lane, bcode, bnode);
-    return wave_select<4>(bcode, bnode);
-}
-
 // Entries of the list a one-wave fallback over a bitmask tabu builds in LDS
-// (unless the launch allows more): the unvisited cities are listed and keyed
-// in passes of at most this many, so the ant's LDS does not grow with n.
+// (unless the launch allows more): with more unvisited cities the fallback
+// goes by draw blocks, so the ant's LDS does not grow with n.
 constexpr int kListCap = 512;
 __host__ __device__ inline int list_cap(const Shape& s) {
     return s.list_cap > 0 ? s.list_cap : (s.n < kListCap ? s.n : kListCap);
-}
-
-// All-node fallback over a bitmask tabu. Each pass takes the next words (one
-// per lane, at most 64), keeps the longest run of them whose unvisited cities
-// fit in `cap` list entries (a wave prefix sum of their counts gives every
-// lane its first slot), lists those cities and keys them; the best key over
-// all passes wins (largest key, lowest city), as over one list of them all.
-template <class F>
-__device__ __forceinline__ uint32_t fallback_bitmask(const BitmaskTabu& tabu, int n, uint16_t* list, int cap,
-                                                     const F& factor, int cl, uint64_t seed, uint32_t it, uint32_t ant,
-                                                     uint32_t step, int lane) {
-    const int words = (n + 31) >> 5;
-    uint32_t bcode = 0u, bnode = kNone;
-    for (int w0 = 0; w0 < words;) {
-        const int wi = w0 + lane;
-        uint32_t fr = 0u;
-        if (wi < words) {
-            fr = ~tabu.bits[wi];
-            if (wi == words - 1 && (n & 31)) fr &= (1u << (n & 31)) - 1u;
-        }
-        const int cnt = __popc(fr);
-        const int incl = wave_incl_scan(cnt, lane);
-        // a prefix of the lanes (incl grows with the lane); lane 0 always
-        // fits, since one word holds at most 32 <= cap cities
-        const bool fits = (wi < words) & (incl <= cap);
-        const int nfit = __popcll(__ballot(fits));
-        const int L = __builtin_amdgcn_readlane(incl, nfit - 1);
-        if (fits) {
-            int p = incl - cnt;
-            while (fr) {
-                const int b = __ffs(fr) - 1;
-                fr &= fr - 1u;
-                list[p++] = (uint16_t)(wi * 32 + b);
-            }
-        }
-        fallback_keys(list, L, factor, cl, seed, it, ant, step, lane, bcode, bnode);
-        w0 += nfit;
-    }
-    return wave_select<4>(bcode, bnode);
 }
 
 // A wave's best (key code, lowest city) packed so that the larger value is
@@ -292,28 +216,6 @@ __device__ __forceinline__ unsigned long long share_result(uint32_t bcode, uint3
     return ((unsigned long long)bc << 32) | (unsigned long long)(~node);
 }
 
-// The all-node fallback of the single-colony kernel, outlined (it is rare
-// with a list, and one copy serves every step of the unrolled step loop):
-// the same keys and winner as fallback_bitmask / fallback_list, but with the
-// LDS tabu and the global factor row passed with their address spaces (an
-// outlined function would otherwise reach both through flat accesses) and
-// without branches around a lane's keys. Two layouts:
-//  - by list entries: a lane keys four entries of the list of the L
-//    unvisited cities a round (the compact and list tabus keep that list,
-//    the bitmask tabu's unvisited cities are listed into `list` first), one
-//    Philox block per entry;
-//  - by draw blocks: a lane takes the block of slots 4b .. 4b+3 a round,
-//    computes it once and keys each of its cities that is unvisited (every
-//    city is looked at, but a block serves four).
-// The cheaper one by instruction count is taken: a round of blocks costs a
-// Philox block (about 45) and four keys (about 45 each with the tabu test);
-// the list costs a Philox block and a key (about 85) for every 64 entries
-// (rounds whose entries are all past L are skipped), plus about 140 to list
-// a bitmask. `tabu`: the bitmask words,
-// the compact tabu's entries or the list tabu's unv (idx follows at n);
-// L: the number of unvisited cities. Key factors: irow[v], the reciprocal of
-// the weight (dense trails), or 1 / (tmin_a * eta(drow[v])^beta)
-// (candidate-only trails).
 // Wave-uniform values that arrive in vector registers (the arguments of an
 // outlined function) read back into scalar registers, so that the branches
 // and loops over them are scalar.
@@ -328,215 +230,306 @@ __device__ __forceinline__ T* uni_ptr(T* p) {
     return reinterpret_cast<T*>(uni((uint64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
+
+// What an all-city fallback of one ant needs, every value wave-uniform. The
+// tabu is the bitmask's words, the compact tabu's entries or the list tabu's
+// unv (idx follows at n); key factors are irow[v], the reciprocal of the
+// weight (dense trails), or 1 / (tmin_a * eta(drow[v])^beta) (candidate-only
+// trails). LDS and global pointers carry their address spaces (an outlined
+// function would otherwise reach both through flat accesses).
+struct Fallback {
+    LdsPtr<const uint16_t> tabu;
+    int L;  // unvisited cities
+    int n, cl, beta;
+    GlbPtr<const float> irow;
+    GlbPtr<const int32_t> drow;
+    float tmin_a;
+    uint64_t seed;
+    uint32_t it, ant, step;
+};
+
+template <int kTabu>
+__device__ __forceinline__ bool fallback_seen(const Fallback& q, uint32_t v) {
+    if constexpr (kTabu == MMAS_TABU_BITMASK)
+        return (((LdsPtr<const uint32_t>)q.tabu)[v >> 5] >> (v & 31u)) & 1u;
+    else if constexpr (kTabu == MMAS_TABU_COMPACT)
+        return q.tabu[v] > v;
+    else
+        return (int)q.tabu[q.n + v] >= q.L;
+}
+
+template <int kPher>
+__device__ __forceinline__ float exact_factor(const Fallback& q, uint32_t v) {
+    if constexpr (kPher == MMAS_PHER_DENSE)
+        return q.irow[v];
+    else
+        return 1.0f / (q.tmin_a * heur_from_dist(q.drow[v], q.beta));
+}
+
+// The exact fallback, for the near ties: city v draws slot cl + v, and the
+// largest key (the lowest city among equal ones) wins.
 template <int kTabu, int kPher>
-__device__ __attribute__((noinline)) uint32_t fallback_lone(LdsPtr<const uint16_t> tabu_v, LdsPtr<uint16_t> list_v,
-                                                            int L_v, int n_v, GlbPtr<const float> irow_v,
-                                                            GlbPtr<const int32_t> drow_v, float tmin_a_v, int beta_v,
-                                                            int cl_v, uint64_t seed_v, uint32_t it_v, uint32_t ant_v,
-                                                            uint32_t step_v, int lane) {
-    constexpr bool kList = kTabu != MMAS_TABU_BITMASK;
-    const LdsPtr<const uint16_t> tabu = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)tabu_v);
-    const LdsPtr<uint16_t> list = (LdsPtr<uint16_t>)uni((uint32_t)(uintptr_t)list_v);
-    const GlbPtr<const float> irow = (GlbPtr<const float>)uni((uint64_t)(uintptr_t)irow_v);
-    const GlbPtr<const int32_t> drow = (GlbPtr<const int32_t>)uni((uint64_t)(uintptr_t)drow_v);
-    int L = uni(L_v);
-    const int n = uni(n_v), beta = uni(beta_v), cl = uni(cl_v);
-    const float tmin_a = uni(tmin_a_v);
-    const uint64_t seed = uni(seed_v);
-    const uint32_t it = uni(it_v), ant = uni(ant_v), step = uni(step_v);
-    auto factor = [&](uint32_t v) -> float {
-        if constexpr (kPher == MMAS_PHER_DENSE)
-            return irow[v];
-        else
-            return 1.0f / (tmin_a * heur_from_dist(drow[v], beta));
-    };
-    const int b_lo = cl >> 2, nb = ((cl + n - 1) >> 2) - b_lo + 1;  // blocks holding slots cl .. cl + n - 1
-    const int rounds_b = (nb + kWave - 1) / kWave, per_lane = (L + kWave - 1) / kWave;
+__device__ __attribute__((noinline)) uint32_t fallback_exact(Fallback q, int lane) {
     uint32_t bcode = 0u, bnode = kNone;
-    if (225 * rounds_b < 85 * per_lane + (kList ? 0 : 140)) {
-        for (int b0 = b_lo; b0 < b_lo + nb; b0 += kWave) {
-            const int b = b0 + lane;
-            uint32_t v[4];
-            bool ok[4];
-            float f[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = 4 * b + j - cl;
-                ok[j] = b < b_lo + nb && c >= 0 && c < n;
-                v[j] = ok[j] ? (uint32_t)c : 0u;
-            }
-            // the tabu and factor loads go out before the draws
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bool seen;
-                if constexpr (kTabu == MMAS_TABU_BITMASK) {
-                    const LdsPtr<const uint32_t> bits = (LdsPtr<const uint32_t>)tabu;
-                    seen = (bits[v[j] >> 5] >> (v[j] & 31u)) & 1u;
-                } else if constexpr (kTabu == MMAS_TABU_COMPACT) {
-                    seen = tabu[v[j]] > v[j];
-                } else {
-                    seen = (int)tabu[n + v[j]] >= L;
-                }
-                ok[j] = ok[j] & !seen;
-                f[j] = factor(v[j]);
-            }
-            const Words4 blk = draw_block(seed, it, ant, step, (uint32_t)(4 * b));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float key = log_u01(u01(blk.w[j])) * f[j];
-                keep_best(ok[j] ? ord_key(key) : 0u, v[j], bcode, bnode);
-            }
-        }
-        return wave_select<4>(bcode, bnode);
-    }
-    if constexpr (!kList) {
-        // every unvisited city in ascending order (one pass: room for n),
-        // lane l taking 16-bit halves l, l + 64, ... of the bitmask, so that
-        // a lane writes at most 16 entries
-        const LdsPtr<const uint16_t> halves = tabu;
-        const int nh = (n + 15) >> 4;
-        L = 0;
-        for (int h0 = 0; h0 < nh; h0 += kWave) {
-            const int hi = h0 + lane;
-            uint32_t fr = 0u;
-            if (hi < nh) {
-                fr = ~(uint32_t)halves[hi] & 0xFFFFu;
-                if (hi == nh - 1 && (n & 15)) fr &= (1u << (n & 15)) - 1u;
-            }
-            const int cnt = __popc(fr);
-            const int incl = wave_incl_scan(cnt, lane);
-            int p = L + incl - cnt;
-            while (fr) {
-                const int b = __ffs(fr) - 1;
-                fr &= fr - 1u;
-                list[p++] = (uint16_t)(hi * 16 + b);
-            }
-            L += __builtin_amdgcn_readlane(incl, 63);
-        }
-    }
-    for (int base = 0; base < L; base += 4 * kWave) {
-        uint32_t v[4];
-        float f[4];
-        bool ok[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + u * kWave + lane;
-            ok[u] = i < L;
-            v[u] = list[ok[u] ? i : 0];
-        }
-        // the factor loads go out before the draws and their logarithms
-#pragma unroll
-        for (int u = 0; u < 4; ++u) f[u] = factor(v[u]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t slot = (uint32_t)cl + v[u];
-            const Words4 blk = draw_block(seed, it, ant, step, slot);
-            const float key = log_u01(u01(pick_word(blk, slot & 3u))) * f[u];
-            const uint32_t code = ok[u] ? ord_key(key) : 0u;
-            keep_best(code, v[u], bcode, bnode);
-        }
+    for (int v0 = 0; v0 < q.n; v0 += kWave) {
+        const uint32_t v = (uint32_t)(v0 + lane);
+        if (v >= (uint32_t)q.n || fallback_seen<kTabu>(q, v)) continue;
+        const uint32_t slot = (uint32_t)q.cl + v;
+        const Words4 blk = draw_block(q.seed, q.it, q.ant, q.step, slot);
+        const float key = log_u01(u01(pick_word(blk, slot & 3u))) * exact_factor<kPher>(q, v);
+        keep_best(ord_key(key), v, bcode, bnode);
     }
     return wave_select<4>(bcode, bnode);
 }
 
-// The same fallback for the compact and list tabus, split between `parts`
-// waves that call this with part = 0 .. parts - 1 and the same other
-// arguments (a single-colony ant's wave and its draw helper): each keys its
-// share (alternate rounds of blocks, or alternate 64-entry chunks of the
-// tabu's list, a round holding up to four) and the best of the parts'
-// results is the winner. Returns this part's best as share_result packs it.
+// A lane's two best approximate codes (device.hpp) and the best one's city.
+struct NearBest {
+    uint32_t m1 = 0u, m2 = 0u, node = 0u;
+};
+
+// The two largest of four codes (the second: a lane that holds two near the
+// wave's best has a near tie of its own).
+__device__ __forceinline__ void top_two(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t& m1,
+                                        uint32_t& m2) {
+    const uint32_t h01 = max(c0, c1), l01 = min(c0, c1), h23 = max(c2, c3), l23 = min(c2, c3);
+    m1 = max(h01, h23);
+    m2 = max(max(min(h01, h23), l01), l23);
+}
+
+// 1 / tmin_a, which the approximate factors of candidate-only trails share.
+template <int kPher>
+__device__ __forceinline__ float near_scale(const Fallback& q) {
+    return kPher == MMAS_PHER_DENSE ? 0.0f : 1.0f / q.tmin_a;
+}
+
+// Approximate keys of an all-city fallback, one of two layouts; wave `part`
+// of `parts` takes every parts-th round of 64.
+//  - by draw blocks: a lane takes the block of slots 4b .. 4b+3, computes it
+//    once and keys each of its cities that is unvisited (every city is looked
+//    at, but a block serves four): about 85 instructions a round;
+//  - by list entries (`list` holds the L unvisited cities): one Philox block
+//    and one key per entry, about 58 instructions a round.
 template <int kTabu, int kPher>
-__device__ __attribute__((noinline)) unsigned long long fallback_half(
-    LdsPtr<const uint16_t> tabu_v, LdsPtr<const uint16_t> list_v, int L_v, int n_v, GlbPtr<const float> irow_v,
-    GlbPtr<const int32_t> drow_v, float tmin_a_v, int beta_v, int cl_v, uint64_t seed_v, uint32_t it_v,
-    uint32_t ant_v, uint32_t step_v, int part_v, int parts_v, int lane) {
-    static_assert(kTabu != MMAS_TABU_BITMASK, "the tabu keeps the list of unvisited cities");
-    const LdsPtr<const uint16_t> tabu = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)tabu_v);
-    const LdsPtr<const uint16_t> list = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)list_v);
-    const GlbPtr<const float> irow = (GlbPtr<const float>)uni((uint64_t)(uintptr_t)irow_v);
-    const GlbPtr<const int32_t> drow = (GlbPtr<const int32_t>)uni((uint64_t)(uintptr_t)drow_v);
-    const int L = uni(L_v);
-    const int n = uni(n_v), beta = uni(beta_v), cl = uni(cl_v);
-    const float tmin_a = uni(tmin_a_v);
-    const uint64_t seed = uni(seed_v);
-    const uint32_t it = uni(it_v), ant = uni(ant_v), step = uni(step_v);
-    const int part = uni(part_v), parts = uni(parts_v);
-    auto factor = [&](uint32_t v) -> float {
-        if constexpr (kPher == MMAS_PHER_DENSE)
-            return irow[v];
-        else
-            return 1.0f / (tmin_a * heur_from_dist(drow[v], beta));
-    };
-    const int b_lo = cl >> 2, nb = ((cl + n - 1) >> 2) - b_lo + 1;  // blocks holding slots cl .. cl + n - 1
-    const int span = kWave * parts;
-    const int rounds_b = (nb + span - 1) / span, per_lane = (L + span - 1) / span;
-    uint32_t bcode = 0u, bnode = kNone;
-    if (225 * rounds_b < 85 * per_lane) {
-        for (int b0 = b_lo + part * kWave; b0 < b_lo + nb; b0 += span) {
-            const int b = b0 + lane;
-            uint32_t v[4];
-            bool ok[4];
-            float f[4];
+__device__ __forceinline__ void near_blocks(const Fallback& q, int part, int parts, int lane, NearBest& nb) {
+    const int n = q.n, cl = q.cl;
+    const float scale = near_scale<kPher>(q);
+    const int b_lo = cl >> 2, b_hi = (cl + n - 1) >> 2;  // blocks holding slots cl .. cl + n - 1
+    int best_b = 0;
+    for (int b0 = b_lo + part * kWave; b0 <= b_hi; b0 += kWave * parts) {
+        const int b = b0 + lane, o = 4 * b - cl;  // the block's cities: o .. o + 3
+        uint32_t live[4];                         // ~0 for an unvisited city
+        float f[4];
+        // (the tabu and factor loads go out before the draws)
+        if (4 * b0 >= cl && 4 * (b0 + kWave) - cl <= n) {
+            // every block of the round lies inside: one read of the bitmask
+            // and of the row for all four cities
+            if constexpr (kTabu == MMAS_TABU_BITMASK) {
+                const LdsPtr<const uint32_t> w = (LdsPtr<const uint32_t>)q.tabu + (o >> 5);
+                // (the word after the bitmask is inside the ant's region)
+                const uint32_t seen = __builtin_amdgcn_alignbit(w[1], w[0], (uint32_t)o & 31u);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = 4 * b + j - cl;
-                ok[j] = b < b_lo + nb && c >= 0 && c < n;
-                v[j] = ok[j] ? (uint32_t)c : 0u;
+                for (int j = 0; j < 4; ++j) live[j] = (uint32_t)((int)(~seen << (31 - j)) >> 31);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) live[j] = fallback_seen<kTabu>(q, (uint32_t)(o + j)) ? 0u : ~0u;
             }
-            // the tabu and factor loads go out before the draws
+            if constexpr (kPher == MMAS_PHER_DENSE) {
+                const f32x4_u r = *(GlbPtr<const f32x4_u>)(q.irow + o);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool seen = kTabu == MMAS_TABU_COMPACT ? tabu[v[j]] > v[j] : (int)tabu[n + v[j]] >= L;
-                ok[j] = ok[j] & !seen;
-                f[j] = factor(v[j]);
+                for (int j = 0; j < 4; ++j) f[j] = r[j];
+            } else {
+                const i32x4_u r = *(GlbPtr<const i32x4_u>)(q.drow + o);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f[j] = powi((float)r[j], q.beta) * scale;
             }
-            const Words4 blk = draw_block(seed, it, ant, step, (uint32_t)(4 * b));
+        } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float key = log_u01(u01(blk.w[j])) * f[j];
-                keep_best(ok[j] ? ord_key(key) : 0u, v[j], bcode, bnode);
+                const bool in = o + j >= 0 && o + j < n;
+                const uint32_t v = in ? (uint32_t)(o + j) : 0u;
+                live[j] = (in & !fallback_seen<kTabu>(q, v)) ? ~0u : 0u;
+                f[j] = kPher == MMAS_PHER_DENSE ? q.irow[v] : powi((float)q.drow[v], q.beta) * scale;
             }
         }
-        return share_result(bcode, bnode);
+        const Words4 blk = draw_block(q.seed, q.it, q.ant, q.step, (uint32_t)(4 * b));
+        uint32_t code[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float key = log2_draw(blk.w[j]) * f[j];
+            code[j] = ((~__float_as_uint(key) & ~3u) | (uint32_t)j) & live[j];
+        }
+        uint32_t t1, t2;
+        top_two(code[0], code[1], code[2], code[3], t1, t2);
+        nb.m2 = max(max(nb.m2, t2), min(nb.m1, t1));
+        best_b = t1 > nb.m1 ? b : best_b;
+        nb.m1 = max(nb.m1, t1);
     }
-    // By list entries (the tabu's list of the L unvisited cities), in chunks
-    // of 64: this part takes chunks part, part + parts, ...
-    const int c0 = part, cs = parts;
-    // U chunks a round (U <= 4): the factor loads go out before the draws
-    // and their logarithms
-    auto key_round = [&](auto u_tag, int c) {
+    nb.node = (uint32_t)(4 * best_b - cl) + (nb.m1 & 3u);
+}
+
+template <int kPher>
+__device__ __forceinline__ void near_list(const Fallback& q, LdsPtr<const uint16_t> list, int part, int parts, int lane,
+                                          NearBest& nb) {
+    const float scale = near_scale<kPher>(q);
+    const int L = q.L;
+    // U rounds at once: the factor loads go out before the draws
+    auto rounds = [&](auto u_tag, int base) {
         constexpr int U = decltype(u_tag)::value;
         uint32_t v[U];
         float f[U];
         bool ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = (c + u * cs) * kWave + lane;
+            const int i = base + u * parts * kWave + lane;
             ok[u] = i < L;
             v[u] = list[ok[u] ? i : 0];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) f[u] = factor(v[u]);
+        for (int u = 0; u < U; ++u)
+            f[u] = kPher == MMAS_PHER_DENSE ? q.irow[v[u]] : powi((float)q.drow[v[u]], q.beta) * scale;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t slot = (uint32_t)cl + v[u];
-            const Words4 blk = draw_block(seed, it, ant, step, slot);
-            const float key = log_u01(u01(pick_word(blk, slot & 3u))) * f[u];
-            const uint32_t code = ok[u] ? ord_key(key) : 0u;
-            keep_best(code, v[u], bcode, bnode);
+            const uint32_t slot = (uint32_t)q.cl + v[u];
+            const Words4 blk = draw_block(q.seed, q.it, q.ant, q.step, slot);
+            const float key = log2_draw(pick_word(blk, slot & 3u)) * f[u];
+            const uint32_t code = ok[u] ? ~__float_as_uint(key) : 0u;
+            nb.m2 = med3(nb.m1, nb.m2, code);
+            nb.node = code > nb.m1 ? v[u] : nb.node;
+            nb.m1 = max(nb.m1, code);
         }
     };
-    const int chunks = (L + kWave - 1) / kWave;
-    int left = chunks > c0 ? (chunks - c0 + cs - 1) / cs : 0;  // this part's chunks
-    int c = c0;
-    for (; left >= 4; left -= 4, c += 4 * cs) key_round(std::integral_constant<int, 4>{}, c);
-    if (left == 3)
-        key_round(std::integral_constant<int, 3>{}, c);
-    else if (left == 2)
-        key_round(std::integral_constant<int, 2>{}, c);
-    else if (left == 1)
-        key_round(std::integral_constant<int, 1>{}, c);
-    return share_result(bcode, bnode);
+    int base = part * kWave;
+    const int span = parts * kWave;
+    for (; base + span < L; base += 2 * span) rounds(std::integral_constant<int, 2>{}, base);
+    if (base < L) rounds(std::integral_constant<int, 1>{}, base);
+}
+
+// A wave's share of a fallback as one word, the larger the better: its best
+// code, the city and (bit 0) whether the wave cannot tell its best for sure;
+// 0 if it saw no city.
+template <int kPher>
+__device__ __forceinline__ unsigned long long near_share(const Fallback& q, const NearBest& nb) {
+    constexpr uint32_t kM = kPher == MMAS_PHER_DENSE ? kNear : kNearPow;
+    const uint32_t best = wave_max_bcast(nb.m1);
+    if (best == 0u) return 0ull;
+    const uint32_t near = near_code<kM>(best);
+    const uint64_t tied = __ballot(nb.m1 >= near);
+    bool clear = ((tied & (tied - 1)) == 0ull) & (__ballot(nb.m2 >= near) == 0ull);
+    if (kPher == MMAS_PHER_CANDIDATES) clear &= (best >= kHuge) & (q.tmin_a <= 1.0f);
+    const uint32_t node = (uint32_t)__builtin_amdgcn_readlane((int)nb.node, (int)__builtin_ctzll(tied));
+    return ((unsigned long long)best << 32) | (unsigned long long)(node << 1) | (unsigned long long)(clear ? 0u : 1u);
+}
+
+// The better of two shares; unclear if they nearly tie.
+template <int kPher>
+__device__ __forceinline__ unsigned long long near_better(unsigned long long a, unsigned long long b) {
+    constexpr uint32_t kM = kPher == MMAS_PHER_DENSE ? kNear : kNearPow;
+    const unsigned long long hi = a > b ? a : b, lo = a > b ? b : a;
+    if ((uint32_t)(hi >> 32) == 0u) return 0ull;
+    return hi | ((uint32_t)(lo >> 32) >= near_code<kM>((uint32_t)(hi >> 32)) ? 1ull : 0ull);
+}
+
+// Part `part` of `parts` of a fallback whose tabu keeps the list of unvisited
+// cities (compact, list): the cheaper layout by instruction count.
+template <int kTabu, int kPher>
+__device__ __forceinline__ unsigned long long near_part(const Fallback& q, int part, int parts, int lane) {
+    static_assert(kTabu != MMAS_TABU_BITMASK, "the tabu keeps the list of unvisited cities");
+    const int nb_ = ((q.cl + q.n - 1) >> 2) - (q.cl >> 2) + 1, span = kWave * parts;
+    NearBest nb;
+    if (85 * ((nb_ + span - 1) / span) < 58 * ((q.L + span - 1) / span))
+        near_blocks<kTabu, kPher>(q, part, parts, lane, nb);
+    else
+        near_list<kPher>(q, q.tabu, part, parts, lane, nb);
+    return near_share<kPher>(q, nb);
+}
+
+// The fallback's arguments read back into scalar registers (an outlined
+// function gets them in vector registers).
+__device__ __forceinline__ Fallback uni(const Fallback& v) {
+    Fallback q;
+    q.tabu = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)v.tabu);
+    q.L = uni(v.L);
+    q.n = uni(v.n);
+    q.cl = uni(v.cl);
+    q.beta = uni(v.beta);
+    q.irow = (GlbPtr<const float>)uni((uint64_t)(uintptr_t)v.irow);
+    q.drow = (GlbPtr<const int32_t>)uni((uint64_t)(uintptr_t)v.drow);
+    q.tmin_a = uni(v.tmin_a);
+    q.seed = uni(v.seed);
+    q.it = uni(v.it);
+    q.ant = uni(v.ant);
+    q.step = uni(v.step);
+    return q;
+}
+
+// The all-city fallback of one wave, outlined (it is rare with a list, and one
+// copy serves every step of the unrolled step loop). By draw blocks or by
+// list, the cheaper by instruction count (listing a bitmask's cities costs
+// about 140); a bitmask's list must fit in `cap` entries at `list`.
+// At n = 1002 a tour has about 35 fallbacks over about 200 cities.
+template <int kTabu, int kPher>
+__device__ __attribute__((noinline)) uint32_t fallback_lone(Fallback qv, LdsPtr<uint16_t> list_v, int cap_v, int lane) {
+    constexpr bool kList = kTabu != MMAS_TABU_BITMASK;
+    Fallback q = uni(qv);
+    unsigned long long r;
+    if constexpr (kList) {
+        r = near_part<kTabu, kPher>(q, 0, 1, lane);
+    } else {
+        const LdsPtr<uint16_t> list = (LdsPtr<uint16_t>)uni((uint32_t)(uintptr_t)list_v);
+        const int cap = uni(cap_v), n = q.n;
+        const int nblk = ((q.cl + n - 1) >> 2) - (q.cl >> 2) + 1;
+        NearBest nb;
+        if (q.L > cap || 85 * ((nblk + kWave - 1) / kWave) < 58 * ((q.L + kWave - 1) / kWave) + 140) {
+            near_blocks<kTabu, kPher>(q, 0, 1, lane, nb);
+        } else {
+            // every unvisited city in ascending order, lane l taking 16-bit
+            // halves l, l + 64, ... of the bitmask, so that a lane writes at
+            // most 16 entries
+            const int nh = (n + 15) >> 4;
+            int L = 0;
+            for (int h0 = 0; h0 < nh; h0 += kWave) {
+                const int hi = h0 + lane;
+                uint32_t fr = 0u;
+                if (hi < nh) {
+                    fr = ~(uint32_t)q.tabu[hi] & 0xFFFFu;
+                    if (hi == nh - 1 && (n & 15)) fr &= (1u << (n & 15)) - 1u;
+                }
+                const int cnt = __popc(fr);
+                const int incl = wave_incl_scan(cnt, lane);
+                int p = L + incl - cnt;
+                while (fr) {
+                    const int b = __ffs(fr) - 1;
+                    fr &= fr - 1u;
+                    list[p++] = (uint16_t)(hi * 16 + b);
+                }
+                L += __builtin_amdgcn_readlane(incl, 63);
+            }
+            q.L = L;
+            near_list<kPher>(q, list, 0, 1, lane, nb);
+        }
+        r = near_share<kPher>(q, nb);
+    }
+    if (__builtin_expect((r & 1ull) == 0ull && r != 0ull, 1)) return (uint32_t)r >> 1;
+    return fallback_exact<kTabu, kPher>(q, lane);
+}
+
+// Part `part` of two of a fallback (compact tabu, the ant's wave and its draw
+// helper), as near_share packs it.
+template <int kTabu, int kPher>
+__device__ __attribute__((noinline)) unsigned long long fallback_half(Fallback qv, int part_v, int lane) {
+    const Fallback q = uni(qv);
+    return near_part<kTabu, kPher>(q, uni(part_v), 2, lane);
+}
+
+// The exact choice of a candidate step whose approximate keys nearly tie:
+// lane r holds rank r (city `node`, factor w, `live` ~0 or 0) of the list of
+// the ant that its half (or the whole wave) serves, and draws slot r. Returns
+// this lane's exact code.
+__device__ __attribute__((noinline)) uint32_t step_exact_code(uint64_t seed, uint32_t it, uint32_t ant, uint32_t k,
+                                                              uint32_t rank, float w, uint32_t live) {
+    const Words4 blk = draw_block(seed, it, ant, k, rank);
+    const float key = log_u01(u01(pick_word(blk, rank & 3u))) * w;
+    return ~__float_as_uint(key) & live;
 }
 
 // ---- several waves per ant: the fallback shared by the workgroup ----------
@@ -546,14 +539,18 @@ __device__ __attribute__((noinline)) unsigned long long fallback_half(
 struct __align__(16) WideStep {
     int k;               // the step that needs the fallback
     uint32_t cur;        // current city
-    int L;               // compact and list tabus: unvisited count
+    int L;               // unvisited count
     int stop;            // the tour is done: every wave leaves
 };
+// Instructions of one wave for gathering a bitmask's cities in a workgroup
+// (the words' bits, an LDS atomic and a barrier), against keying rounds.
+constexpr int kGatherCost = 300;
+
 struct WideLds {
     WideStep step;       // written by the leading wave before the first barrier
                          // of a fallback, read by all after it
     uint32_t counter;    // bitmask tabu: list fill counter
-    unsigned long long res[16];  // per wave: (key code << 32) | ~city, 0 = none
+    unsigned long long res[16];  // per wave: its near_share
 };
 
 // The unvisited cities of a bitmask tabu gathered by the whole workgroup
@@ -586,64 +583,6 @@ __device__ void gather_unvisited_block(const BitmaskTabu& tabu, int n, uint16_t*
 }
 
 
-// This wave's share of a workgroup-wide fallback (entries wave*64 + lane,
-// then every 64*waves): its best (key code, lowest city), packed so that the
-// larger value is the better one; 0 if the wave saw no city.
-template <class F>
-__device__ __forceinline__ unsigned long long fallback_share(const uint16_t* list, int L, const F& factor, int cl, uint64_t seed,
-                                             uint32_t it, uint32_t ant, uint32_t step, int lane, int wv, int nw) {
-    uint32_t bcode = 0u, bnode = kNone;
-    const int stride = kWave * nw;
-    for (int base = wv * kWave; base < L; base += 4 * stride) {
-        uint32_t v[4];
-        float f[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + u * stride + lane;
-            v[u] = i < L ? (uint32_t)list[i] : kNone;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) f[u] = v[u] != kNone ? factor(v[u]) : 1.0f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (v[u] == kNone) continue;
-            const uint32_t slot = (uint32_t)cl + v[u];
-            const Words4 blk = draw_block(seed, it, ant, step, slot);
-            const float key = log_u01(u01(pick_word(blk, slot & 3u))) * f[u];
-            keep_best(ord_key(key), v[u], bcode, bnode);
-        }
-    }
-    return share_result(bcode, bnode);
-}
-
-// The same share laid out by draw blocks instead of list entries: a lane
-// takes the block of slots 4b .. 4b+3 (b from the first block holding slot
-// cl, wave*64 + lane, then every 64*waves), computes that Philox block once
-// and keys each of its cities (slot - cl) that is unvisited. While most
-// cities are unvisited this needs a quarter of the blocks of the list layout;
-// the keys, and so the winner, are the same.
-template <class T, class F>
-__device__ __forceinline__ unsigned long long fallback_share_blocks(const T& tabu, int n, const F& factor, int cl,
-                                                                    uint64_t seed, uint32_t it, uint32_t ant,
-                                                                    uint32_t step, int lane, int wv, int nw) {
-    uint32_t bcode = 0u, bnode = kNone;
-    const int b_lo = cl >> 2, b_hi = (cl + n - 1) >> 2;  // blocks holding slots cl .. cl + n - 1
-    for (int b0 = b_lo + wv * kWave; b0 <= b_hi; b0 += kWave * nw) {
-        const int b = b0 + lane;
-        if (b <= b_hi) {
-            const Words4 blk = draw_block(seed, it, ant, step, (uint32_t)(4 * b));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int v = 4 * b + j - cl;
-                if (v < 0 || v >= n || tabu.visited((uint32_t)v)) continue;
-                const float key = log_u01(u01(blk.w[j])) * factor((uint32_t)v);
-                keep_best(ord_key(key), (uint32_t)v, bcode, bnode);
-            }
-        }
-    }
-    return share_result(bcode, bnode);
-}
-
 // LDS layout of one workgroup: the candidate table of cities 0..R-1 (ids,
 // then choice_info), then one region per ant (its draws, its tabu and, for
 // the bitmask, room to list the unvisited cities during a fallback).
@@ -665,35 +604,53 @@ __device__ void stage_table(const Views& vw, int cl, int R, uint16_t* tcand, flo
     }
 }
 
+// The arguments of an all-city fallback at step k from city cur with L
+// unvisited cities, over `tabu` (the bitmask's words, or the other tabus' list).
+template <int kPher>
+__device__ __forceinline__ Fallback fallback_args(const Views& vw, const Shape& s, uint32_t it, uint32_t ant, int k,
+                                                  uint32_t cur, int L, const void* tabu, float tmin_a) {
+    Fallback q;
+    // (C-style casts: the only casts that change the address space)
+    q.tabu = (LdsPtr<const uint16_t>)tabu;
+    q.L = L;
+    q.n = s.n;
+    q.cl = s.cl;
+    q.beta = s.beta;
+    q.irow = kPher == MMAS_PHER_DENSE ? (GlbPtr<const float>)(vw.choice_inv + (size_t)cur * s.n) : nullptr;
+    q.drow = kPher == MMAS_PHER_DENSE ? nullptr : (GlbPtr<const int32_t>)(vw.dist + (size_t)cur * s.n);
+    q.tmin_a = tmin_a;
+    q.seed = s.seed;
+    q.it = it;
+    q.ant = ant;
+    q.step = (uint32_t)k;
+    return q;
+}
+__device__ __forceinline__ const void* fallback_tabu(const BitmaskTabu& t) { return t.bits; }
+__device__ __forceinline__ const void* fallback_tabu(const CompactTabu& t) { return t.entries; }
+__device__ __forceinline__ const void* fallback_tabu(const ListTabu& t) { return t.unv; }
+
 // One wave's share of a workgroup-wide fallback at step k from city fcur
-// (the bitmask tabu's unvisited cities are first gathered by the whole
-// workgroup, with a barrier): the wave's best (key code, ~city), 0 if none.
+// (near_share). A bitmask's unvisited cities are gathered by the whole
+// workgroup first, with a barrier, unless keying by draw blocks is cheaper.
 template <int kTabu, int kPher, class T>
 __device__ unsigned long long wide_share(const Views& vw, const Shape& s, uint32_t it, int ant, int k, uint32_t fcur,
                                          int L, T& tabu, uint16_t* ulist, WideLds* wl, float tmin_a, int lane, int wv,
                                          int nw) {
-    const int n = s.n, cl = s.cl;
-    const uint16_t* list;
+    Fallback q = fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, fcur, L, fallback_tabu(tabu), tmin_a);
     if constexpr (kTabu == MMAS_TABU_BITMASK) {
-        gather_unvisited_block(tabu, n, ulist, &wl->counter);
-        __syncthreads();
-        L = __builtin_amdgcn_readfirstlane((int)wl->counter);
-        list = ulist;
+        NearBest nb;
+        const int nblk = ((q.cl + q.n - 1) >> 2) - (q.cl >> 2) + 1, span = kWave * nw;
+        if (85 * ((nblk + span - 1) / span) < 58 * ((L + span - 1) / span) + kGatherCost) {
+            near_blocks<kTabu, kPher>(q, wv, nw, lane, nb);
+        } else {
+            gather_unvisited_block(tabu, s.n, ulist, &wl->counter);
+            __syncthreads();
+            q.L = __builtin_amdgcn_readfirstlane((int)wl->counter);
+            near_list<kPher>(q, (LdsPtr<const uint16_t>)ulist, wv, nw, lane, nb);
+        }
+        return near_share<kPher>(q, nb);
     } else {
-        list = tabu.list();
-        if constexpr (kTabu == MMAS_TABU_LIST) tabu.L = L;  // the helpers' copy of the length
-    }
-    // by draw blocks while they are cheaper: a block costs about a Philox
-    // and four keys, a listed city a Philox and one key
-    const bool by_blocks = kTabu != MMAS_TABU_BITMASK && 46 * L > 25 * n;
-    if constexpr (kPher == MMAS_PHER_DENSE) {
-        const DenseFactor wt{vw.choice_inv + (size_t)fcur * n};
-        return by_blocks ? fallback_share_blocks(tabu, n, wt, cl, s.seed, it, (uint32_t)ant, (uint32_t)k, lane, wv, nw)
-                         : fallback_share(list, L, wt, cl, s.seed, it, (uint32_t)ant, (uint32_t)k, lane, wv, nw);
-    } else {
-        const CandFactor wt{vw.dist + (size_t)fcur * n, tmin_a, s.beta};
-        return by_blocks ? fallback_share_blocks(tabu, n, wt, cl, s.seed, it, (uint32_t)ant, (uint32_t)k, lane, wv, nw)
-                         : fallback_share(list, L, wt, cl, s.seed, it, (uint32_t)ant, (uint32_t)k, lane, wv, nw);
+        return near_part<kTabu, kPher>(q, wv, nw, lane);
     }
 }
 
@@ -724,38 +681,37 @@ __device__ void wide_helpers(const Views& vw, const Shape& s, uint32_t it, int a
 
 // The leading wave's side of a workgroup-wide fallback at step k from city
 // cur: posts it, keys its share with the helpers, and takes the best over
-// the waves (the largest key code, then the lowest city); kNone if none.
+// the waves (a near tie it settles by the exact keys alone); kNone if none.
 template <int kTabu, int kPher, class T>
 __device__ uint32_t wide_lead_fallback(const Views& vw, const Shape& s, uint32_t it, int ant, int k, uint32_t cur,
                                        T& tabu, uint16_t* ulist, WideLds* wl, float tmin_a, int lane, int nw) {
+    const int L = s.n - k;  // unvisited cities
     if (lane == 0) {
         WideStep st;
         st.k = k;
         st.cur = cur;
-        st.L = 0;
-        if constexpr (kTabu != MMAS_TABU_BITMASK) st.L = tabu.L;
+        st.L = L;
         st.stop = 0;
         wl->step = st;
         if constexpr (kTabu == MMAS_TABU_BITMASK) wl->counter = 0u;
     }
     __syncthreads();
-    int L = 0;
-    if constexpr (kTabu != MMAS_TABU_BITMASK) L = tabu.L;
     const unsigned long long mine = wide_share<kTabu, kPher>(vw, s, it, ant, k, cur, L, tabu, ulist, wl, tmin_a, lane, 0, nw);
     if (lane == 0) wl->res[0] = mine;
     __syncthreads();
     // (the record, the counter and the list are read before the second
     // barrier; res is written again only after the next fallback's first)
     const unsigned long long r = lane < nw ? wl->res[lane] : 0ull;
+    constexpr uint32_t kM = kPher == MMAS_PHER_DENSE ? kNear : kNearPow;
     const uint32_t hi = (uint32_t)(r >> 32), lo = (uint32_t)r;
-    const uint32_t mx = wave_max_u32<2>(hi);
-    uint32_t best_lo;
-    const uint64_t tied = __ballot(hi == mx && lane < nw);
-    if (__popcll(tied) == 1)
-        best_lo = (uint32_t)__builtin_amdgcn_readlane((int)lo, __ffsll((unsigned long long)tied) - 1);
-    else
-        best_lo = wave_max_u32<2>(hi == mx ? lo : 0u);
-    return mx ? ~best_lo : kNone;
+    const uint32_t near = near_code<kM>(wave_max_u32<2>(hi));
+    const uint64_t tied = __ballot(hi >= near);
+    if (__builtin_expect(__popcll(tied) == 1, 1)) {
+        const uint32_t pick = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)__builtin_ctzll(tied));
+        if (__builtin_expect((pick & 1u) == 0u, 1)) return pick >> 1;
+    }
+    return fallback_exact<kTabu, kPher>(
+        fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, cur, L, fallback_tabu(tabu), tmin_a), lane);
 }
 
 // The end of the leading wave's tour: the helpers leave.
@@ -793,7 +749,7 @@ struct HelpLds {
     uint32_t cur;            // current city,
     int L;                   // unvisited cities,
     int stop;                // and 1 once the tour is done (the helper leaves)
-    unsigned long long res;  // part 1's best (share_result) of fallback `done`
+    unsigned long long res;  // part 1's best (near_share) of fallback `done`
     int pad[2];              // (to 48 bytes)
 };
 static_assert(sizeof(HelpLds) == 48, "16-byte multiple");
@@ -831,15 +787,8 @@ template <int kTabu, int kPher, class T>
 __device__ __forceinline__ unsigned long long half_part(const Views& vw, const Shape& s, uint32_t it, int ant, int k,
                                                         uint32_t cur, int L, const T& tabu, float tmin_a, int part,
                                                         int lane) {
-    const int n = s.n;
-    // (C-style casts: the only casts that change the address space)
-    const GlbPtr<const float> irow =
-        kPher == MMAS_PHER_DENSE ? (GlbPtr<const float>)(vw.choice_inv + (size_t)cur * n) : nullptr;
-    const GlbPtr<const int32_t> drow =
-        kPher == MMAS_PHER_DENSE ? nullptr : (GlbPtr<const int32_t>)(vw.dist + (size_t)cur * n);
-    const LdsPtr<const uint16_t> lv = (LdsPtr<const uint16_t>)tabu.list();
-    return fallback_half<kTabu, kPher>(lv, lv, L, n, irow, drow, tmin_a, s.beta, s.cl, s.seed, it, (uint32_t)ant,
-                                       (uint32_t)k, part, 2, lane);
+    return fallback_half<kTabu, kPher>(
+        fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, cur, L, fallback_tabu(tabu), tmin_a), part, lane);
 }
 
 // The helper wave of ant `ant`: `region` is the ant's region (draw buffer 0
@@ -980,10 +929,10 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
                 const int ks = k + (lane >> gsh);
                 const Words4 b = draw_block(seed, it, (uint32_t)ant, (uint32_t)ks, (uint32_t)(4 * (lane & (G - 1))));
                 float4 lv;
-                lv.x = log_u01(u01(b.w[0]));
-                lv.y = log_u01(u01(b.w[1]));
-                lv.z = log_u01(u01(b.w[2]));
-                lv.w = log_u01(u01(b.w[3]));
+                lv.x = log2_draw(b.w[0]);
+                lv.y = log2_draw(b.w[1]);
+                lv.z = log2_draw(b.w[2]);
+                lv.w = log2_draw(b.w[3]);
                 *reinterpret_cast<float4*>(lnbuf + 4 * lane) = lv;
             }
             // branch-free: every lane of the list computes its key; visited
@@ -995,28 +944,28 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
             float key = lnu * w;  // (w holds 1 / choice_info)
             asm volatile("" : "+v"(key));
             const bool live = (lane < cl) & !seen;  // no short circuit: no exec mask
-            const uint32_t code = live ? ord_key(key) : 0u;
+            // (approximate keys: device.hpp)
+            const uint32_t code = live ? ~__float_as_uint(key) : 0u;
             // (all four rows even for cl <= 32: lanes past the list hold no key,
             // and one code path is faster than two)
-            next = wave_select_step<4>(code, node);
+            const uint32_t best = wave_max_u32<4>(code);
+            if (best != 0u) {
+                const uint64_t tied = __ballot(code >= near_code(best));
+                next = (uint32_t)__builtin_amdgcn_readlane((int)node, (int)__builtin_ctzll(tied));
+                if (__builtin_expect((tied & (tied - 1)) != 0ull, 0)) {
+                    const uint32_t c = step_exact_code(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)lane, w,
+                                                       live ? ~0u : 0u);
+                    const uint32_t top = wave_max_u32<4>(c);
+                    next = wave_min_u32<4>(c == top ? node : kNone);
+                }
+            }
         }
         if (next == kNone) {
             fb_steps += 1;
             fb_nodes += n - k;
-            const int cap = list_cap(s);
-            if constexpr (kPher == MMAS_PHER_DENSE) {
-                const DenseFactor wt{vw.choice_inv + (size_t)cur * n};
-                if constexpr (kTabu == MMAS_TABU_BITMASK)
-                    next = fallback_bitmask(tabu, n, ulist, cap, wt, cl, seed, it, (uint32_t)ant, (uint32_t)k, lane);
-                else
-                    next = fallback_list(tabu.list(), tabu.L, wt, cl, seed, it, (uint32_t)ant, (uint32_t)k, lane);
-            } else {
-                const CandFactor wt{dist + (size_t)cur * n, tmin_a, s.beta};
-                if constexpr (kTabu == MMAS_TABU_BITMASK)
-                    next = fallback_bitmask(tabu, n, ulist, cap, wt, cl, seed, it, (uint32_t)ant, (uint32_t)k, lane);
-                else
-                    next = fallback_list(tabu.list(), tabu.L, wt, cl, seed, it, (uint32_t)ant, (uint32_t)k, lane);
-            }
+            next = fallback_lone<kTabu, kPher>(
+                fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, cur, n - k, fallback_tabu(tabu), tmin_a),
+                (LdsPtr<uint16_t>)ulist, list_cap(s), lane);
         }
         if (next >= (uint32_t)n) {
             // unreachable with a validated instance (some unvisited city always
@@ -1067,6 +1016,9 @@ template <int kTabu, int kPher, int kRows, int kG, bool kWide = false, bool kHel
 __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int ant, int lane, uint8_t* region,
                                const uint16_t* tcand, const float* tchc, int R, WideLds* wl = nullptr,
                                int nw = 1, uint8_t* help = nullptr) {
+    // the draws' logarithms: approximate where this wave computes them, exact
+    // from the draw helper (whose time is not on the ant's chain)
+    constexpr bool kApprox = !kHelp;
     const int n = s.n, cl = s.cl;
     const uint64_t seed = s.seed;
     float* lnbuf = reinterpret_cast<float*>(region);
@@ -1152,22 +1104,17 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
                     bad_help = true;
                     r1 = half_part<kTabu, kPher>(vw, s, it, ant, kk, (uint32_t)cur, L, tabu, tmin_a, 1, lane);
                 }
-                const unsigned long long r = r0 > r1 ? r0 : r1;
-                pick = r ? ~(uint32_t)r : kNone;
-            } else {
-                // (C-style casts: the only casts that change the address space)
-                const GlbPtr<const float> irow =
-                    kPher == MMAS_PHER_DENSE ? (GlbPtr<const float>)(vw.choice_inv + (size_t)cur * n) : nullptr;
-                const GlbPtr<const int32_t> drow =
-                    kPher == MMAS_PHER_DENSE ? nullptr : (GlbPtr<const int32_t>)(dist + (size_t)cur * n);
-                if constexpr (kTabu == MMAS_TABU_BITMASK)
-                    pick = fallback_lone<kTabu, kPher>((LdsPtr<const uint16_t>)tabu.bits, (LdsPtr<uint16_t>)ulist, L,
-                                                       n, irow, drow, tmin_a, s.beta, cl, seed, it, (uint32_t)ant,
-                                                       (uint32_t)k, lane);
+                const unsigned long long r = near_better<kPher>(r0, r1);
+                if (__builtin_expect((r & 1ull) == 0ull && r != 0ull, 1))
+                    pick = (uint32_t)r >> 1;
                 else
-                    pick = fallback_lone<kTabu, kPher>((LdsPtr<const uint16_t>)tabu.list(),
-                                                       (LdsPtr<uint16_t>)tabu.list(), L, n, irow, drow, tmin_a,
-                                                       s.beta, cl, seed, it, (uint32_t)ant, (uint32_t)k, lane);
+                    pick = fallback_exact<kTabu, kPher>(
+                        fallback_args<kPher>(vw, s, it, (uint32_t)ant, kk, (uint32_t)cur, L, fallback_tabu(tabu), tmin_a),
+                        lane);
+            } else {
+                pick = fallback_lone<kTabu, kPher>(
+                    fallback_args<kPher>(vw, s, it, (uint32_t)ant, kk, (uint32_t)cur, L, fallback_tabu(tabu), tmin_a),
+                    (LdsPtr<uint16_t>)ulist, list_cap(s), lane);
             }
         }
         const uint32_t next = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick);
@@ -1222,16 +1169,23 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
         float key = lnu * w;  // (w holds 1 / choice_info)
         asm volatile("" : "+v"(key));
         // ln(u) < 0 and w >= 0 give a key with the sign bit set (a negative
-        // number, -0 or -inf), whose order code is ~bits
+        // number, -0 or -inf), whose order code is ~bits (kApprox: the key is
+        // approximate, and the exact ones settle a near tie)
         const uint32_t code = ~__float_as_uint(key) & live & lane_ok;
         const uint32_t best = wave_max_u32<kRows>(code);
         uint32_t next = kNone;
         if (best != 0u) {
-            const uint64_t tied = __ballot(code == best);
+            const uint64_t tied = __ballot(code >= (kApprox ? near_code(best) : best));
             const int first = (int)__builtin_ctzll(tied);
             next = (uint32_t)__builtin_amdgcn_readlane((int)node, first);
-            if (__builtin_expect(first != 63 - (int)__builtin_clzll(tied), 0))
-                next = wave_min_u32<kRows>(code == best ? node : kNone);
+            if (__builtin_expect(first != 63 - (int)__builtin_clzll(tied), 0)) {
+                uint32_t c = code, top = best;
+                if constexpr (kApprox) {
+                    c = step_exact_code(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)lane, w, live & lane_ok);
+                    top = wave_max_u32<kRows>(c);
+                }
+                next = wave_min_u32<kRows>(c == top ? node : kNone);
+            }
         }
         if (__builtin_expect(next == kNone, 0)) next = fallback(k);
         load_row((int)next);
@@ -1261,10 +1215,10 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
         const Words4 b = draw_block(seed, it, (uint32_t)ant, (uint32_t)(k0 + (lane >> gsh)),
                                     (uint32_t)(4 * (lane & (G - 1))));
         float4 lv;
-        lv.x = log_u01(u01(b.w[0]));
-        lv.y = log_u01(u01(b.w[1]));
-        lv.z = log_u01(u01(b.w[2]));
-        lv.w = log_u01(u01(b.w[3]));
+        lv.x = log2_draw(b.w[0]);
+        lv.y = log2_draw(b.w[1]);
+        lv.z = log2_draw(b.w[2]);
+        lv.w = log2_draw(b.w[3]);
         *reinterpret_cast<float4*>(lnbuf + 4 * lane) = lv;
     };
 
@@ -1331,10 +1285,10 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
                         philox_rounds<6, 9>(c, k0s, k1s);
                     } else if (q == 3) {
                         philox_rounds<9, 10>(c, k0s, k1s);
-                        lv[0] = log_u01(u01(c.w[0]));
+                        lv[0] = log2_draw(c.w[0]);
                         asm volatile("" : "+v"(lv[0]));
                     } else if (q < 7) {
-                        lv[q - 3] = log_u01(u01(c.w[q - 3]));
+                        lv[q - 3] = log2_draw(c.w[q - 3]);
                         asm volatile("" : "+v"(lv[q - 3]));
                     }
                     if (q < 4) asm volatile("" : "+v"(c.w[0]), "+v"(c.w[1]), "+v"(c.w[2]), "+v"(c.w[3]));
@@ -1391,26 +1345,12 @@ __device__ __forceinline__ void half_min_u32(uint32_t x, uint32_t& lo, uint32_t&
 
 // The all-node fallback of one ant (whole wave), as in construct_ant.
 template <int kTabu, int kPher, class Tabu>
-__device__ uint32_t fallback_step(const Views& vw, const Shape& s, uint32_t it, uint32_t ant, uint32_t cur, int k,
-                                  const Tabu& tabu, uint8_t* region, float tmin_a, int lane) {
-    const int n = s.n;
-    if constexpr (kPher == MMAS_PHER_DENSE) {
-        const DenseFactor wt{vw.choice_inv + (size_t)cur * n};
-        if constexpr (kTabu == MMAS_TABU_BITMASK) {
-            uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((n + 31) / 32)));
-            return fallback_bitmask(tabu, n, ulist, list_cap(s), wt, s.cl, s.seed, it, ant, (uint32_t)k, lane);
-        } else {
-            return fallback_list(tabu.list(), tabu.L, wt, s.cl, s.seed, it, ant, (uint32_t)k, lane);
-        }
-    } else {
-        const CandFactor wt{vw.dist + (size_t)cur * n, tmin_a, s.beta};
-        if constexpr (kTabu == MMAS_TABU_BITMASK) {
-            uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((n + 31) / 32)));
-            return fallback_bitmask(tabu, n, ulist, list_cap(s), wt, s.cl, s.seed, it, ant, (uint32_t)k, lane);
-        } else {
-            return fallback_list(tabu.list(), tabu.L, wt, s.cl, s.seed, it, ant, (uint32_t)k, lane);
-        }
-    }
+__device__ __forceinline__ uint32_t fallback_step(const Views& vw, const Shape& s, uint32_t it, uint32_t ant,
+                                                  uint32_t cur, int k, const Tabu& tabu, uint8_t* region, float tmin_a,
+                                                  int lane) {
+    uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((s.n + 31) / 32)));
+    return fallback_lone<kTabu, kPher>(fallback_args<kPher>(vw, s, it, ant, k, cur, s.n - k, fallback_tabu(tabu), tmin_a),
+                                       (LdsPtr<uint16_t>)ulist, list_cap(s), lane);
 }
 
 // The visited test of a lane's candidate in a wave serving two ants: lane
@@ -1489,10 +1429,10 @@ __device__ void construct_pair(const Views& vw, const Shape& s, uint32_t it, int
         {
             const Words4 b = draw_block(seed, it, my_ant, (uint32_t)(k0 + (hl >> gsh)), (uint32_t)(4 * (hl & (G - 1))));
             float4 lv;
-            lv.x = log_u01(u01(b.w[0]));
-            lv.y = log_u01(u01(b.w[1]));
-            lv.z = log_u01(u01(b.w[2]));
-            lv.w = log_u01(u01(b.w[3]));
+            lv.x = log2_draw(b.w[0]);
+            lv.y = log2_draw(b.w[1]);
+            lv.z = log2_draw(b.w[2]);
+            lv.w = log2_draw(b.w[3]);
             *reinterpret_cast<float4*>(lnbuf + 4 * hl) = lv;
         }
         const int kb = k0 > 0 ? k0 : 1;
@@ -1521,15 +1461,18 @@ __device__ void construct_pair(const Views& vw, const Shape& s, uint32_t it, int
             const uint32_t code = ~__float_as_uint(key) & live & lane_ok;
             uint32_t bestA, bestB;
             half_max_u32(code, bestA, bestB);
-            const uint32_t best_l = h ? bestB : bestA;
-            const uint64_t tied = __ballot(code == best_l);
+            // (approximate keys: device.hpp; no code is near a best of 0)
+            const uint32_t near_l = h ? near_code(bestB) : near_code(bestA);
+            const uint64_t tied = __ballot(code >= near_l);
             const uint32_t tA = (uint32_t)tied, tB = (uint32_t)(tied >> 32);
             uint32_t nextA = kNone, nextB = kNone;
             if (bestA) nextA = (uint32_t)__builtin_amdgcn_readlane((int)node, __builtin_ctz(tA));
             if (bestB) nextB = (uint32_t)__builtin_amdgcn_readlane((int)node, 32 + __builtin_ctz(tB));
             if (__builtin_expect(((tA & (tA - 1)) | (tB & (tB - 1))) != 0, 0)) {
-                uint32_t mA, mB;
-                half_min_u32(((tied >> lane) & 1ull) ? node : kNone, mA, mB);
+                const uint32_t c = step_exact_code(seed, it, my_ant, (uint32_t)k, (uint32_t)hl, w, live & lane_ok);
+                uint32_t topA, topB, mA, mB;
+                half_max_u32(c, topA, topB);
+                half_min_u32(c == (h ? topB : topA) ? node : kNone, mA, mB);
                 if (bestA) nextA = mA;
                 if (bestB) nextB = mB;
             }
@@ -1670,15 +1613,6 @@ __global__ __launch_bounds__(1024) void k_construct_wide(Views vw, Shape s, uint
     }
     // the leading wave: the single-colony step, its fallbacks shared
     construct_lone<kTabu, kPher, kRows, kG, true>(vw, s, it, (int)blockIdx.x, lane, region, tcand, tchc, R, &wl, nw);
-}
-
-// The two largest of four codes (the second: a lane that holds two near the
-// wave's best has a near tie of its own).
-__device__ __forceinline__ void top_two(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t& m1,
-                                        uint32_t& m2) {
-    const uint32_t h01 = max(c0, c1), l01 = min(c0, c1), h23 = max(c2, c3), l23 = min(c2, c3);
-    m1 = max(h01, h23);
-    m2 = max(max(min(h01, h23), l01), l23);
 }
 
 // Without candidate lists, up to 4096 cities: a team of W waves per ant and no
