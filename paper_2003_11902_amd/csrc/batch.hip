@@ -95,8 +95,7 @@ mmas_status rebuild_tiles(mmas_batch* b) {
                                   hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return mmas::hip_fail(e, "tile table");
-    const int lds = b->table_bytes + b->ants_per_block * b->per_ant;
-    int g = mmas::batch_construct_grid(b->tabu, b->pher, b->ants_per_block, b->lanes_per_ant, lds);
+    int g = mmas::batch_construct_grid(b->tabu, b->pher, b->ants_per_block, b->lanes_per_ant, b->table_bytes, b->per_ant);
     if (g <= 0) return MMAS_EUNSUPPORTED;
     b->grid = std::min(g, b->ntiles);
     return MMAS_OK;

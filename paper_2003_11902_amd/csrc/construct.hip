@@ -30,6 +30,7 @@ template <class T>
 using LdsPtr = __attribute__((address_space(3))) T*;
 template <class T>
 using GlbPtr = __attribute__((address_space(1))) T*;
+__host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 // four consecutive row entries, aligned to one
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
@@ -47,10 +48,10 @@ struct BitmaskTabu {
         for (int w = lane; w < words; w += kWave) bits[w] = 0u;
     }
     __device__ __forceinline__ bool visited(uint32_t v) const { return (bits[v >> 5] >> (v & 31u)) & 1u; }
-    // ~0 if city v is unvisited, else 0 (a bit-field extract and a decrement)
-    __device__ __forceinline__ uint32_t live(uint32_t v) const {
+    // ~0 if city v is visited, else 0 (a signed bit-field extract)
+    __device__ __forceinline__ uint32_t seen(uint32_t v) const {
         const uint32_t word = bits[__builtin_amdgcn_ubfe(v, 5u, 11u)];
-        return __builtin_amdgcn_ubfe(word, v, 1u) - 1u;  // (the offset is taken mod 32)
+        return (uint32_t)__builtin_amdgcn_sbfe((int)word, v, 1u);  // (the offset is taken mod 32)
     }
     __device__ __forceinline__ void mark(uint32_t v, int lane) {
         if (lane == 0) atomicOr(&bits[v >> 5], 1u << (v & 31u));
@@ -76,7 +77,7 @@ struct CompactTabu {
         for (int i = lane; i < n_; i += kWave) entries[i] = (uint16_t)i;
     }
     __device__ __forceinline__ bool visited(uint32_t v) const { return entries[v] > v; }
-    __device__ __forceinline__ uint32_t live(uint32_t v) const { return entries[v] > v ? 0u : ~0u; }
+    __device__ __forceinline__ uint32_t seen(uint32_t v) const { return entries[v] > v ? ~0u : 0u; }
     __device__ __forceinline__ const uint16_t* list() const { return entries; }  // the L unvisited cities
     __device__ __forceinline__ void mark(uint32_t u, int lane) {
         // u is wave-uniform: both cells are read at once (the same for every
@@ -120,7 +121,7 @@ struct ListTabu {
         }
     }
     __device__ __forceinline__ bool visited(uint32_t v) const { return (int)idx[v] >= L; }
-    __device__ __forceinline__ uint32_t live(uint32_t v) const { return (int)idx[v] >= L ? 0u : ~0u; }
+    __device__ __forceinline__ uint32_t seen(uint32_t v) const { return (int)idx[v] >= L ? ~0u : 0u; }
     __device__ __forceinline__ const uint16_t* list() const { return unv; }
     __device__ __forceinline__ void mark(uint32_t u, int lane) {
         // every lane reads the same cells; lane 0 writes
@@ -230,6 +231,16 @@ __device__ __forceinline__ T* uni_ptr(T* p) {
     return reinterpret_cast<T*>(uni((uint64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
+
+// A kernel's instance, read through the constant address space (scalar loads):
+// an entry of the batch's array, or the first two arguments of a kernel that
+// serves one colony. Rare paths read what they need from it again instead of
+// keeping it in scalar registers all along.
+using ItemPtr = const __attribute__((address_space(4))) BatchItem*;
+__device__ __forceinline__ ItemPtr opaque(ItemPtr p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
 
 // What an all-city fallback of one ant needs, every value wave-uniform. The
 // tabu is the bitmask's words, the compact tabu's entries or the list tabu's
@@ -462,21 +473,18 @@ __device__ __forceinline__ Fallback uni(const Fallback& v) {
     return q;
 }
 
-// The all-city fallback of one wave, outlined (it is rare with a list, and one
-// copy serves every step of the unrolled step loop). By draw blocks or by
-// list, the cheaper by instruction count (listing a bitmask's cities costs
-// about 140); a bitmask's list must fit in `cap` entries at `list`.
-// At n = 1002 a tour has about 35 fallbacks over about 200 cities.
+// The all-city fallback of one wave: by draw blocks or by list, the cheaper by
+// instruction count (listing a bitmask's cities costs about 140); a bitmask's
+// list must fit in `cap` entries at `list`. At n = 1002 a tour has about 35
+// fallbacks over about 200 cities.
 template <int kTabu, int kPher>
-__device__ __attribute__((noinline)) uint32_t fallback_lone(Fallback qv, LdsPtr<uint16_t> list_v, int cap_v, int lane) {
+__device__ __forceinline__ uint32_t fallback_wave(Fallback q, LdsPtr<uint16_t> list, int cap, int lane) {
     constexpr bool kList = kTabu != MMAS_TABU_BITMASK;
-    Fallback q = uni(qv);
     unsigned long long r;
     if constexpr (kList) {
         r = near_part<kTabu, kPher>(q, 0, 1, lane);
     } else {
-        const LdsPtr<uint16_t> list = (LdsPtr<uint16_t>)uni((uint32_t)(uintptr_t)list_v);
-        const int cap = uni(cap_v), n = q.n;
+        const int n = q.n;
         const int nblk = ((q.cl + n - 1) >> 2) - (q.cl >> 2) + 1;
         NearBest nb;
         if (q.L > cap || 85 * ((nblk + kWave - 1) / kWave) < 58 * ((q.L + kWave - 1) / kWave) + 140) {
@@ -511,6 +519,13 @@ __device__ __attribute__((noinline)) uint32_t fallback_lone(Fallback qv, LdsPtr<
     }
     if (__builtin_expect((r & 1ull) == 0ull && r != 0ull, 1)) return (uint32_t)r >> 1;
     return fallback_exact<kTabu, kPher>(q, lane);
+}
+
+// ... outlined (it is rare with a list, and one copy serves every step of the
+// unrolled step loop).
+template <int kTabu, int kPher>
+__device__ __attribute__((noinline)) uint32_t fallback_lone(Fallback qv, LdsPtr<uint16_t> list_v, int cap_v, int lane) {
+    return fallback_wave<kTabu, kPher>(uni(qv), (LdsPtr<uint16_t>)uni((uint32_t)(uintptr_t)list_v), uni(cap_v), lane);
 }
 
 // Part `part` of two of a fallback (compact tabu, the ant's wave and its draw
@@ -591,8 +606,6 @@ struct Lds {
     int table_bytes;   // bytes of the table part (16-aligned)
     int per_ant;       // bytes of one ant's region
 };
-
-__host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 
 // The whole workgroup copies the first R rows of the candidate table (ids,
 // then the reciprocals of choice_info) into LDS; the caller synchronises.
@@ -1165,13 +1178,13 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
         const float w = w_next;
         mid();
         const float lnu = lds_ln[4 * j * G + ln_lane];
-        const uint32_t live = tabu.live(node);
+        const uint32_t seen = tabu.seen(node);
         float key = lnu * w;  // (w holds 1 / choice_info)
         asm volatile("" : "+v"(key));
         // ln(u) < 0 and w >= 0 give a key with the sign bit set (a negative
         // number, -0 or -inf), whose order code is ~bits (kApprox: the key is
         // approximate, and the exact ones settle a near tie)
-        const uint32_t code = ~__float_as_uint(key) & live & lane_ok;
+        const uint32_t code = ~__float_as_uint(key) & ~seen & lane_ok;
         const uint32_t best = wave_max_u32<kRows>(code);
         uint32_t next = kNone;
         if (best != 0u) {
@@ -1181,7 +1194,7 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
             if (__builtin_expect(first != 63 - (int)__builtin_clzll(tied), 0)) {
                 uint32_t c = code, top = best;
                 if constexpr (kApprox) {
-                    c = step_exact_code(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)lane, w, live & lane_ok);
+                    c = step_exact_code(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)lane, w, ~seen & lane_ok);
                     top = wave_max_u32<kRows>(c);
                 }
                 next = wave_min_u32<kRows>(c == top ? node : kNone);
@@ -1343,91 +1356,136 @@ __device__ __forceinline__ void half_min_u32(uint32_t x, uint32_t& lo, uint32_t&
     hi = min((uint32_t)__builtin_amdgcn_readlane((int)x, 32), (uint32_t)__builtin_amdgcn_readlane((int)x, 48));
 }
 
-// The all-node fallback of one ant (whole wave), as in construct_ant.
-template <int kTabu, int kPher, class Tabu>
-__device__ __forceinline__ uint32_t fallback_step(const Views& vw, const Shape& s, uint32_t it, uint32_t ant,
-                                                  uint32_t cur, int k, const Tabu& tabu, uint8_t* region, float tmin_a,
-                                                  int lane) {
-    uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((s.n + 31) / 32)));
-    return fallback_lone<kTabu, kPher>(fallback_args<kPher>(vw, s, it, ant, k, cur, s.n - k, fallback_tabu(tabu), tmin_a),
-                                       (LdsPtr<uint16_t>)ulist, list_cap(s), lane);
+// The all-node fallback of one ant on the whole wave (outlined: its arguments
+// are wave-uniform and arrive in vector registers).
+template <int kTabu, int kPher>
+__device__ __attribute__((noinline)) uint32_t fallback_item(ItemPtr item_v, LdsPtr<uint8_t> region_v, uint32_t it,
+                                                            uint32_t ant, int k_v, uint32_t cur_v, float tmin_a,
+                                                            int lane) {
+    const ItemPtr item = (ItemPtr)uni((uint64_t)(uintptr_t)item_v);
+    const uint32_t region = uni((uint32_t)(uintptr_t)region_v);
+    const int k = uni(k_v), n = item->s.n;
+    const size_t row = (size_t)uni(cur_v) * n;
+    Fallback q;
+    q.tabu = (LdsPtr<const uint16_t>)(region + (uint32_t)(kDrawBytes + kScratchBytes));
+    q.L = n - k;
+    q.n = n;
+    q.cl = item->s.cl;
+    q.beta = item->s.beta;
+    // (C-style casts: the only casts that change the address space)
+    q.irow = kPher == MMAS_PHER_DENSE ? (GlbPtr<const float>)(item->v.choice_inv + row) : nullptr;
+    q.drow = kPher == MMAS_PHER_DENSE ? nullptr : (GlbPtr<const int32_t>)(item->v.dist + row);
+    q.tmin_a = uni(tmin_a);
+    q.seed = item->s.seed;
+    q.it = uni(it);
+    q.ant = uni(ant);
+    q.step = (uint32_t)k;
+    const int cap = item->s.list_cap > 0 ? item->s.list_cap : (n < kListCap ? n : kListCap);
+    return fallback_wave<kTabu, kPher>(
+        q, (LdsPtr<uint16_t>)(region + (uint32_t)(kDrawBytes + kScratchBytes) + (uint32_t)align16(4 * ((n + 31) / 32))),
+        cap, lane);
 }
 
-// The visited test of a lane's candidate in a wave serving two ants: lane
-// half h reads the tabu of its own ant (~0 if unvisited, else 0).
-__device__ __forceinline__ uint32_t live_pair(const BitmaskTabu& a, const BitmaskTabu& b, int h, uint32_t v) {
-    const uint32_t* bits = h ? b.bits : a.bits;
-    return __builtin_amdgcn_ubfe(bits[v >> 5], v, 1u) - 1u;
+// The visited test of a lane's candidate in a wave serving two ants: half h
+// reads the tabu of its own ant, whose cells start at LDS byte `cells` (~0 if
+// visited, else 0).
+template <int kTabu>
+__device__ __forceinline__ uint32_t seen_pair(uint32_t cells, int n, int L, uint32_t v) {
+    if constexpr (kTabu == MMAS_TABU_BITMASK) {
+        const uint32_t word = *(LdsPtr<const uint32_t>)(cells + 4u * __builtin_amdgcn_ubfe(v, 5u, 11u));
+        return (uint32_t)__builtin_amdgcn_sbfe((int)word, v, 1u);
+    } else if constexpr (kTabu == MMAS_TABU_COMPACT) {
+        return *(LdsPtr<const uint16_t>)(cells + 2u * v) > v ? ~0u : 0u;
+    } else {
+        return (int)*(LdsPtr<const uint16_t>)(cells + 2u * ((uint32_t)n + v)) >= L ? ~0u : 0u;
+    }
 }
-__device__ __forceinline__ uint32_t live_pair(const CompactTabu& a, const CompactTabu& b, int h, uint32_t v) {
-    const uint16_t* e = h ? b.entries : a.entries;
-    return e[v] > v ? 0u : ~0u;
-}
-__device__ __forceinline__ uint32_t live_pair(const ListTabu& a, const ListTabu& b, int h, uint32_t v) {
-    const uint16_t* idx = h ? b.idx : a.idx;
-    const int L = h ? b.L : a.L;
-    return (int)idx[v] >= L ? 0u : ~0u;
-}
+__device__ __forceinline__ int pair_left(const BitmaskTabu&, const BitmaskTabu&, int) { return 0; }
+template <class T>
+__device__ __forceinline__ int pair_left(const T& a, const T& b, int h) { return h ? b.L : a.L; }
 
 // Two ants per wave64 (1 <= cl <= 32): lanes 0-31 serve ant `ant0`, lanes
-// 32-63 ant `ant0 + 1` (absent if !hasB). Both take their candidate steps
-// together: lane 32h + r holds rank r of ant h's current row, the keys and
-// the per-half argmax are those of construct_ant. A step in which an ant has
-// no unvisited candidate runs that ant's fallback on the whole wave. Same
-// draws, same arithmetic, same tours as one ant per wave. Laid out like the
-// single colony's step: both current cities wave-uniform, draws generated
-// once per group of steps, the visited test folded into the key code.
-template <int kTabu, int kPher>
-__device__ void construct_pair(const Views& vw, const Shape& s, uint32_t it, int ant0, bool hasB, int lane,
-                               uint8_t* regA, uint8_t* regB, const uint16_t* tcand, const float* tchc, int R) {
+// 32-63 ant `ant0 + 1` (without one, ant0 again in the second region, its
+// results not stored). Both take their candidate steps together: lane 32h + r
+// holds rank r of ant h's current row, the keys and the per-half argmax are
+// those of construct_ant. A step in which an ant has no unvisited candidate
+// runs that ant's fallback on the whole wave. Same draws, same choices, same
+// tours as one ant per wave. With eight waves on a SIMD the step is bound by
+// instruction issue, so what is wave-uniform (ant0, both cities, the
+// selection) stays in scalar registers and instructions, rows are addressed
+// by 32-bit offsets, and whatever only the rare paths need (a near tie, a
+// fallback) is read again there: about 47 vector instructions a step (75 with
+// the instance held in spilled scalar registers), 16 more for a quarter of the
+// draws' Philox block and logarithms. kTable: some rows are in LDS.
+template <int kTabu, int kPher, bool kTable>
+__device__ __forceinline__ void construct_pair(ItemPtr item, uint32_t it, int ant0, int lane, uint8_t* regA, uint8_t* regB,
+                               const uint16_t* tcand, const float* tchc, int R) {
     using Tabu = typename TabuOf<kTabu>::type;
-    const int n = s.n, cl = s.cl;
-    const uint64_t seed = s.seed;
+    const int n = item->s.n, cl = item->s.cl;
     const int h = lane >> 5, hl = lane & 31;
-    const uint32_t antA = (uint32_t)ant0, antB = (uint32_t)ant0 + 1u;
+    const bool hasB = ant0 + 1 < item->s.ants;
+    const uint32_t antA = (uint32_t)ant0, antB = hasB ? antA + 1u : antA;
     const uint32_t my_ant = h ? antB : antA;
 
     Tabu tabA, tabB;
     tabA.init(regA + kDrawBytes + kScratchBytes, n, lane);
     tabB.init(regB + kDrawBytes + kScratchBytes, n, lane);
     float* lnbuf = reinterpret_cast<float*>(h ? regB : regA);
+    const uint32_t cells = (uint32_t)(uintptr_t)(LdsPtr<float>)lnbuf + (uint32_t)(kDrawBytes + kScratchBytes);
 
     float tmin_a = 0.0f;
-    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(vw.state->tau_min, s.alpha);
+    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(item->v.state->tau_min, item->s.alpha);
     const LdsPtr<const uint16_t> lds_cand = (LdsPtr<const uint16_t>)tcand;
     const LdsPtr<const float> lds_chc = (LdsPtr<const float>)tchc;
-    const GlbPtr<const uint16_t> glb_cand = (GlbPtr<const uint16_t>)vw.cand;
-    const GlbPtr<const float> glb_chc = (GlbPtr<const float>)vw.chc_inv;  // reciprocals
+    const GlbPtr<const uint8_t> glb_cand = (GlbPtr<const uint8_t>)item->v.cand;
+    const GlbPtr<const uint8_t> glb_chc = (GlbPtr<const uint8_t>)item->v.chc_inv;  // reciprocals
+    uint32_t k0s = (uint32_t)item->s.seed, k1s = (uint32_t)(item->s.seed >> 32);
 
     // start cities: floor(x * n / 2^32) of draw (step 0, slot 0) of each ant
-    const uint32_t x0 = draw_block(seed, it, my_ant, 0u, 0u).w[0];
+    const uint32_t x0 = draw_block(item->s.seed, it, my_ant, 0u, 0u).w[0];
     const uint32_t st_l = (uint32_t)(((uint64_t)x0 * (uint64_t)n) >> 32);
     const int startA = __builtin_amdgcn_readlane((int)st_l, 0);
     const int startB = __builtin_amdgcn_readlane((int)st_l, 32);
     tabA.mark((uint32_t)startA, lane);
-    if (hasB) tabB.mark((uint32_t)startB, lane ^ 32);
+    tabB.mark((uint32_t)startB, lane ^ 32);
 
     // draws ahead, S = 32/G steps at a time, each half for its own ant
     const int gsh = cl <= 4 ? 0 : cl <= 8 ? 1 : cl <= 16 ? 2 : 3;
     const int G = 1 << gsh;
     const int S = 32 >> gsh;
     const int lr = hl < cl ? hl : cl - 1;
-    const uint32_t lane_ok = ((hl < cl) & (h == 0 || hasB)) ? ~0u : 0u;
-    const int ln_lane = hl & (4 * G - 1);
+    const uint32_t lane_ok = hl < cl ? ~0u : 0u;
+    const uint32_t ln_lane = (uint32_t)(uintptr_t)(LdsPtr<float>)lnbuf + 4u * (uint32_t)(hl & (4 * G - 1));
+    // bitmask marks, both in one LDS OR issued by every lane: lane 0 sets A's
+    // bit, lane 32 B's, the others OR zero into their own word of the draw
+    // buffer (a field of no bits gives them offset 0, and their "bit" is 0)
+    uint32_t mark_bits = hl == 0 ? 11u : 0u, mark_one = hl == 0 ? 1u : 0u;
+    uint32_t mark_base = hl == 0 ? cells : (uint32_t)(uintptr_t)(LdsPtr<float>)lnbuf + 4u * (uint32_t)hl;
+    asm volatile("" : "+v"(mark_bits), "+v"(mark_one), "+v"(mark_base));
 
-    uint16_t* tour_out = vw.tours + (size_t)my_ant * n;
-    const int32_t* dist = vw.dist;
-    const bool writer = h == 0 || hasB;
     uint32_t tbuf = (uint32_t)(h ? startB : startA);  // lane 32h + (k & 31) holds the city of step k
     uint32_t prev_last = 0;
     int64_t len = 0;
-    int64_t fbA_steps = 0, fbA_nodes = 0, fbB_steps = 0, fbB_nodes = 0;
+    uint32_t fbA_steps = 0, fbA_nodes = 0, fbB_steps = 0, fbB_nodes = 0;
     int curA = startA, curB = startB;
     bool bad = false;
 
+    // an ant without an unvisited candidate (no city at all is unreachable with
+    // a validated instance; were it so, report it after the tour and go on with
+    // city 0: the tour is void)
+    auto fallback = [&](uint32_t ant, int cur, int k, uint8_t* reg) -> uint32_t {
+        const uint32_t pick = (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)fallback_item<kTabu, kPher>(opaque(item), (LdsPtr<uint8_t>)reg, it, ant, k, (uint32_t)cur, tmin_a, lane));
+        bad |= pick >= (uint32_t)n;
+        return pick < (uint32_t)n ? pick : 0u;
+    };
+
     for (int k0 = 0; k0 < n; k0 += S) {
         {
-            const Words4 b = draw_block(seed, it, my_ant, (uint32_t)(k0 + (hl >> gsh)), (uint32_t)(4 * (hl & (G - 1))));
+            // (the round keys are formed anew: kept, they would be spilled)
+            asm volatile("" : "+s"(k0s), "+s"(k1s));
+            const Words4 b = philox4x32_10((uint32_t)(hl & (G - 1)) | ((uint32_t)(k0 + (hl >> gsh)) << 16), my_ant, it,
+                                           0u, k0s, k1s);
             float4 lv;
             lv.x = log2_draw(b.w[0]);
             lv.y = log2_draw(b.w[1]);
@@ -1438,86 +1496,81 @@ __device__ void construct_pair(const Views& vw, const Shape& s, uint32_t it, int
         const int kb = k0 > 0 ? k0 : 1;
         const int ke = k0 + S < n ? k0 + S : n;
         for (int k = kb; k < ke; ++k) {
-            const int cur_l = h ? curB : curA;
-            const int e = cur_l * cl + lr;
+            const uint32_t offA = (uint32_t)(curA * cl), offB = (uint32_t)(curB * cl);
+            const uint32_t e = (h ? offB : offA) + (uint32_t)lr;
             uint32_t node;
             float w;
-            if (R == 0) {
-                // no table (a wave-uniform test, so no exec-mask bookkeeping)
-                node = glb_cand[e];
-                w = glb_chc[e];
-            } else if (cur_l >= R) {
-                node = glb_cand[e];
-                w = glb_chc[e];
+            if constexpr (kTable) {
+                const int cur_l = h ? curB : curA;
+                if (cur_l >= R) {
+                    node = *(GlbPtr<const uint16_t>)(glb_cand + 2u * e);
+                    w = *(GlbPtr<const float>)(glb_chc + 4u * e);
+                } else {
+                    node = lds_cand[e];
+                    w = lds_chc[e];
+                }
             } else {
-                node = lds_cand[e];
-                w = lds_chc[e];
+                node = *(GlbPtr<const uint16_t>)(glb_cand + 2u * e);
+                w = *(GlbPtr<const float>)(glb_chc + 4u * e);
             }
-            const float lnu = lnbuf[4 * (k - k0) * G + ln_lane];
-            const uint32_t live = live_pair(tabA, tabB, h, node);
+            const float lnu = *(LdsPtr<const float>)(ln_lane + (uint32_t)(16 * (k - k0) * G));
+            const uint32_t seen = seen_pair<kTabu>(cells, n, pair_left(tabA, tabB, h), node);
             float key = lnu * w;  // (w holds 1 / choice_info)
             asm volatile("" : "+v"(key));
-            // ln(u) < 0 and w >= 0: the key's sign bit is set, its order code is ~bits
-            const uint32_t code = ~__float_as_uint(key) & live & lane_ok;
+            // log2(u) < 0 and w >= 0: the key's sign bit is set, its order code
+            // is ~bits (approximate keys: device.hpp)
+            const uint32_t code = ~__float_as_uint(key) & ~seen & lane_ok;
             uint32_t bestA, bestB;
             half_max_u32(code, bestA, bestB);
-            // (approximate keys: device.hpp; no code is near a best of 0)
-            const uint32_t near_l = h ? near_code(bestB) : near_code(bestA);
-            const uint64_t tied = __ballot(code >= near_l);
-            const uint32_t tA = (uint32_t)tied, tB = (uint32_t)(tied >> 32);
-            uint32_t nextA = kNone, nextB = kNone;
-            if (bestA) nextA = (uint32_t)__builtin_amdgcn_readlane((int)node, __builtin_ctz(tA));
-            if (bestB) nextB = (uint32_t)__builtin_amdgcn_readlane((int)node, 32 + __builtin_ctz(tB));
-            if (__builtin_expect(((tA & (tA - 1)) | (tB & (tB - 1))) != 0, 0)) {
-                const uint32_t c = step_exact_code(seed, it, my_ant, (uint32_t)k, (uint32_t)hl, w, live & lane_ok);
-                uint32_t topA, topB, mA, mB;
-                half_max_u32(c, topA, topB);
-                half_min_u32(c == (h ? topB : topA) ? node : kNone, mA, mB);
-                if (bestA) nextA = mA;
-                if (bestB) nextB = mB;
+            // (no code is near a best of 0)
+            const uint32_t tA = (uint32_t)__ballot(code >= near_code(bestA));
+            const uint32_t tB = (uint32_t)(__ballot(code >= near_code(bestB)) >> 32);
+            uint32_t nextA = (uint32_t)__builtin_amdgcn_readlane((int)node, __builtin_ctz(tA | 0x80000000u));
+            uint32_t nextB = (uint32_t)__builtin_amdgcn_readlane((int)node, 32 + __builtin_ctz(tB | 0x80000000u));
+            const int cntA = __builtin_popcount(tA), cntB = __builtin_popcount(tB);
+            if (__builtin_expect(((cntA ^ 1) | (cntB ^ 1)) != 0, 0)) {
+                if (cntA > 1 || cntB > 1) {
+                    const uint32_t c = step_exact_code(opaque(item)->s.seed, it, my_ant, (uint32_t)k, (uint32_t)hl, w,
+                                                       ~seen & lane_ok);
+                    uint32_t topA, topB, mA, mB;
+                    half_max_u32(c, topA, topB);
+                    half_min_u32(c == (h ? topB : topA) ? node : kNone, mA, mB);
+                    if (cntA > 1) nextA = mA;
+                    if (cntB > 1) nextB = mB;
+                }
+                if (cntA == 0) {
+                    fbA_steps += 1;
+                    fbA_nodes += (uint32_t)(n - k);
+                    nextA = fallback(antA, curA, k, regA);
+                }
+                if (cntB == 0) {
+                    fbB_steps += 1;
+                    fbB_nodes += (uint32_t)(n - k);
+                    nextB = fallback(antB, curB, k, regB);
+                }
             }
-            if (__builtin_expect(nextA == kNone, 0)) {
-                fbA_steps += 1;
-                fbA_nodes += n - k;
-                nextA = (uint32_t)__builtin_amdgcn_readfirstlane(
-                    (int)fallback_step<kTabu, kPher>(vw, s, it, antA, (uint32_t)curA, k, tabA, regA, tmin_a, lane));
-            }
-            if (!hasB) {
-                nextB = (uint32_t)curB;  // an absent second ant stays at its (valid) start city
-            } else if (__builtin_expect(nextB == kNone, 0)) {
-                fbB_steps += 1;
-                fbB_nodes += n - k;
-                nextB = (uint32_t)__builtin_amdgcn_readfirstlane(
-                    (int)fallback_step<kTabu, kPher>(vw, s, it, antB, (uint32_t)curB, k, tabB, regB, tmin_a, lane));
-            }
-            // no city is unreachable with a validated instance; were it not,
-            // report it after the tour and go on with city 0 (the tour is void)
-            bad |= (nextA >= (uint32_t)n) | (nextB >= (uint32_t)n);
-            nextA = nextA < (uint32_t)n ? nextA : 0u;
-            nextB = nextB < (uint32_t)n ? nextB : 0u;
+            const uint32_t nx = h ? nextB : nextA;
             if constexpr (kTabu == MMAS_TABU_BITMASK) {
-                // both marks in one LDS OR issued by every lane: lane 0 sets
-                // A's bit, lane 32 B's (when B is there), the others OR zero
-                // into their own word of the draw buffer
-                const uint32_t nx = h ? nextB : nextA;
-                const bool setter = hl == 0 && (h == 0 || hasB);
-                uint32_t* word = setter ? (h ? tabB.bits : tabA.bits) + (nx >> 5)
-                                        : reinterpret_cast<uint32_t*>(lnbuf) + hl;
-                atomicOr(word, setter ? 1u << (nx & 31u) : 0u);
+                const uint32_t addr = mark_base + 4u * __builtin_amdgcn_ubfe(nx, 5u, mark_bits);
+                __hip_atomic_fetch_or((LdsPtr<uint32_t>)(uintptr_t)addr, mark_one << (nx & 31u), __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
             } else {
                 tabA.mark(nextA, lane);
-                if (hasB) tabB.mark(nextB, lane ^ 32);
+                tabB.mark(nextB, lane ^ 32);
             }
-            if (hl == (k & 31)) tbuf = h ? nextB : nextA;
-            curA = __builtin_amdgcn_readfirstlane((int)nextA);
-            curB = __builtin_amdgcn_readfirstlane((int)nextB);
+            if (hl == (k & 31)) tbuf = nx;
+            curA = (int)nextA;
+            curB = (int)nextB;
         }
         if ((ke & 31) == 0 || ke == n) {
             // flush steps c0 .. ke - 1; lane 32h + l holds step c0 + l of ant h
             const int c0 = (ke - 1) & ~31;
             const int last = ke - 1 - c0;
+            const ItemPtr im = opaque(item);
+            uint16_t* tour_out = im->v.tours + (size_t)my_ant * n;
+            const int32_t* dist = im->v.dist;
             const uint32_t prev = __shfl_up(tbuf, 1);
-            if (hl <= last && writer) {
+            if (hl <= last && (h == 0 || hasB)) {
                 tour_out[c0 + hl] = (uint16_t)tbuf;
                 const uint32_t from = hl == 0 ? prev_last : prev;
                 if (c0 + hl > 0) len += dist[(size_t)from * n + tbuf];
@@ -1527,19 +1580,14 @@ __device__ void construct_pair(const Views& vw, const Shape& s, uint32_t it, int
             prev_last = h ? plB : plA;
         }
     }
-    if (bad && lane == 0) atomicOr(&vw.state->flags, 8u);
-    if (lane == 0) len += dist[(size_t)curA * n + startA];  // closing edges
-    if (lane == 32 && hasB) len += dist[(size_t)curB * n + startB];
+    const ItemPtr im = opaque(item);
+    if (bad && lane == 0) atomicOr(&im->v.state->flags, 8u);
+    if (hl == 0) len += im->v.dist[(size_t)(h ? curB : curA) * n + (h ? startB : startA)];  // closing edges
     for (int o = 16; o >= 1; o >>= 1) len += __shfl_xor(len, o);
-    if (lane == 0) {
-        vw.lengths[antA] = len;
-        vw.fallback[antA] = fbA_steps;
-        vw.fallback[s.ants + antA] = fbA_nodes;
-    }
-    if (lane == 32 && hasB) {
-        vw.lengths[antB] = len;
-        vw.fallback[antB] = fbB_steps;
-        vw.fallback[s.ants + antB] = fbB_nodes;
+    if (hl == 0 && (h == 0 || hasB)) {
+        im->v.lengths[my_ant] = len;
+        im->v.fallback[my_ant] = h ? fbB_steps : fbA_steps;
+        im->v.fallback[im->s.ants + my_ant] = h ? fbB_nodes : fbA_nodes;
     }
 }
 
@@ -1553,7 +1601,8 @@ template <int kTabu, int kPher, bool kPair, int kRows = 4, int kG = 0, bool kHel
 __global__ __launch_bounds__(1024) void k_construct(Views vw, Shape s, uint32_t it, int ants_per_block, Lds lds) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    // (two ants per wave: wave-uniform values in scalar registers)
+    const int wave = kPair ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> 6);
     const int R = lds.rows;
     uint16_t* tcand = reinterpret_cast<uint16_t*>(smem);
     float* tchc = reinterpret_cast<float*>(smem + align16(R * s.cl * 2));
@@ -1582,9 +1631,12 @@ __global__ __launch_bounds__(1024) void k_construct(Views vw, Shape s, uint32_t 
                                                                  nullptr, 1, help);
         return;
     }
-    if constexpr (kPair)
-        construct_pair<kTabu, kPher>(vw, s, it, ant, ant + 1 < s.ants, lane, regions + (size_t)(2 * wave) * lds.per_ant,
-                                     regions + (size_t)(2 * wave + 1) * lds.per_ant, tcand, tchc, R);
+    if constexpr (kPair) {
+        // (the kernel's first two arguments are laid out as a BatchItem)
+        const ItemPtr item = (ItemPtr)__builtin_amdgcn_kernarg_segment_ptr();
+        construct_pair<kTabu, kPher, true>(item, it, ant, lane, regions + (size_t)(2 * wave) * lds.per_ant,
+                                           regions + (size_t)(2 * wave + 1) * lds.per_ant, tcand, tchc, R);
+    }
     else
         construct_lone<kTabu, kPher, kRows, kG>(vw, s, it, ant, lane, regions + (size_t)wave * lds.per_ant, tcand,
                                                 tchc, R);
@@ -1778,7 +1830,8 @@ __global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, ui
 // a group of ants_per_block ants) from a queue ordered by decreasing n. Each
 // tile stages as many candidate rows of its instance as fit in the table part
 // of LDS, then every wave builds one ant's tour (two with kPair).
-template <int kTabu, int kPher, bool kPair>
+// kTable: the launch has a table part.
+template <int kTabu, int kPher, bool kPair, bool kTable>
 // (limited to 64 VGPRs, which lets eight waves share a SIMD: the persistent
 // batch is bound by instruction issue, and the extra waves hide more latency
 // than the few spilled registers cost)
@@ -1789,18 +1842,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ int s_tile;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t it = *it_dev;
     for (;;) {
         if (threadIdx.x == 0) s_tile = (int)atomicAdd(queue, 1u);
         __syncthreads();
-        const int t = s_tile;
+        const int t = __builtin_amdgcn_readfirstlane(s_tile);
         if (t >= ntiles) break;  // every wave of the workgroup leaves here
-        const BatchTile tile = tiles[t];
-        const Views vw = items[tile.inst].v;
-        const Shape s = items[tile.inst].s;
+        const int inst = __builtin_amdgcn_readfirstlane(tiles[t].inst);
+        const Views& vw = items[inst].v;
+        const Shape& s = items[inst].s;
         int R = 0;
-        if (s.cl > 0) {
+        if (kTable && s.cl > 0) {
             R = (table_bytes - 16) / (s.cl * 6);
             if (R > s.n) R = s.n;
             while (R > 0 && align16(R * s.cl * 2) + R * s.cl * 4 > table_bytes) --R;
@@ -1809,13 +1862,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         float* tchc = reinterpret_cast<float*>(smem + align16(R * s.cl * 2));
         if (R > 0) stage_table(vw, s.cl, R, tcand, tchc);
         __syncthreads();
-        const int ant = tile.ant0 + (kPair ? 2 * wave : wave);
+        const int ant = __builtin_amdgcn_readfirstlane(tiles[t].ant0) + (kPair ? 2 * wave : wave);
         uint8_t* regions = smem + table_bytes;
         if (ant < s.ants) {
             if constexpr (kPair)
-                construct_pair<kTabu, kPher>(vw, s, it, ant, ant + 1 < s.ants, lane,
-                                             regions + (size_t)(2 * wave) * per_ant,
-                                             regions + (size_t)(2 * wave + 1) * per_ant, tcand, tchc, R);
+                construct_pair<kTabu, kPher, kTable>((ItemPtr)&items[inst], it, ant, lane,
+                                                     regions + (size_t)(2 * wave) * per_ant,
+                                                     regions + (size_t)(2 * wave + 1) * per_ant, tcand, tchc, R);
             else
                 construct_ant<kTabu, kPher>(vw, s, it, ant, lane, regions + (size_t)wave * per_ant, tcand, tchc, R);
         }
@@ -2015,26 +2068,25 @@ hipError_t launch_tp(const Views& v, const Shape& s, uint32_t it, hipStream_t st
 }
 
 // the persistent batched kernel for a configuration
-const void* batch_kernel(int tabu, int pher, bool pair) {
-    if (tabu == MMAS_TABU_BITMASK) {
-        if (pher == MMAS_PHER_DENSE)
-            return pair ? (const void*)k_batch_construct<MMAS_TABU_BITMASK, MMAS_PHER_DENSE, true>
-                        : (const void*)k_batch_construct<MMAS_TABU_BITMASK, MMAS_PHER_DENSE, false>;
-        return pair ? (const void*)k_batch_construct<MMAS_TABU_BITMASK, MMAS_PHER_CANDIDATES, true>
-                    : (const void*)k_batch_construct<MMAS_TABU_BITMASK, MMAS_PHER_CANDIDATES, false>;
-    }
-    if (tabu == MMAS_TABU_COMPACT) {
-        if (pher == MMAS_PHER_DENSE)
-            return pair ? (const void*)k_batch_construct<MMAS_TABU_COMPACT, MMAS_PHER_DENSE, true>
-                        : (const void*)k_batch_construct<MMAS_TABU_COMPACT, MMAS_PHER_DENSE, false>;
-        return pair ? (const void*)k_batch_construct<MMAS_TABU_COMPACT, MMAS_PHER_CANDIDATES, true>
-                    : (const void*)k_batch_construct<MMAS_TABU_COMPACT, MMAS_PHER_CANDIDATES, false>;
-    }
-    if (pher == MMAS_PHER_DENSE)
-        return pair ? (const void*)k_batch_construct<MMAS_TABU_LIST, MMAS_PHER_DENSE, true>
-                    : (const void*)k_batch_construct<MMAS_TABU_LIST, MMAS_PHER_DENSE, false>;
-    return pair ? (const void*)k_batch_construct<MMAS_TABU_LIST, MMAS_PHER_CANDIDATES, true>
-                : (const void*)k_batch_construct<MMAS_TABU_LIST, MMAS_PHER_CANDIDATES, false>;
+template <int kTabu, int kPher>
+const void* batch_kernel_t(bool pair, bool table) {
+    if (pair)
+        return table ? (const void*)k_batch_construct<kTabu, kPher, true, true>
+                     : (const void*)k_batch_construct<kTabu, kPher, true, false>;
+    return table ? (const void*)k_batch_construct<kTabu, kPher, false, true>
+                 : (const void*)k_batch_construct<kTabu, kPher, false, false>;
+}
+
+const void* batch_kernel(int tabu, int pher, bool pair, bool table) {
+    const bool dense = pher == MMAS_PHER_DENSE;
+    if (tabu == MMAS_TABU_BITMASK)
+        return dense ? batch_kernel_t<MMAS_TABU_BITMASK, MMAS_PHER_DENSE>(pair, table)
+                     : batch_kernel_t<MMAS_TABU_BITMASK, MMAS_PHER_CANDIDATES>(pair, table);
+    if (tabu == MMAS_TABU_COMPACT)
+        return dense ? batch_kernel_t<MMAS_TABU_COMPACT, MMAS_PHER_DENSE>(pair, table)
+                     : batch_kernel_t<MMAS_TABU_COMPACT, MMAS_PHER_CANDIDATES>(pair, table);
+    return dense ? batch_kernel_t<MMAS_TABU_LIST, MMAS_PHER_DENSE>(pair, table)
+                 : batch_kernel_t<MMAS_TABU_LIST, MMAS_PHER_CANDIDATES>(pair, table);
 }
 
 }  // namespace
@@ -2061,7 +2113,7 @@ hipError_t launch_batch_construct(const BatchItem* items, const BatchTile* tiles
                                   int table_bytes, int per_ant, int grid, hipStream_t st) {
     const size_t bytes = (size_t)table_bytes + (size_t)ants_per_block * per_ant;
     const bool pair = lanes_per_ant == 32;
-    const void* kern = batch_kernel(tabu, pher, pair);
+    const void* kern = batch_kernel(tabu, pher, pair, table_bytes > 0);
     // the LDS limit was raised by batch_construct_grid for this footprint (a
     // graph capture must not need it here)
     void* args[] = {(void*)&items, (void*)&tiles, (void*)&ntiles, (void*)&queue, (void*)&it_dev,
@@ -2069,9 +2121,10 @@ hipError_t launch_batch_construct(const BatchItem* items, const BatchTile* tiles
     return hipLaunchKernel(kern, dim3(grid), dim3(64 * (pair ? ants_per_block / 2 : ants_per_block)), args, bytes, st);
 }
 
-int batch_construct_grid(int tabu, int pher, int ants_per_block, int lanes_per_ant, int lds_bytes) {
+int batch_construct_grid(int tabu, int pher, int ants_per_block, int lanes_per_ant, int table_bytes, int per_ant) {
+    const int lds_bytes = table_bytes + ants_per_block * per_ant;
     const bool pair = lanes_per_ant == 32;
-    const void* kern = batch_kernel(tabu, pher, pair);
+    const void* kern = batch_kernel(tabu, pher, pair, table_bytes > 0);
     if (lds_bytes > 64 * 1024 &&
         hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes) != hipSuccess) {
         (void)hipGetLastError();  // do not leave the error for the next launch check

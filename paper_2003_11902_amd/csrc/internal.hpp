@@ -99,7 +99,7 @@ hipError_t launch_batch_construct(const BatchItem* items, const BatchTile* tiles
                                   const uint32_t* it_dev, int tabu, int pher, int ants_per_block, int lanes_per_ant,
                                   int table_bytes, int per_ant, int grid, hipStream_t st);
 // Persistent-grid size for this LDS footprint (workgroups that fit at once).
-int batch_construct_grid(int tabu, int pher, int ants_per_block, int lanes_per_ant, int lds_bytes);
+int batch_construct_grid(int tabu, int pher, int ants_per_block, int lanes_per_ant, int table_bytes, int per_ant);
 // update.hip: best/limits for every instance (one workgroup each), then the
 // fused update of every row of every instance (`row_start` = prefix sums of
 // the instances' row counts, count + 1 entries); increments *it_dev and
