@@ -14,6 +14,7 @@
 // Tours are gathered in a register (lane k % 64 holds step k) and stored 64
 // cities at a time; tour lengths accumulate at those flushes.
 #include <atomic>
+#include <cstddef>
 #include <type_traits>
 
 #include "device.hpp"
@@ -36,6 +37,13 @@ typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr size_t kDrawBytes = 4 * kWave * sizeof(float);  // candidate draws of the next steps
 constexpr size_t kScratchBytes = 16;                       // per-ant counter of the fallback list
+
+// x with lane kLane's value replaced by the wave-uniform v.
+template <int kLane>
+__device__ __forceinline__ int write_lane(int v, int x) {
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(x) : "s"(__builtin_amdgcn_readfirstlane(v)), "n"(kLane));
+    return x;
+}
 
 // ---- tabu variants ---------------------------------------------------------
 
@@ -61,41 +69,45 @@ struct BitmaskTabu {
 // Compact tabu: entries[i] for i < L lists the unvisited cities; for i >= L,
 // entries[i] is the position of city i if it was moved left, or n once city i
 // is visited. City u is visited iff entries[u] > u.
+// A mark needs two cells: the marked city's, which the step's visited test has
+// read already (mark_at), and the last one of the left part, read ahead after
+// the mark before (`tail`), so that a mark waits for no LDS read of its own.
 struct CompactTabu {
     uint16_t* entries;
     int L;
     int n;
+    uint32_t tail;  // entries[L - 1] (0 once L is 0)
     __device__ void attach(uint8_t* lds, int n_) {
         entries = reinterpret_cast<uint16_t*>(lds);
         n = n_;
         L = n_;
+        tail = 0u;
     }
     __device__ void init(uint8_t* lds, int n_, int lane) {
-        entries = reinterpret_cast<uint16_t*>(lds);
-        n = n_;
-        L = n_;
+        attach(lds, n_);
         for (int i = lane; i < n_; i += kWave) entries[i] = (uint16_t)i;
+        tail = (uint32_t)(n_ - 1);
     }
     __device__ __forceinline__ bool visited(uint32_t v) const { return entries[v] > v; }
-    __device__ __forceinline__ uint32_t seen(uint32_t v) const { return entries[v] > v ? ~0u : 0u; }
+    __device__ __forceinline__ uint32_t cell(uint32_t v) const { return entries[v]; }
+    __device__ __forceinline__ uint32_t seen(uint32_t v, uint32_t cell_v) const { return cell_v > v ? ~0u : 0u; }
     __device__ __forceinline__ const uint16_t* list() const { return entries; }  // the L unvisited cities
-    __device__ __forceinline__ void mark(uint32_t u, int lane) {
-        // u is wave-uniform: both cells are read at once (the same for every
-        // lane, one LDS round trip) into scalar registers; lane 0 writes
-        const int iu_v = entries[u];     // position of u in the left part
-        const int t_v = entries[L - 1];  // last city of the left part
-        const int iu = __builtin_amdgcn_readfirstlane(iu_v);
-        const int t = __builtin_amdgcn_readfirstlane(t_v);
+    // u and iu = entries[u] (the position of u in the left part) are
+    // wave-uniform, and the whole wave comes here: lane 0 writes the cell at
+    // iu, lane 1 the last entry's, the others the marked city's (once more
+    // what lane 0 writes where u was not moved), so that no branch is taken
+    __device__ __forceinline__ void mark_at(uint32_t u, int iu) {
+        const int t = __builtin_amdgcn_readfirstlane((int)tail);
         L = L - 1;
-        if (lane == 0) {
-            if (iu == L) {
-                entries[L] = (uint16_t)n;
-            } else {
-                entries[iu] = (uint16_t)t;
-                entries[t] = (uint16_t)iu;
-            }
-            if ((int)u != iu) entries[u] = (uint16_t)n;
-        }
+        const bool end = iu == L;
+        const int v0 = end ? n : t, v2 = (int)u != iu ? n : v0;
+        const int at = write_lane<1>(end ? iu : t, write_lane<0>(iu, (int)u));
+        const int val = write_lane<1>(end ? n : iu, write_lane<0>(v0, v2));
+        entries[at] = (uint16_t)val;
+        tail = entries[L > 0 ? L - 1 : 0];
+    }
+    __device__ __forceinline__ void mark(uint32_t u, int) {
+        mark_at(u, __builtin_amdgcn_readfirstlane((int)entries[u]));
     }
 };
 
@@ -103,15 +115,17 @@ struct CompactTabu {
 // unv[0 .. L) lists the unvisited cities, idx[v] is the position of city v
 // in unv; marking v swaps it with the last unvisited entry and shortens the
 // list (reading C-18: the swap that the worked example of Sec. 4.1 needs), so
-// city v is visited iff idx[v] >= L. 4n bytes.
+// city v is visited iff idx[v] >= L. 4n bytes. Marks as the compact tabu's.
 struct ListTabu {
     uint16_t* unv;
     uint16_t* idx;
     int L;
+    uint32_t tail;  // unv[L - 1]
     __device__ void attach(uint8_t* lds, int n_) {
         unv = reinterpret_cast<uint16_t*>(lds);
         idx = unv + n_;
         L = n_;
+        tail = 0u;
     }
     __device__ void init(uint8_t* lds, int n_, int lane) {
         attach(lds, n_);
@@ -119,21 +133,29 @@ struct ListTabu {
             unv[i] = (uint16_t)i;
             idx[i] = (uint16_t)i;
         }
+        tail = (uint32_t)(n_ - 1);
     }
     __device__ __forceinline__ bool visited(uint32_t v) const { return (int)idx[v] >= L; }
-    __device__ __forceinline__ uint32_t seen(uint32_t v) const { return (int)idx[v] >= L ? ~0u : 0u; }
+    __device__ __forceinline__ uint32_t cell(uint32_t v) const { return idx[v]; }
+    __device__ __forceinline__ uint32_t seen(uint32_t, uint32_t cell_v) const { return (int)cell_v >= L ? ~0u : 0u; }
     __device__ __forceinline__ const uint16_t* list() const { return unv; }
-    __device__ __forceinline__ void mark(uint32_t u, int lane) {
-        // every lane reads the same cells; lane 0 writes
-        const int iu = idx[u];
+    // (idx lies n cells after unv: lanes 0 to 3 write one cell each, the others
+    // lane 3's again)
+    __device__ __forceinline__ void mark_at(uint32_t u, int iu) {
+        const int last = __builtin_amdgcn_readfirstlane((int)tail);
+        const int n = (int)(idx - unv);
         L = L - 1;
-        const int last = unv[L];
-        if (lane == 0) {
-            unv[iu] = (uint16_t)last;
-            idx[last] = (uint16_t)iu;
-            unv[L] = (uint16_t)u;
-            idx[u] = (uint16_t)L;
-        }
+        int at = write_lane<0>(iu, n + (int)u);
+        at = write_lane<1>(n + last, at);
+        at = write_lane<2>(L, at);
+        int val = write_lane<0>(last, L);
+        val = write_lane<1>(iu, val);
+        val = write_lane<2>((int)u, val);
+        unv[at] = (uint16_t)val;
+        tail = unv[L > 0 ? L - 1 : 0];
+    }
+    __device__ __forceinline__ void mark(uint32_t u, int) {
+        mark_at(u, __builtin_amdgcn_readfirstlane((int)idx[u]));
     }
 };
 
@@ -199,8 +221,8 @@ __device__ __forceinline__ void keep_best(uint32_t code, uint32_t node, uint32_t
 // (unless the launch allows more): with more unvisited cities the fallback
 // goes by draw blocks, so the ant's LDS does not grow with n.
 constexpr int kListCap = 512;
-__host__ __device__ inline int list_cap(const Shape& s) {
-    return s.list_cap > 0 ? s.list_cap : (s.n < kListCap ? s.n : kListCap);
+__host__ __device__ inline int list_cap(int n, int asked) {
+    return asked > 0 ? asked : (n < kListCap ? n : kListCap);
 }
 
 // A wave's best (key code, lowest city) packed so that the larger value is
@@ -237,6 +259,9 @@ __device__ __forceinline__ T* uni_ptr(T* p) {
 // serves one colony. Rare paths read what they need from it again instead of
 // keeping it in scalar registers all along.
 using ItemPtr = const __attribute__((address_space(4))) BatchItem*;
+// (the first two arguments of such a kernel, Views and Shape, are laid out as
+// a BatchItem)
+__device__ __forceinline__ ItemPtr kernel_item() { return (ItemPtr)__builtin_amdgcn_kernarg_segment_ptr(); }
 __device__ __forceinline__ ItemPtr opaque(ItemPtr p) {
     asm volatile("" : "+s"(p));
     return p;
@@ -431,15 +456,6 @@ __device__ __forceinline__ unsigned long long near_share(const Fallback& q, cons
     return ((unsigned long long)best << 32) | (unsigned long long)(node << 1) | (unsigned long long)(clear ? 0u : 1u);
 }
 
-// The better of two shares; unclear if they nearly tie.
-template <int kPher>
-__device__ __forceinline__ unsigned long long near_better(unsigned long long a, unsigned long long b) {
-    constexpr uint32_t kM = kPher == MMAS_PHER_DENSE ? kNear : kNearPow;
-    const unsigned long long hi = a > b ? a : b, lo = a > b ? b : a;
-    if ((uint32_t)(hi >> 32) == 0u) return 0ull;
-    return hi | ((uint32_t)(lo >> 32) >= near_code<kM>((uint32_t)(hi >> 32)) ? 1ull : 0ull);
-}
-
 // Part `part` of `parts` of a fallback whose tabu keeps the list of unvisited
 // cities (compact, list): the cheaper layout by instruction count.
 template <int kTabu, int kPher>
@@ -528,14 +544,6 @@ __device__ __attribute__((noinline)) uint32_t fallback_lone(Fallback qv, LdsPtr<
     return fallback_wave<kTabu, kPher>(uni(qv), (LdsPtr<uint16_t>)uni((uint32_t)(uintptr_t)list_v), uni(cap_v), lane);
 }
 
-// Part `part` of two of a fallback (compact tabu, the ant's wave and its draw
-// helper), as near_share packs it.
-template <int kTabu, int kPher>
-__device__ __attribute__((noinline)) unsigned long long fallback_half(Fallback qv, int part_v, int lane) {
-    const Fallback q = uni(qv);
-    return near_part<kTabu, kPher>(q, uni(part_v), 2, lane);
-}
-
 // The exact choice of a candidate step whose approximate keys nearly tie:
 // lane r holds rank r (city `node`, factor w, `live` ~0 or 0) of the list of
 // the ant that its half (or the whole wave) serves, and draws slot r. Returns
@@ -620,43 +628,43 @@ __device__ void stage_table(const Views& vw, int cl, int R, uint16_t* tcand, flo
 // The arguments of an all-city fallback at step k from city cur with L
 // unvisited cities, over `tabu` (the bitmask's words, or the other tabus' list).
 template <int kPher>
-__device__ __forceinline__ Fallback fallback_args(const Views& vw, const Shape& s, uint32_t it, uint32_t ant, int k,
-                                                  uint32_t cur, int L, const void* tabu, float tmin_a) {
+__device__ __forceinline__ Fallback fallback_args(ItemPtr item, uint32_t it, uint32_t ant, int k, uint32_t cur, int L,
+                                                  LdsPtr<const void> tabu, float tmin_a) {
     Fallback q;
+    const int n = item->s.n;
     // (C-style casts: the only casts that change the address space)
     q.tabu = (LdsPtr<const uint16_t>)tabu;
     q.L = L;
-    q.n = s.n;
-    q.cl = s.cl;
-    q.beta = s.beta;
-    q.irow = kPher == MMAS_PHER_DENSE ? (GlbPtr<const float>)(vw.choice_inv + (size_t)cur * s.n) : nullptr;
-    q.drow = kPher == MMAS_PHER_DENSE ? nullptr : (GlbPtr<const int32_t>)(vw.dist + (size_t)cur * s.n);
+    q.n = n;
+    q.cl = item->s.cl;
+    q.beta = item->s.beta;
+    q.irow = kPher == MMAS_PHER_DENSE ? (GlbPtr<const float>)(item->v.choice_inv + (size_t)cur * n) : nullptr;
+    q.drow = kPher == MMAS_PHER_DENSE ? nullptr : (GlbPtr<const int32_t>)(item->v.dist + (size_t)cur * n);
     q.tmin_a = tmin_a;
-    q.seed = s.seed;
+    q.seed = item->s.seed;
     q.it = it;
     q.ant = ant;
     q.step = (uint32_t)k;
     return q;
 }
-__device__ __forceinline__ const void* fallback_tabu(const BitmaskTabu& t) { return t.bits; }
-__device__ __forceinline__ const void* fallback_tabu(const CompactTabu& t) { return t.entries; }
-__device__ __forceinline__ const void* fallback_tabu(const ListTabu& t) { return t.unv; }
+__device__ __forceinline__ LdsPtr<const void> fallback_tabu(const BitmaskTabu& t) { return (LdsPtr<const void>)t.bits; }
+__device__ __forceinline__ LdsPtr<const void> fallback_tabu(const CompactTabu& t) { return (LdsPtr<const void>)t.entries; }
+__device__ __forceinline__ LdsPtr<const void> fallback_tabu(const ListTabu& t) { return (LdsPtr<const void>)t.unv; }
 
 // One wave's share of a workgroup-wide fallback at step k from city fcur
 // (near_share). A bitmask's unvisited cities are gathered by the whole
 // workgroup first, with a barrier, unless keying by draw blocks is cheaper.
 template <int kTabu, int kPher, class T>
-__device__ unsigned long long wide_share(const Views& vw, const Shape& s, uint32_t it, int ant, int k, uint32_t fcur,
-                                         int L, T& tabu, uint16_t* ulist, WideLds* wl, float tmin_a, int lane, int wv,
-                                         int nw) {
-    Fallback q = fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, fcur, L, fallback_tabu(tabu), tmin_a);
+__device__ unsigned long long wide_share(ItemPtr item, uint32_t it, int ant, int k, uint32_t fcur, int L, T& tabu,
+                                         uint16_t* ulist, WideLds* wl, float tmin_a, int lane, int wv, int nw) {
+    Fallback q = fallback_args<kPher>(item, it, (uint32_t)ant, k, fcur, L, fallback_tabu(tabu), tmin_a);
     if constexpr (kTabu == MMAS_TABU_BITMASK) {
         NearBest nb;
         const int nblk = ((q.cl + q.n - 1) >> 2) - (q.cl >> 2) + 1, span = kWave * nw;
         if (85 * ((nblk + span - 1) / span) < 58 * ((L + span - 1) / span) + kGatherCost) {
             near_blocks<kTabu, kPher>(q, wv, nw, lane, nb);
         } else {
-            gather_unvisited_block(tabu, s.n, ulist, &wl->counter);
+            gather_unvisited_block(tabu, q.n, ulist, &wl->counter);
             __syncthreads();
             q.L = __builtin_amdgcn_readfirstlane((int)wl->counter);
             near_list<kPher>(q, (LdsPtr<const uint16_t>)ulist, wv, nw, lane, nb);
@@ -671,20 +679,20 @@ __device__ unsigned long long wide_share(const Views& vw, const Shape& s, uint32
 // the leading wave posts a fallback (or the end of its tour), key their share
 // and post their best, so the steps without a fallback need no barrier.
 template <int kTabu, int kPher>
-__device__ void wide_helpers(const Views& vw, const Shape& s, uint32_t it, int ant, int lane, uint8_t* region,
-                             WideLds* wl, int wv, int nw) {
-    const int n = s.n;
+__device__ __forceinline__ void wide_helpers(ItemPtr item, uint32_t it, int ant, int lane, uint8_t* region, WideLds* wl,
+                                             int wv, int nw) {
+    const int n = item->s.n;
     typename TabuOf<kTabu>::type tabu;
     tabu.attach(region + kDrawBytes + kScratchBytes, n);
     uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((n + 31) / 32)));
     float tmin_a = 0.0f;
-    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(vw.state->tau_min, s.alpha);
+    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(item->v.state->tau_min, item->s.alpha);
     for (;;) {
         __syncthreads();  // a posted fallback, or the end
         const WideStep st = wl->step;
         if (__builtin_amdgcn_readfirstlane(st.stop)) return;
         const unsigned long long mine =
-            wide_share<kTabu, kPher>(vw, s, it, ant, __builtin_amdgcn_readfirstlane(st.k),
+            wide_share<kTabu, kPher>(item, it, ant, __builtin_amdgcn_readfirstlane(st.k),
                                      (uint32_t)__builtin_amdgcn_readfirstlane((int)st.cur),
                                      __builtin_amdgcn_readfirstlane(st.L), tabu, ulist, wl, tmin_a, lane, wv, nw);
         if (lane == 0) wl->res[wv] = mine;
@@ -696,9 +704,9 @@ __device__ void wide_helpers(const Views& vw, const Shape& s, uint32_t it, int a
 // cur: posts it, keys its share with the helpers, and takes the best over
 // the waves (a near tie it settles by the exact keys alone); kNone if none.
 template <int kTabu, int kPher, class T>
-__device__ uint32_t wide_lead_fallback(const Views& vw, const Shape& s, uint32_t it, int ant, int k, uint32_t cur,
-                                       T& tabu, uint16_t* ulist, WideLds* wl, float tmin_a, int lane, int nw) {
-    const int L = s.n - k;  // unvisited cities
+__device__ uint32_t wide_lead_fallback(ItemPtr item, uint32_t it, int ant, int k, uint32_t cur, T& tabu,
+                                       uint16_t* ulist, WideLds* wl, float tmin_a, int lane, int nw) {
+    const int L = item->s.n - k;  // unvisited cities
     if (lane == 0) {
         WideStep st;
         st.k = k;
@@ -709,7 +717,7 @@ __device__ uint32_t wide_lead_fallback(const Views& vw, const Shape& s, uint32_t
         if constexpr (kTabu == MMAS_TABU_BITMASK) wl->counter = 0u;
     }
     __syncthreads();
-    const unsigned long long mine = wide_share<kTabu, kPher>(vw, s, it, ant, k, cur, L, tabu, ulist, wl, tmin_a, lane, 0, nw);
+    const unsigned long long mine = wide_share<kTabu, kPher>(item, it, ant, k, cur, L, tabu, ulist, wl, tmin_a, lane, 0, nw);
     if (lane == 0) wl->res[0] = mine;
     __syncthreads();
     // (the record, the counter and the list are read before the second
@@ -724,7 +732,7 @@ __device__ uint32_t wide_lead_fallback(const Views& vw, const Shape& s, uint32_t
         if (__builtin_expect((pick & 1u) == 0u, 1)) return pick >> 1;
     }
     return fallback_exact<kTabu, kPher>(
-        fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, cur, L, fallback_tabu(tabu), tmin_a), lane);
+        fallback_args<kPher>(item, it, (uint32_t)ant, k, cur, L, fallback_tabu(tabu), tmin_a), lane);
 }
 
 // The end of the leading wave's tour: the helpers leave.
@@ -744,35 +752,24 @@ __device__ void wide_lead_end(WideLds* wl, int lane) {
 //
 // A second wave per ant computes the draws (Philox blocks and logarithms) of
 // each group of S = 64 / G steps into one of two LDS buffers, a group ahead
-// of the ant's wave, which then only reads them; with the compact tabu
-// (kHelpShare) it also keys half of every all-city fallback (fallback_half's
-// part 1) while the ant's wave keys the other half. Counters in LDS hand the
-// buffers and the fallbacks over: the helper writes group g once group
-// g - 2 is read, and serves a posted fallback whenever it waits. Waits are
+// of the ant's wave, which then only reads them. Two counters in LDS hand the
+// buffers over: the helper writes group g once group g - 2 is read. Waits are
 // bounded: past the limit the ant's wave flags the tour (state flag 32) and
-// keys the rest alone, and the helper leaves, so no wave can wait for ever.
-// Both waves must read any counter the other writes through lds_get (a
-// volatile LDS read) and write their own through lds_put.
+// goes on, and the helper leaves, so no wave can wait for ever. Both waves
+// must read the counter the other writes through lds_get (a volatile LDS
+// read) and write their own through lds_put. (Sharing the all-city fallbacks
+// with the helper pays for no tabu any more: at n = 1002 the compact tabu
+// takes 338 us a construction with it and 329 without, the bitmask 297 an
+// iteration with and 287 without. Nor do approximate logarithms from the
+// helper: the ant's chain then ends in two more instructions, 285 -> 294 us.)
 struct HelpLds {
-    int made;                // draw groups written (helper)
-    int read;                // draw groups read (ant's wave)
-    int req;                 // fallbacks posted (ant's wave)
-    int done;                // fallbacks whose part 1 is keyed (helper)
-    int k;                   // the posted fallback: step,
-    uint32_t cur;            // current city,
-    int L;                   // unvisited cities,
-    int stop;                // and 1 once the tour is done (the helper leaves)
-    unsigned long long res;  // part 1's best (near_share) of fallback `done`
-    int pad[2];              // (to 48 bytes)
+    int made;    // draw groups written (helper)
+    int read;    // draw groups read (ant's wave)
+    int pad[2];  // (to 16 bytes)
 };
-static_assert(sizeof(HelpLds) == 48, "16-byte multiple");
+static_assert(sizeof(HelpLds) == 16, "cleared by one store");
 constexpr size_t kHelpBytes = kDrawBytes + sizeof(HelpLds);  // second draw buffer, then the counters
 constexpr int kHelpSpins = 1 << 24;                          // sleeps of 64 clocks before a wait gives up
-// The tabus whose fallbacks the helper shares: measured at n = 1002, the
-// shared fallback made the compact tabu's construction about 7 % faster; the
-// bitmask tabu's it made 1-3 % slower and the list tabu's no faster.
-template <int kTabu>
-constexpr bool kHelpShare = kTabu == MMAS_TABU_COMPACT;
 
 __device__ __forceinline__ int lds_get(const int* c) {
     return __builtin_amdgcn_readfirstlane(*(LdsPtr<volatile const int>)c);
@@ -794,94 +791,45 @@ __device__ __forceinline__ bool wait_count(const int* c, int want) {
     return false;
 }
 
-// Part `part` of two of the all-city fallback of step k from city cur with
-// L unvisited cities, on the list of the ant's tabu (compact or list).
-template <int kTabu, int kPher, class T>
-__device__ __forceinline__ unsigned long long half_part(const Views& vw, const Shape& s, uint32_t it, int ant, int k,
-                                                        uint32_t cur, int L, const T& tabu, float tmin_a, int part,
-                                                        int lane) {
-    return fallback_half<kTabu, kPher>(
-        fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, cur, L, fallback_tabu(tabu), tmin_a), part, lane);
-}
-
 // The helper wave of ant `ant`: `region` is the ant's region (draw buffer 0
-// at its start, the tabu after it), `help` the helper's part (draw buffer 1,
-// then the HelpLds).
-template <int kTabu, int kPher, int kG>
-__device__ void draw_helper(const Views& vw, const Shape& s, uint32_t it, int ant, int lane, uint8_t* region,
-                            uint8_t* help) {
+// at its start), `help` the helper's part (draw buffer 1, then the HelpLds).
+template <int kG>
+__device__ __forceinline__ void draw_helper(ItemPtr item, uint32_t it, int ant, int lane, uint8_t* region,
+                                            uint8_t* help) {
     constexpr int gsh = kG == 1 ? 0 : kG == 2 ? 1 : kG == 4 ? 2 : kG == 8 ? 3 : 4;
     constexpr int S = kWave >> gsh;
-    const int n = s.n;
+    const int n = item->s.n;
+    const uint64_t seed = item->s.seed;
     float* buf0 = reinterpret_cast<float*>(region);
     float* buf1 = reinterpret_cast<float*>(help);
     HelpLds* h = reinterpret_cast<HelpLds*>(help + kDrawBytes);
-    typename TabuOf<kTabu>::type tabu;
-    tabu.attach(region + kDrawBytes + kScratchBytes, n);
-    float tmin_a = 0.0f;
-    if (kHelpShare<kTabu> && kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(vw.state->tau_min, s.alpha);
-    int served = 0;
-    // keys part 1 of a posted fallback, if there is one; true if it did
-    auto serve = [&]() -> bool {
-        if constexpr (!kHelpShare<kTabu>) {
-            return false;
-        } else {
-            const int r = lds_get(&h->req);
-            if (r <= served) return false;
-            asm volatile("" ::: "memory");
-            const unsigned long long res =
-                half_part<kTabu, kPher>(vw, s, it, ant, lds_get(&h->k), (uint32_t)lds_get(reinterpret_cast<int*>(&h->cur)),
-                                        lds_get(&h->L), tabu, tmin_a, 1, lane);
-            asm volatile("" ::: "memory");
-            *(LdsPtr<volatile unsigned long long>)&h->res = res;
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the result is in LDS before the count
-            lds_put(&h->done, r);
-            served = r;
-            return true;
-        }
-    };
-    // waits until the counter c reaches `want`, serving fallbacks meanwhile;
-    // false if it gave up
-    auto wait_serving = [&](const int* c, int want) -> bool {
-        for (int spins = 0; spins < kHelpSpins; ++spins) {
-            if (serve()) spins = 0;
-            if (lds_get(c) >= want) {
-                asm volatile("" ::: "memory");
-                return true;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        return false;
-    };
     const int groups = (n + S - 1) / S;
     for (int g = 0; g < groups; ++g) {
-        const Words4 b = draw_block(s.seed, it, (uint32_t)ant, (uint32_t)(g * S + (lane >> gsh)),
+        const Words4 b = draw_block(seed, it, (uint32_t)ant, (uint32_t)(g * S + (lane >> gsh)),
                                     (uint32_t)(4 * (lane & (kG - 1))));
         float4 lv;
         lv.x = log_u01(u01(b.w[0]));
         lv.y = log_u01(u01(b.w[1]));
         lv.z = log_u01(u01(b.w[2]));
         lv.w = log_u01(u01(b.w[3]));
-        // (computed before the wait, so that the waits serve fallbacks at once)
+        // (computed before the wait)
         asm volatile("" : "+v"(lv.x), "+v"(lv.y), "+v"(lv.z), "+v"(lv.w));
         // the buffer of group g held group g - 2
-        if (g >= 2 && !wait_serving(&h->read, g - 1)) return;
+        if (g >= 2 && !wait_count(&h->read, g - 1)) return;
         *reinterpret_cast<float4*>(((g & 1) ? buf1 : buf0) + 4 * lane) = lv;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the draws are in LDS before the count
         lds_put(&h->made, g + 1);
     }
-    // every group is written: serve fallbacks until the tour is done
-    wait_serving(&h->stop, 1);
 }
 
 // One ant's tour (one wave64, the batched kernel's step): start city, n - 1
 // selection steps, tour and length stores. `region` is the ant's LDS region;
 // rows 0..R-1 of the candidate table are in LDS at tcand / tchc.
 template <int kTabu, int kPher>
-__device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int ant, int lane, uint8_t* region,
-                              const uint16_t* tcand, const float* tchc, int R) {
-    const int n = s.n, cl = s.cl;
-    const uint64_t seed = s.seed;
+__device__ __forceinline__ void construct_ant(ItemPtr item, uint32_t it, int ant, int lane, uint8_t* region,
+                                              const uint16_t* tcand, const float* tchc, int R) {
+    const int n = item->s.n, cl = item->s.cl;
+    const uint64_t seed = item->s.seed;
 
     // per-ant LDS: the draws of the next steps (256 floats), then the tabu
     float* lnbuf = reinterpret_cast<float*>(region);
@@ -890,12 +838,12 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
     uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((n + 31) / 32)));
 
     float tmin_a = 0.0f;
-    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(vw.state->tau_min, s.alpha);
+    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(item->v.state->tau_min, item->s.alpha);
     // (C-style casts: the only casts that change the address space)
     const LdsPtr<const uint16_t> lds_cand = (LdsPtr<const uint16_t>)tcand;
     const LdsPtr<const float> lds_chc = (LdsPtr<const float>)tchc;
-    const GlbPtr<const uint16_t> glb_cand = (GlbPtr<const uint16_t>)vw.cand;
-    const GlbPtr<const float> glb_chc = (GlbPtr<const float>)vw.chc_inv;  // reciprocals
+    const GlbPtr<const uint16_t> glb_cand = (GlbPtr<const uint16_t>)item->v.cand;
+    const GlbPtr<const float> glb_chc = (GlbPtr<const float>)item->v.chc_inv;  // reciprocals
 
     // start city: floor(x * n / 2^32) of draw (step 0, slot 0)
     const uint32_t x0 = draw_block(seed, it, (uint32_t)ant, 0u, 0u).w[0];
@@ -910,8 +858,8 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
     const int G = 1 << gsh;
     const int S = kWave >> gsh;
 
-    uint16_t* tour_out = vw.tours + (size_t)ant * n;
-    const int32_t* dist = vw.dist;
+    uint16_t* tour_out = item->v.tours + (size_t)ant * n;
+    const int32_t* dist = item->v.dist;
     uint32_t tbuf = start;   // lane (k & 63) holds the city of step k
     uint32_t prev_last = 0;  // last city of the previous 64-step chunk
     int64_t len = 0;
@@ -977,13 +925,14 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
             fb_steps += 1;
             fb_nodes += n - k;
             next = fallback_lone<kTabu, kPher>(
-                fallback_args<kPher>(vw, s, it, (uint32_t)ant, k, cur, n - k, fallback_tabu(tabu), tmin_a),
-                (LdsPtr<uint16_t>)ulist, list_cap(s), lane);
+                fallback_args<kPher>(opaque(item), it, (uint32_t)ant, k, cur, n - k, fallback_tabu(tabu), tmin_a),
+                (LdsPtr<uint16_t>)ulist, list_cap(n, item->s.list_cap), lane);
         }
+        next = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
         if (next >= (uint32_t)n) {
             // unreachable with a validated instance (some unvisited city always
             // has a key); report it instead of indexing out of bounds
-            if (lane == 0) atomicOr(&vw.state->flags, 8u);
+            if (lane == 0) atomicOr(&item->v.state->flags, 8u);
             break;
         }
         tabu.mark(next, lane);
@@ -1006,9 +955,9 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
     if (lane == 0) len += dist[(size_t)cur * n + start];  // closing edge
     len = wave_sum_i64(len);
     if (lane == 0) {
-        vw.lengths[ant] = len;
-        vw.fallback[ant] = fb_steps;
-        vw.fallback[s.ants + ant] = fb_nodes;
+        item->v.lengths[ant] = len;
+        item->v.fallback[ant] = fb_steps;
+        item->v.fallback[item->s.ants + ant] = fb_nodes;
     }
 }
 
@@ -1023,28 +972,28 @@ __device__ void construct_ant(const Views& vw, const Shape& s, uint32_t it, int 
 // argmax reduces only the two rows that hold the list.
 // kWide: the wave leads a workgroup whose other waves share its fallbacks
 // (wide_helpers), nw waves in all. kHelp (kG > 0): a draw helper wave
-// (draw_helper) fills the draw buffers and keys half of every fallback;
-// `help` is its part of the region (second buffer, counters).
+// (draw_helper) fills the draw buffers; `help` is its part of the region
+// (second buffer, counters).
 template <int kTabu, int kPher, int kRows, int kG, bool kWide = false, bool kHelp = false>
-__device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int ant, int lane, uint8_t* region,
-                               const uint16_t* tcand, const float* tchc, int R, WideLds* wl = nullptr,
-                               int nw = 1, uint8_t* help = nullptr) {
+__device__ __forceinline__ void construct_lone(ItemPtr item, uint32_t it, int ant, int lane, uint8_t* region,
+                                               const uint16_t* tcand, const float* tchc, int R, WideLds* wl = nullptr,
+                                               int nw = 1, uint8_t* help = nullptr) {
     // the draws' logarithms: approximate where this wave computes them, exact
     // from the draw helper (whose time is not on the ant's chain)
     constexpr bool kApprox = !kHelp;
-    const int n = s.n, cl = s.cl;
-    const uint64_t seed = s.seed;
+    const int n = item->s.n, cl = item->s.cl;
+    const uint64_t seed = item->s.seed;
     float* lnbuf = reinterpret_cast<float*>(region);
     typename TabuOf<kTabu>::type tabu;
     tabu.init(region + kDrawBytes + kScratchBytes, n, lane);
     uint16_t* ulist = reinterpret_cast<uint16_t*>(region + kDrawBytes + kScratchBytes + align16(4 * ((n + 31) / 32)));
 
     float tmin_a = 0.0f;
-    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(vw.state->tau_min, s.alpha);
+    if (kPher == MMAS_PHER_CANDIDATES) tmin_a = powi(item->v.state->tau_min, item->s.alpha);
     const LdsPtr<const uint16_t> lds_cand = (LdsPtr<const uint16_t>)tcand;
     const LdsPtr<const float> lds_chc = (LdsPtr<const float>)tchc;
-    const GlbPtr<const uint16_t> glb_cand = (GlbPtr<const uint16_t>)vw.cand;
-    const GlbPtr<const float> glb_chc = (GlbPtr<const float>)vw.chc_inv;  // reciprocals
+    const GlbPtr<const uint16_t> glb_cand = (GlbPtr<const uint16_t>)item->v.cand;
+    const GlbPtr<const float> glb_chc = (GlbPtr<const float>)item->v.chc_inv;  // reciprocals
     LdsPtr<const float> lds_ln = (LdsPtr<const float>)lnbuf;
 
     const uint32_t x0 = draw_block(seed, it, (uint32_t)ant, 0u, 0u).w[0];
@@ -1063,18 +1012,19 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
     const int G = 1 << gsh;
     const int S = kWave >> gsh;
     const int lr = lane < cl ? lane : cl - 1;       // lanes past the list repeat the last entry
-    const uint32_t lane_ok = lane < cl ? ~0u : 0u;  // ... and never hold a key
+    uint32_t lane_ok = lane < cl ? ~0u : 0u;        // ... and never hold a key
     const int ln_lane = lane & (4 * G - 1);
+    const uint32_t cells = (uint32_t)(uintptr_t)(LdsPtr<uint8_t>)region + (uint32_t)(kDrawBytes + kScratchBytes);
     // bitmask marks: LDS byte address of each lane's OR (see below)
     uint32_t mark_mask = lane == 0 ? ~0u : 0u;
     uint32_t mark_base = (uint32_t)(uintptr_t)(LdsPtr<uint8_t>)region +
                          (lane == 0 ? (uint32_t)(kDrawBytes + kScratchBytes) : 4u * (uint32_t)lane);
     // (opaque to the compiler, which would otherwise turn the arithmetic
     // below back into lane-0 selects)
-    asm volatile("" : "+v"(mark_mask), "+v"(mark_base));
+    asm volatile("" : "+v"(mark_mask), "+v"(mark_base), "+v"(lane_ok));
 
-    uint16_t* tour_out = vw.tours + (size_t)ant * n;
-    const int32_t* dist = vw.dist;
+    uint16_t* tour_out = item->v.tours + (size_t)ant * n;
+    const int32_t* dist = item->v.dist;
     uint32_t tbuf = (uint32_t)start;  // lane (k & 63) holds the city of step k
     uint32_t prev_last = 0;           // city of the last step of the previous chunk
     int64_t len = 0;
@@ -1082,7 +1032,6 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
     int cur = start;
     bool bad = false;
     bool bad_help = false;  // a wait for the draw helper gave up
-    int fseq = 0;           // fallbacks posted to the helper
     HelpLds* hl = kHelp ? reinterpret_cast<HelpLds*>(help + kDrawBytes) : nullptr;
 
     // the all-city fallback of step k from city cur (rare with a list)
@@ -1098,37 +1047,12 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
         fb_nodes += n - kk;
         uint32_t pick;
         if constexpr (kWide) {
-            pick = wide_lead_fallback<kTabu, kPher>(vw, s, it, ant, kk, (uint32_t)cur, tabu, ulist, wl, tmin_a, lane, nw);
+            pick = wide_lead_fallback<kTabu, kPher>(opaque(item), it, ant, kk, (uint32_t)cur, tabu, ulist, wl, tmin_a, lane, nw);
         } else {
-            int L = n - kk;
-            if constexpr (kTabu != MMAS_TABU_BITMASK) L = tabu.L;
-            if constexpr (kHelp && kHelpShare<kTabu>) {
-                // post the fallback, key part 0 and take the better of the parts
-                ++fseq;
-                *reinterpret_cast<int4*>(&hl->k) = make_int4(kk, cur, L, 0);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the record is in LDS before the count
-                lds_put(&hl->req, fseq);
-                const unsigned long long r0 =
-                    half_part<kTabu, kPher>(vw, s, it, ant, kk, (uint32_t)cur, L, tabu, tmin_a, 0, lane);
-                unsigned long long r1;
-                if (!bad_help && wait_count(&hl->done, fseq)) {
-                    r1 = *(LdsPtr<volatile unsigned long long>)&hl->res;
-                } else {  // (never expected) part 1 here too
-                    bad_help = true;
-                    r1 = half_part<kTabu, kPher>(vw, s, it, ant, kk, (uint32_t)cur, L, tabu, tmin_a, 1, lane);
-                }
-                const unsigned long long r = near_better<kPher>(r0, r1);
-                if (__builtin_expect((r & 1ull) == 0ull && r != 0ull, 1))
-                    pick = (uint32_t)r >> 1;
-                else
-                    pick = fallback_exact<kTabu, kPher>(
-                        fallback_args<kPher>(vw, s, it, (uint32_t)ant, kk, (uint32_t)cur, L, fallback_tabu(tabu), tmin_a),
-                        lane);
-            } else {
-                pick = fallback_lone<kTabu, kPher>(
-                    fallback_args<kPher>(vw, s, it, (uint32_t)ant, kk, (uint32_t)cur, L, fallback_tabu(tabu), tmin_a),
-                    (LdsPtr<uint16_t>)ulist, list_cap(s), lane);
-            }
+            const ItemPtr im = opaque(item);
+            pick = fallback_lone<kTabu, kPher>(
+                fallback_args<kPher>(im, it, (uint32_t)ant, kk, (uint32_t)cur, n - kk, fallback_tabu(tabu), tmin_a),
+                (LdsPtr<uint16_t>)ulist, list_cap(n, im->s.list_cap), lane);
         }
         const uint32_t next = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick);
         // no city is unreachable with a validated instance; were it not,
@@ -1139,7 +1063,7 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
     };
 
     // marks the chosen city, records it as step k and moves there
-    auto advance = [&](uint32_t next, int k) {
+    auto advance = [&](uint32_t next, int at, int k) {
         if constexpr (kTabu == MMAS_TABU_BITMASK) {
             // every lane issues the OR, so that no exec mask is set up around
             // it: lane 0 into the city's word, the others a 0 into their own
@@ -1148,7 +1072,7 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
             __hip_atomic_fetch_or((LdsPtr<uint32_t>)(uintptr_t)addr, (1u << (next & 31u)) & mark_mask,
                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
-            tabu.mark(next, lane);
+            tabu.mark_at(next, at);
         }
         if (lane == (k & 63)) tbuf = next;
         cur = __builtin_amdgcn_readfirstlane((int)next);
@@ -1157,52 +1081,94 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
     // The row entry of this lane for city c (rank lr of its candidate list),
     // loaded one step ahead: as soon as the next city is known, before it is
     // marked, so the loads are not queued behind the mark.
-    uint16_t node_next = 0;  // (16 bits: widened where it is used, not where the loads meet)
+    // (typed as a 16-bit float only so that its bits are never widened)
+    _Float16 node_next = 0;
     float w_next = 0.0f;
+    uint32_t lds_cand_l = (uint32_t)(uintptr_t)lds_cand + 2u * (uint32_t)lr;
+    uint32_t lds_chc_l = (uint32_t)(uintptr_t)lds_chc + 4u * (uint32_t)lr;
+    asm volatile("" : "+v"(lds_cand_l), "+v"(lds_chc_l));
+    auto load_row_near = [&](int c) {
+        const uint32_t e = (uint32_t)(c * cl);
+        node_next = *(LdsPtr<const _Float16>)(lds_cand_l + 2u * e);
+        w_next = *(LdsPtr<const float>)(lds_chc_l + 4u * e);
+    };
+    auto load_row_far = [&](int c) {
+        const uint32_t e = (uint32_t)(c * cl);
+        node_next = ((GlbPtr<const _Float16>)glb_cand + e)[(uint32_t)lr];
+        w_next = (glb_chc + e)[(uint32_t)lr];
+    };
     auto load_row = [&](int c) {
-        const int e = c * cl + lr;
-        if (__builtin_expect(c < R, 1)) {
-            node_next = lds_cand[e];
-            w_next = lds_chc[e];
-        } else {
-            node_next = glb_cand[e];
-            w_next = glb_chc[e];
-        }
+        if (__builtin_expect(c < R, 1))
+            load_row_near(c);
+        else
+            load_row_far(c);
     };
 
     // One candidate-phase step k reading its draws at lnbuf[4jG + r] and the
     // row loaded ahead for the current city; `mid` runs before the row's
     // first use (independent work that fills the loads' latency).
     auto cand_step = [&](int k, int j, auto&& mid) {
-        const uint32_t node = node_next;
+        // (a bitmask's visited test does not look at the bits above 16, so the
+        // city is not widened on its chain)
+        uint32_t node_raw, node_word = 0u;
+        if constexpr (kTabu == MMAS_TABU_BITMASK) {
+            asm("v_bfe_u32 %0, %1, 5, 11" : "=v"(node_word) : "v"(node_next));
+            asm("v_mov_b32 %0, %1" : "=v"(node_raw) : "v"(node_next));
+        } else {
+            asm("v_and_b32 %0, 0xffff, %1" : "=v"(node_raw) : "v"(node_next));
+        }
         const float w = w_next;
         mid();
         const float lnu = lds_ln[4 * j * G + ln_lane];
-        const uint32_t seen = tabu.seen(node);
+        uint32_t seen = 0u, cell = 0u;
+        if constexpr (kTabu == MMAS_TABU_BITMASK)
+            seen = (uint32_t)__builtin_amdgcn_sbfe((int)*(LdsPtr<const uint32_t>)(cells + 4u * node_word), node_raw, 1u);
+        else
+            cell = tabu.cell(node_raw);
+        if constexpr (kTabu != MMAS_TABU_BITMASK) {
+            // (both LDS reads go out before the product waits for the first)
+            __builtin_amdgcn_sched_barrier(0);
+            seen = tabu.seen(node_raw, cell);
+        }
         float key = lnu * w;  // (w holds 1 / choice_info)
         asm volatile("" : "+v"(key));
         // ln(u) < 0 and w >= 0 give a key with the sign bit set (a negative
         // number, -0 or -inf), whose order code is ~bits (kApprox: the key is
         // approximate, and the exact ones settle a near tie)
         const uint32_t code = ~__float_as_uint(key) & ~seen & lane_ok;
-        const uint32_t best = wave_max_u32<kRows>(code);
-        uint32_t next = kNone;
-        if (best != 0u) {
-            const uint64_t tied = __ballot(code >= (kApprox ? near_code(best) : best));
-            const int first = (int)__builtin_ctzll(tied);
-            next = (uint32_t)__builtin_amdgcn_readlane((int)node, first);
-            if (__builtin_expect(first != 63 - (int)__builtin_clzll(tied), 0)) {
-                uint32_t c = code, top = best;
+        // (for cl <= 32 only the first half's maximum counts: lanes past the
+        // list have no code, so none of them holds or is near it)
+        const uint32_t top = rows_max_lanes<kRows>(code);
+        const uint64_t tied = __ballot(kApprox ? code >= near_code(top) : code == top) & (kRows == 2 ? 0xFFFFFFFFull : ~0ull);
+        const int first = (int)__builtin_ctzll(tied | (1ull << 63));
+        uint32_t next = (uint32_t)__builtin_amdgcn_readlane((int)node_raw, first) & 0xFFFFu;
+        // the chosen city's cell (compact and list tabus)
+        int at = __builtin_amdgcn_readlane((int)cell, first);
+        if (__builtin_expect(__popcll(tied) != 1, 0)) {
+            const uint32_t node = node_raw & 0xFFFFu;
+            const uint32_t best = (uint32_t)__builtin_amdgcn_readfirstlane((int)top);
+            if (best == 0u) {
+                next = fallback(k);
+            } else {
+                uint32_t c = code, t = best;
                 if constexpr (kApprox) {
-                    c = step_exact_code(seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)lane, w, ~seen & lane_ok);
-                    top = wave_max_u32<kRows>(c);
+                    c = step_exact_code(opaque(item)->s.seed, it, (uint32_t)ant, (uint32_t)k, (uint32_t)lane, w,
+                                        ~seen & lane_ok);
+                    t = wave_max_u32<kRows>(c);
                 }
-                next = wave_min_u32<kRows>(c == top ? node : kNone);
+                next = wave_min_u32<kRows>(c == t ? node : kNone);
             }
+            if constexpr (kTabu != MMAS_TABU_BITMASK) at = __builtin_amdgcn_readfirstlane((int)tabu.cell(next));
         }
-        if (__builtin_expect(next == kNone, 0)) next = fallback(k);
-        load_row((int)next);
-        advance(next, k);
+        // (the move is written out for both kinds of row: as one piece of code
+        // after the loads it cost the compiler two more branches a step)
+        if (__builtin_expect((int)next < R, 1)) {
+            load_row_near((int)next);
+            advance(next, at, k);
+        } else {
+            load_row_far((int)next);
+            advance(next, at, k);
+        }
     };
 
     // after the steps before ke: at the end of a 64-step chunk or of the
@@ -1242,7 +1208,10 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
 
     if (cl == 0) {
         for (int k = 1; k < n; ++k) {
-            advance(fallback(k), k);
+            const uint32_t next = fallback(k);
+            int at = 0;
+            if constexpr (kTabu != MMAS_TABU_BITMASK) at = __builtin_amdgcn_readfirstlane((int)tabu.cell(next));
+            advance(next, at, k);
             flush(k + 1);
         }
     } else if constexpr (kG > 0 && kHelp) {
@@ -1260,7 +1229,6 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
             lds_put(&hl->read, g + 1);  // after the group's last read of its buffer
             flush(ke);
         }
-        lds_put(&hl->stop, 1);
     } else if constexpr (kG > 0) {
         load_row(cur);
         // Draws computed one group ahead, spread over the steps of the group
@@ -1326,14 +1294,14 @@ __device__ void construct_lone(const Views& vw, const Shape& s, uint32_t it, int
         }
     }
     if constexpr (kWide) wide_lead_end(wl, lane);
-    if (bad && lane == 0) atomicOr(&vw.state->flags, 8u);
-    if (bad_help && lane == 0) atomicOr(&vw.state->flags, 32u);
+    if (bad && lane == 0) atomicOr(&item->v.state->flags, 8u);
+    if (bad_help && lane == 0) atomicOr(&item->v.state->flags, 32u);
     if (lane == 0) len += dist[(size_t)cur * n + start];  // closing edge
     len = wave_sum_i64(len);
     if (lane == 0) {
-        vw.lengths[ant] = len;
-        vw.fallback[ant] = fb_steps;
-        vw.fallback[s.ants + ant] = fb_nodes;
+        item->v.lengths[ant] = len;
+        item->v.fallback[ant] = fb_steps;
+        item->v.fallback[item->s.ants + ant] = fb_nodes;
     }
 }
 
@@ -1380,7 +1348,7 @@ __device__ __attribute__((noinline)) uint32_t fallback_item(ItemPtr item_v, LdsP
     q.it = uni(it);
     q.ant = uni(ant);
     q.step = (uint32_t)k;
-    const int cap = item->s.list_cap > 0 ? item->s.list_cap : (n < kListCap ? n : kListCap);
+    const int cap = list_cap(n, item->s.list_cap);
     return fallback_wave<kTabu, kPher>(
         q, (LdsPtr<uint16_t>)(region + (uint32_t)(kDrawBytes + kScratchBytes) + (uint32_t)align16(4 * ((n + 31) / 32))),
         cap, lane);
@@ -1454,14 +1422,14 @@ __device__ __forceinline__ void construct_pair(ItemPtr item, uint32_t it, int an
     const int G = 1 << gsh;
     const int S = 32 >> gsh;
     const int lr = hl < cl ? hl : cl - 1;
-    const uint32_t lane_ok = hl < cl ? ~0u : 0u;
+    uint32_t lane_ok = hl < cl ? ~0u : 0u;
     const uint32_t ln_lane = (uint32_t)(uintptr_t)(LdsPtr<float>)lnbuf + 4u * (uint32_t)(hl & (4 * G - 1));
     // bitmask marks, both in one LDS OR issued by every lane: lane 0 sets A's
     // bit, lane 32 B's, the others OR zero into their own word of the draw
     // buffer (a field of no bits gives them offset 0, and their "bit" is 0)
     uint32_t mark_bits = hl == 0 ? 11u : 0u, mark_one = hl == 0 ? 1u : 0u;
     uint32_t mark_base = hl == 0 ? cells : (uint32_t)(uintptr_t)(LdsPtr<float>)lnbuf + 4u * (uint32_t)hl;
-    asm volatile("" : "+v"(mark_bits), "+v"(mark_one), "+v"(mark_base));
+    asm volatile("" : "+v"(mark_bits), "+v"(mark_one), "+v"(mark_base), "+v"(lane_ok));
 
     uint32_t tbuf = (uint32_t)(h ? startB : startA);  // lane 32h + (k & 31) holds the city of step k
     uint32_t prev_last = 0;
@@ -1520,11 +1488,9 @@ __device__ __forceinline__ void construct_pair(ItemPtr item, uint32_t it, int an
             // log2(u) < 0 and w >= 0: the key's sign bit is set, its order code
             // is ~bits (approximate keys: device.hpp)
             const uint32_t code = ~__float_as_uint(key) & ~seen & lane_ok;
-            uint32_t bestA, bestB;
-            half_max_u32(code, bestA, bestB);
             // (no code is near a best of 0)
-            const uint32_t tA = (uint32_t)__ballot(code >= near_code(bestA));
-            const uint32_t tB = (uint32_t)(__ballot(code >= near_code(bestB)) >> 32);
+            const uint64_t tied = __ballot(code >= near_code(half_max_lanes(code)));
+            const uint32_t tA = (uint32_t)tied, tB = (uint32_t)(tied >> 32);
             uint32_t nextA = (uint32_t)__builtin_amdgcn_readlane((int)node, __builtin_ctz(tA | 0x80000000u));
             uint32_t nextB = (uint32_t)__builtin_amdgcn_readlane((int)node, 32 + __builtin_ctz(tB | 0x80000000u));
             const int cntA = __builtin_popcount(tA), cntB = __builtin_popcount(tB);
@@ -1601,20 +1567,18 @@ template <int kTabu, int kPher, bool kPair, int kRows = 4, int kG = 0, bool kHel
 __global__ __launch_bounds__(1024) void k_construct(Views vw, Shape s, uint32_t it, int ants_per_block, Lds lds) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = threadIdx.x & 63;
-    // (two ants per wave: wave-uniform values in scalar registers)
-    const int wave = kPair ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const ItemPtr item = kernel_item();
     const int R = lds.rows;
     uint16_t* tcand = reinterpret_cast<uint16_t*>(smem);
     float* tchc = reinterpret_cast<float*>(smem + align16(R * s.cl * 2));
     uint8_t* regions = smem + lds.table_bytes;
     if (R > 0) stage_table(vw, s.cl, R, tcand, tchc);
     if constexpr (kHelp) {
-        // every ant's HelpLds starts at 0 (three 16-byte stores each)
-        if ((int)threadIdx.x < 3 * ants_per_block) {
-            const int a = (int)threadIdx.x / 3, q = (int)threadIdx.x % 3;
-            *reinterpret_cast<int4*>(regions + (size_t)(a + 1) * lds.per_ant - sizeof(HelpLds) + 16 * q) =
+        // every ant's HelpLds starts at 0
+        if ((int)threadIdx.x < ants_per_block)
+            *reinterpret_cast<int4*>(regions + (size_t)(threadIdx.x + 1) * lds.per_ant - sizeof(HelpLds)) =
                 make_int4(0, 0, 0, 0);
-        }
     }
     if (R > 0 || kHelp) __syncthreads();
     const bool helper = kHelp && wave >= ants_per_block;
@@ -1625,20 +1589,18 @@ __global__ __launch_bounds__(1024) void k_construct(Views vw, Shape s, uint32_t 
         uint8_t* region = regions + (size_t)aw * lds.per_ant;
         uint8_t* help = region + lds.per_ant - kHelpBytes;
         if (helper)
-            draw_helper<kTabu, kPher, kG>(vw, s, it, ant, lane, region, help);
+            draw_helper<kG>(item, it, ant, lane, region, help);
         else
-            construct_lone<kTabu, kPher, kRows, kG, false, true>(vw, s, it, ant, lane, region, tcand, tchc, R,
+            construct_lone<kTabu, kPher, kRows, kG, false, true>(item, it, ant, lane, region, tcand, tchc, R,
                                                                  nullptr, 1, help);
         return;
     }
     if constexpr (kPair) {
-        // (the kernel's first two arguments are laid out as a BatchItem)
-        const ItemPtr item = (ItemPtr)__builtin_amdgcn_kernarg_segment_ptr();
         construct_pair<kTabu, kPher, true>(item, it, ant, lane, regions + (size_t)(2 * wave) * lds.per_ant,
                                            regions + (size_t)(2 * wave + 1) * lds.per_ant, tcand, tchc, R);
     }
     else
-        construct_lone<kTabu, kPher, kRows, kG>(vw, s, it, ant, lane, regions + (size_t)wave * lds.per_ant, tcand,
+        construct_lone<kTabu, kPher, kRows, kG>(item, it, ant, lane, regions + (size_t)wave * lds.per_ant, tcand,
                                                 tchc, R);
 }
 
@@ -1653,6 +1615,7 @@ __global__ __launch_bounds__(1024) void k_construct_wide(Views vw, Shape s, uint
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nw = (int)(blockDim.x >> 6);
+    const ItemPtr item = kernel_item();
     const int R = lds.rows;
     uint16_t* tcand = reinterpret_cast<uint16_t*>(smem);
     float* tchc = reinterpret_cast<float*>(smem + align16(R * s.cl * 2));
@@ -1660,11 +1623,11 @@ __global__ __launch_bounds__(1024) void k_construct_wide(Views vw, Shape s, uint
     __syncthreads();
     uint8_t* region = smem + lds.table_bytes;
     if (wave > 0) {
-        wide_helpers<kTabu, kPher>(vw, s, it, (int)blockIdx.x, lane, region, &wl, wave, nw);
+        wide_helpers<kTabu, kPher>(item, it, (int)blockIdx.x, lane, region, &wl, wave, nw);
         return;
     }
     // the leading wave: the single-colony step, its fallbacks shared
-    construct_lone<kTabu, kPher, kRows, kG, true>(vw, s, it, (int)blockIdx.x, lane, region, tcand, tchc, R, &wl, nw);
+    construct_lone<kTabu, kPher, kRows, kG, true>(item, it, (int)blockIdx.x, lane, region, tcand, tchc, R, &wl, nw);
 }
 
 // Without candidate lists, up to 4096 cities: a team of W waves per ant and no
@@ -1826,6 +1789,9 @@ __global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, ui
     }
 }
 
+static_assert(offsetof(BatchItem, v) == 0 && offsetof(BatchItem, s) == sizeof(Views) && alignof(Shape) == alignof(Views),
+              "kernel_item reads the kernel's first two arguments");
+
 // Batched construction: a persistent grid pulls tiles (instance, first ant of
 // a group of ants_per_block ants) from a queue ordered by decreasing n. Each
 // tile stages as many candidate rows of its instance as fit in the table part
@@ -1870,7 +1836,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
                                                      regions + (size_t)(2 * wave) * per_ant,
                                                      regions + (size_t)(2 * wave + 1) * per_ant, tcand, tchc, R);
             else
-                construct_ant<kTabu, kPher>(vw, s, it, ant, lane, regions + (size_t)wave * per_ant, tcand, tchc, R);
+                construct_ant<kTabu, kPher>((ItemPtr)&items[inst], it, ant, lane, regions + (size_t)wave * per_ant, tcand, tchc, R);
         }
         __syncthreads();  // the next tile reuses the table part
     }
@@ -2095,7 +2061,7 @@ size_t construct_lds_per_ant(const Shape& s) {
     // draws; tabu (bitmask words, or compact entries); for the bitmask, the
     // list of unvisited cities built in a fallback
     const int bits = align16(4 * ((s.n + 31) / 32));
-    const int tab = s.tabu == MMAS_TABU_BITMASK ? bits + align16(2 * list_cap(s))
+    const int tab = s.tabu == MMAS_TABU_BITMASK ? bits + align16(2 * list_cap(s.n, s.list_cap))
                     : s.tabu == MMAS_TABU_COMPACT ? align16(2 * s.n) : align16(4 * s.n);
     return kDrawBytes + kScratchBytes + tab;
 }
