@@ -27,11 +27,11 @@ struct mmas_batch {
     std::vector<mmas::BatchItem> items;
     std::vector<int> order;  // instances by decreasing n
     mmas::BatchItem* d_items;
-    int* d_row_start;
+    mmas::BatchTile* d_update_tiles;
     mmas::BatchTile* d_tiles;
     uint32_t* d_it;
     uint32_t* d_queue;
-    int total_rows;
+    int update_tiles;
     int max_tiles;
     int tabu, pher;
     int per_ant;        // largest per-ant LDS region over the instances (current tabu)
@@ -62,16 +62,16 @@ constexpr int kStaticLds = 64;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 struct Header {
-    size_t items, row_start, tiles, counters, end;
+    size_t items, update_tiles, tiles, counters, end;
 };
 
-Header header_layout(int count, size_t total_ants) {
+Header header_layout(int count, size_t total_ants, size_t total_rows) {
     Header h{};
     size_t pos = 0;
     h.items = pos;
     pos = align_up(pos + sizeof(mmas::BatchItem) * (size_t)count);
-    h.row_start = pos;
-    pos = align_up(pos + sizeof(int) * (size_t)(count + 1));
+    h.update_tiles = pos;
+    pos = align_up(pos + sizeof(mmas::BatchTile) * total_rows);  // worst case: one row per tile
     h.tiles = pos;
     pos = align_up(pos + sizeof(mmas::BatchTile) * total_ants);  // worst case: one ant per tile
     h.counters = pos;
@@ -126,7 +126,8 @@ mmas_status launch_step(mmas_batch* b) {
             b->spare.push_back(ev);
     }
     if (e != hipSuccess) return mmas::hip_fail(e, "batched construction launch");
-    e = mmas::launch_batch_update(b->d_items, b->count, b->d_row_start, b->total_rows, b->d_it, b->d_queue, b->stream);
+    e = mmas::launch_batch_update(b->d_items, b->count, b->d_update_tiles, b->update_tiles, b->d_it, b->d_queue,
+                                  b->stream);
     return e == hipSuccess ? MMAS_OK : mmas::hip_fail(e, "batched update launch");
 }
 
@@ -170,14 +171,15 @@ extern "C" {
 
 mmas_status mmas_batch_workspace_bytes(int32_t count, const mmas_params* params, size_t* bytes) {
     if (count < 1 || !params || !bytes) return MMAS_EINVAL;
-    size_t total_ants = 0, sub = 0;
+    size_t total_ants = 0, total_rows = 0, sub = 0;
     for (int i = 0; i < count; ++i) {
         const size_t w = mmas_workspace_bytes(&params[i]);
         if (w == 0) return MMAS_EINVAL;
         sub += align_up(w);
         total_ants += (size_t)params[i].ants;
+        total_rows += (size_t)params[i].n;
     }
-    *bytes = header_layout(count, total_ants).end + sub;
+    *bytes = header_layout(count, total_ants, total_rows).end + sub;
     return MMAS_OK;
 }
 
@@ -204,11 +206,14 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
     b->ws = reinterpret_cast<char*>(dev_ws);
     b->tabu = params[0].tabu;
     b->pher = params[0].pher_mode;
-    size_t total_ants = 0;
-    for (int i = 0; i < count; ++i) total_ants += (size_t)params[i].ants;
-    const Header h = header_layout(count, total_ants);
+    size_t total_ants = 0, total_rows = 0;
+    for (int i = 0; i < count; ++i) {
+        total_ants += (size_t)params[i].ants;
+        total_rows += (size_t)params[i].n;
+    }
+    const Header h = header_layout(count, total_ants, total_rows);
     b->d_items = reinterpret_cast<mmas::BatchItem*>(b->ws + h.items);
-    b->d_row_start = reinterpret_cast<int*>(b->ws + h.row_start);
+    b->d_update_tiles = reinterpret_cast<mmas::BatchTile*>(b->ws + h.update_tiles);
     b->d_tiles = reinterpret_cast<mmas::BatchTile*>(b->ws + h.tiles);
     b->d_it = reinterpret_cast<uint32_t*>(b->ws + h.counters);
     b->d_queue = b->d_it + 1;
@@ -216,7 +221,7 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
     size_t pos = h.end;
     b->ctx.assign(count, nullptr);
     b->items.resize(count);
-    std::vector<int> row_start(count + 1, 0);
+    std::vector<mmas::BatchTile> rows;
     b->per_ant = 0;
     b->per_ant_tabu[0] = b->per_ant_tabu[1] = b->per_ant_tabu[2] = 0;
     for (int i = 0; i < count; ++i) {
@@ -230,7 +235,8 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
         }
         pos += align_up(w);
         mmas::ctx_views(b->ctx[i], &b->items[i].v, &b->items[i].s);
-        row_start[i + 1] = row_start[i] + b->items[i].s.n;
+        const int tile = mmas::update_tile_rows(b->items[i].s);
+        for (int r0 = 0; r0 < b->items[i].s.n; r0 += tile) rows.push_back(mmas::BatchTile{i, r0});
         b->per_ant = std::max(b->per_ant, (int)mmas::construct_lds_per_ant(b->items[i].s));
         for (int t = 0; t < 3; ++t) {
             mmas::Shape st = b->items[i].s;
@@ -238,7 +244,7 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
             b->per_ant_tabu[t] = std::max(b->per_ant_tabu[t], (int)mmas::construct_lds_per_ant(st));
         }
     }
-    b->total_rows = row_start[count];
+    b->update_tiles = (int)rows.size();
     b->order.resize(count);
     std::iota(b->order.begin(), b->order.end(), 0);
     std::stable_sort(b->order.begin(), b->order.end(),
@@ -247,7 +253,8 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
     hipError_t e = hipMemcpyAsync(b->d_items, b->items.data(), sizeof(mmas::BatchItem) * count, hipMemcpyHostToDevice,
                                   b->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(b->d_row_start, row_start.data(), sizeof(int) * (count + 1), hipMemcpyHostToDevice, b->stream);
+        e = hipMemcpyAsync(b->d_update_tiles, rows.data(), sizeof(mmas::BatchTile) * rows.size(), hipMemcpyHostToDevice,
+                           b->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(b->d_it, zero, sizeof(zero), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
@@ -257,10 +264,19 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
     }
     b->pair_ok = true;
     for (int i = 0; i < count; ++i) b->pair_ok = b->pair_ok && b->items[i].s.cl >= 1 && b->items[i].s.cl <= 32;
-    b->ants_per_block = 4;
-    b->lanes_per_ant = 64;
-    b->table_request = -1;
-    b->table_bytes = std::max(0, (mmas::max_lds_per_block() - kStaticLds - b->ants_per_block * b->per_ant) & ~15);
+    // Without a launch asked for: two ants per wave, eight per workgroup and no
+    // LDS table (rows from L2; a table leaves fewer waves per SIMD to hide the
+    // steps' chains), the fastest or within 3 % of it from 512 to 20 thousand
+    // ants: 160 colonies of 64 ants, n 200-1000: 1.21 ms a step against 3.62
+    // with one ant per wave, four per workgroup and a full table, and 1.41
+    // without the table; 20 instances with ants = n: 1.59, 9.49 and 2.51 ms.
+    // Lists longer than 32 take one ant per wave, with the table only while
+    // every workgroup has a CU of its own.
+    const int lds = mmas::max_lds_per_block() - kStaticLds;
+    b->lanes_per_ant = b->pair_ok ? 32 : 64;
+    b->ants_per_block = b->pair_ok && 8 * b->per_ant <= lds ? 8 : 4;
+    b->table_request = b->pair_ok || (int64_t)total_ants > 4 * (int64_t)mmas::compute_units() ? 0 : -1;
+    b->table_bytes = b->table_request < 0 ? std::max(0, (lds - b->ants_per_block * b->per_ant) & ~15) : 0;
     r = rebuild_tiles(b);
     if (r != MMAS_OK) {
         for (mmas_ctx* c : b->ctx) mmas_destroy(c);

@@ -1864,6 +1864,7 @@ int device_attr(std::atomic<int>* cache, hipDeviceAttribute_t attr, int scale, i
 }  // namespace
 
 int max_lds_per_block() { return device_attr(g_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, 1, 65536); }
+int compute_units() { return device_attr(g_cus, hipDeviceAttributeMultiprocessorCount, 1, 0); }
 
 namespace {
 

@@ -29,6 +29,7 @@ struct Views {
     uint16_t* succ;     // n: successor of each city in the iteration best
     uint16_t* pred;     // n
     mmas_device_state* state;
+    uint32_t* ticket;   // workgroups done with the update (0 between updates)
 };
 
 // Problem constants every kernel needs.
@@ -63,7 +64,7 @@ struct BatchItem {
 };
 
 // One construction tile of a batch: ants ant0 .. ant0 + ants_per_block - 1
-// of instance `inst`.
+// of instance `inst` (an update tile: its rows from ant0 on).
 struct BatchTile {
     int inst;
     int ant0;
@@ -101,12 +102,16 @@ hipError_t launch_batch_construct(const BatchItem* items, const BatchTile* tiles
 // Persistent-grid size for this LDS footprint (workgroups that fit at once).
 int batch_construct_grid(int tabu, int pher, int ants_per_block, int lanes_per_ant, int table_bytes, int per_ant);
 // update.hip: best/limits for every instance (one workgroup each), then the
-// fused update of every row of every instance (`row_start` = prefix sums of
-// the instances' row counts, count + 1 entries); increments *it_dev and
-// re-arms *queue.
-hipError_t launch_batch_update(const BatchItem* items, int count, const int* row_start, int total_rows,
-                               uint32_t* it_dev, uint32_t* queue, hipStream_t st);
+// fused update of every row of every instance by `tiles` (instance, first
+// row): update_tile_rows(s) rows each; increments *it_dev and re-arms *queue.
+hipError_t launch_batch_update(const BatchItem* items, int count, const BatchTile* tiles, int ntiles, uint32_t* it_dev,
+                               uint32_t* queue, hipStream_t st);
+// Cities up to which one wave updates a row of dense trails (a workgroup four
+// rows); a longer row takes a workgroup.
+constexpr int kRowWave = 2048;
+inline int update_tile_rows(const Shape& s) { return s.pher == MMAS_PHER_DENSE && s.n > kRowWave ? 1 : 4; }
 int max_lds_per_block();
+int compute_units();
 
 // ---- learned heuristic (learned.hip) ----
 int mlp_param_count();

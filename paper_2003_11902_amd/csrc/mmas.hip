@@ -26,7 +26,7 @@ struct mmas_ctx {
     size_t ws_bytes;
     size_t off[MMAS_BUF_COUNT];
     size_t len[MMAS_BUF_COUNT];
-    size_t off_succ, off_pred, off_nnd, off_inv, off_cinv;
+    size_t off_succ, off_pred, off_nnd, off_inv, off_cinv, off_ticket;
     bool choice_stale;
     bool constructed;
     // per-call timing (mmas_set_timing): event pairs not yet read, and the totals
@@ -88,7 +88,7 @@ Shape shape_of(const mmas_params* p) {
 
 // Byte sizes of every view, then their offsets (256-byte aligned).
 size_t layout(const Shape& s, size_t* off, size_t* len, size_t* off_succ, size_t* off_pred, size_t* off_nnd,
-              size_t* off_inv, size_t* off_cinv) {
+              size_t* off_inv, size_t* off_cinv, size_t* off_ticket) {
     const size_t n = (size_t)s.n, cl = (size_t)s.cl, ants = (size_t)s.ants;
     const bool dense = s.pher == MMAS_PHER_DENSE;
     len[MMAS_BUF_DIST] = 4 * n * n;
@@ -109,6 +109,8 @@ size_t layout(const Shape& s, size_t* off, size_t* len, size_t* off_succ, size_t
         off[b] = pos;
         pos = align_up(pos + len[b]);
     }
+    *off_ticket = pos;  // of the update
+    pos = align_up(pos + sizeof(uint32_t));
     *off_succ = pos;
     pos = align_up(pos + 2 * n);
     *off_pred = pos;
@@ -209,8 +211,8 @@ extern "C" {
 size_t mmas_workspace_bytes(const mmas_params* p) {
     if (!params_ok(p)) return 0;
     Shape s = shape_of(p);
-    size_t off[MMAS_BUF_COUNT], len[MMAS_BUF_COUNT], os, op, od, oi, oc;
-    return layout(s, off, len, &os, &op, &od, &oi, &oc);
+    size_t off[MMAS_BUF_COUNT], len[MMAS_BUF_COUNT], os, op, od, oi, oc, ot;
+    return layout(s, off, len, &os, &op, &od, &oi, &oc, &ot);
 }
 
 mmas_status mmas_create(const int32_t* dist_host, const mmas_params* p, void* dev_ws, size_t ws_bytes,
@@ -227,7 +229,8 @@ mmas_status mmas_create(const int32_t* dist_host, const mmas_params* p, void* de
     c->stream = reinterpret_cast<hipStream_t>(hip_stream);
     c->ws = reinterpret_cast<char*>(dev_ws);
     c->ws_bytes = ws_bytes;
-    const size_t need = layout(s, c->off, c->len, &c->off_succ, &c->off_pred, &c->off_nnd, &c->off_inv, &c->off_cinv);
+    const size_t need = layout(s, c->off, c->len, &c->off_succ, &c->off_pred, &c->off_nnd, &c->off_inv, &c->off_cinv,
+                               &c->off_ticket);
     if (ws_bytes < need) {
         delete c;
         return MMAS_ENOSPACE;
@@ -265,11 +268,13 @@ mmas_status mmas_create(const int32_t* dist_host, const mmas_params* p, void* de
     v.choice_inv = c->len[MMAS_BUF_CHOICE] ? reinterpret_cast<float*>(b + c->off_cinv) : nullptr;
     v.succ = reinterpret_cast<uint16_t*>(b + c->off_succ);
     v.pred = reinterpret_cast<uint16_t*>(b + c->off_pred);
+    v.ticket = reinterpret_cast<uint32_t*>(b + c->off_ticket);
 
     hipStream_t st = c->stream;
     const char* step = "copy of the distance matrix";
     hipError_t e = hipMemcpyAsync(v.dist, dist_host, c->len[MMAS_BUF_DIST], hipMemcpyHostToDevice, st);
     if (e == hipSuccess && (step = "state reset")) e = hipMemsetAsync(v.state, 0, sizeof(mmas_device_state), st);
+    if (e == hipSuccess && (step = "ticket reset")) e = hipMemsetAsync(v.ticket, 0, sizeof(uint32_t), st);
     if (e == hipSuccess && (step = "validation")) e = mmas::launch_validate(v, s, st);
     if (e == hipSuccess && (step = "candidate lists")) e = mmas::launch_nearest(v.dist, s.n, s.cl, v.cand, st);
     if (e == hipSuccess && (step = "2-opt lists")) e = mmas::launch_nearest(v.dist, s.n, s.ls_nn, v.lsnn, st);

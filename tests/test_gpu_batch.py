@@ -153,3 +153,27 @@ def test_fallback_list_in_passes(gpu):
     for it in range(2):
         o.iterate(it, 8)
     assert np.array_equal(b.instance(2).tours(), o.tours())
+
+
+@pytest.mark.parametrize("cl,ants", [(32, 5), (40, 300), (40, 3), (0, 4)])
+def test_default_launch(gpu, cl, ants):
+    """The launch a batch has without set_launch or the tuner: two ants per
+    wave where every list fits, else one, with the LDS table only for few
+    ants; rows of one wave and of a workgroup (n above 2048) in the update."""
+    from paper_2003_11902_amd import mmas as M
+    dists, params = [], []
+    for k, n in enumerate((2049, 61, 254) if ants < 10 else (300, 258, 9)):
+        _, d = I.make_instance("uniform", n, seed=70 + k)
+        dists.append(d)
+        params.append(M.make_params(n, ants, cand_len=cl, rho=0.05, seed=7 + k))
+    say(f"default launch cl={cl} ants={ants}")
+    ref = singles(dists, params, 2)
+    b = M.Batch(dists, params)
+    for it in range(2):
+        b.step()
+        b.synchronize()
+        for k in range(len(dists)):
+            v = b.instance(k)
+            assert np.array_equal(v.tours(), ref[k][it][0])
+            assert np.array_equal(v.lengths(), ref[k][it][2])
+            assert np.array_equal(v.pheromone(), ref[k][it][1])

@@ -320,3 +320,17 @@ def test_team_blocks_per_lane(gpu, n, ants):
     _, d = I.make_instance("uniform", n, seed=n, side=1e5)
     say(f"team blocks n={n} ants={ants}")
     run_parity(d, 1, ants=ants, cand_len=0, rho=0.1, seed=4)
+
+
+@pytest.mark.parametrize("n,ants", [(3, 2), (5, 2048), (1024, 3), (1024, 2049), (1025, 3), (2048, 3), (2050, 3)])
+@pytest.mark.parametrize("deposit,problem", [("iteration", "tsp"), ("global", "atsp")])
+def test_update_sizes(gpu, n, ants, deposit, problem):
+    """The update in one launch and in two, one and four entries a thread:
+    trails, limits and best tours equal the oracle's on both sides of the
+    sizes where the launch changes."""
+    _, d = I.make_instance("uniform", n, seed=n, side=1e5)
+    if problem == "atsp":
+        d = I.asymmetric(d, 0.5, 3)
+    say(f"update n={n} ants={ants} {deposit} {problem}")
+    g, o, _ = run_parity(d, 3, ants=ants, cand_len=8, rho=0.2, seed=3, deposit=deposit, problem=problem)
+    assert np.array_equal(g.best()[0], o.best()[0])
