@@ -57,94 +57,250 @@ __global__ __launch_bounds__(256) void k_heur_cand(const int32_t* __restrict__ d
     }
 }
 
-// Row i: the k nearest other cities by (distance, index). Round r takes the
-// smallest (d, j) strictly above the one taken in round r-1.
+// Entries of a row that k_nearest sorts at once.
+constexpr int kNearCap = 256;
+
+// The k <= 64 nearest other cities of row i by (distance, index), one wave a
+// row: the row's entries fall into 128 groups (two per lane); the k-th
+// smallest group minimum, or a little more, bounds the k-th smallest entry, so
+// a second pass gathers the few entries up to that bound (37 of 3795 on
+// average for k = 32) and their ranks among each other are their places.
+// Reads the row twice where taking the next smallest entry k times read it k
+// times: n = 3795, k = 16: 184 -> 34 us, n = 1002, k = 32: 43 -> 8 us.
+// Rows with more than kNearCap entries up to the bound (long runs of equal
+// distances) take the smallest remaining entry k times.
 __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, int n, int k,
                                                  uint16_t* __restrict__ out) {
-    __shared__ uint64_t part[4];
-    const int i = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ uint64_t s_key[4][kNearCap];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int i = (int)blockIdx.x * 4 + wave;
+    if (i >= n) return;
     const int32_t* row = d + (size_t)i * n;
+    uint16_t* o = out + (size_t)i * k;
+    uint32_t m0 = ~0u, m1 = ~0u;
+    int j = lane;
+    for (; j + 3 * kWave < n; j += 4 * kWave) {
+        uint32_t x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = (uint32_t)row[j + u * kWave];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t v = j + u * kWave == i ? ~0u : x[u];
+            if (u & 1)
+                m1 = min(m1, v);
+            else
+                m0 = min(m0, v);
+        }
+    }
+    for (int u = 0; j < n; j += kWave, ++u) {
+        const uint32_t v = j == i ? ~0u : (uint32_t)row[j];
+        if (u & 1)
+            m1 = min(m1, v);
+        else
+            m0 = min(m0, v);
+    }
+    // the least bound under which at least k group minima lie, or one with up
+    // to eight more (bisection; every group but that of i alone has a minimum,
+    // and there are at least k such groups)
+    uint32_t lo = wave_min_u32<4>(min(m0, m1)), hi = ~0u - 1u;
+    {
+        const uint32_t g0 = m0 == ~0u ? 0u : m0, g1 = m1 == ~0u ? 0u : m1;
+        hi = wave_max_u32<4>(max(g0, g1));
+    }
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        const int c = __popcll(__ballot(m0 <= mid)) + __popcll(__ballot(m1 <= mid));
+        if (c < k)
+            lo = mid + 1;
+        else
+            hi = mid;
+        if (c >= k && c <= k + 8) break;
+    }
+    // the entries up to the bound
+    int m = 0;
+    for (int j0 = 0; j0 < n; j0 += kWave) {
+        const int q = j0 + lane;
+        const uint32_t v = q < n && q != i ? (uint32_t)row[q] : ~0u;
+        const uint64_t in = __ballot(v <= hi);
+        if (in) {
+            const int at = m + __popcll(in & ((1ull << lane) - 1ull));
+            if (v <= hi && at < kNearCap) s_key[wave][at] = ((uint64_t)v << 32) | (uint32_t)q;
+            m += __popcll(in);
+        }
+    }
+    if (__builtin_expect(m <= kNearCap, 1)) {
+        // (one wave's LDS operations complete in order)
+        for (int e = lane; e < ((m + kWave - 1) & ~(kWave - 1)); e += kWave) {
+            const uint64_t key = e < m ? s_key[wave][e] : ~0ull;
+            int rank = 0;
+            for (int q = 0; q < m; ++q) rank += s_key[wave][q] < key ? 1 : 0;
+            if (e < m && rank < k) o[rank] = (uint16_t)key;
+        }
+        // (a matrix that is refused may leave too few: any city keeps the
+        // later set-up steps in bounds)
+        for (int r = m + lane; r < k; r += kWave) o[r] = 0;
+        return;
+    }
     uint64_t prev = 0;  // keys are (d << 32 | j) with d >= 1 for j != i
     for (int r = 0; r < k; ++r) {
         uint64_t best = ~0ull;
-        for (int j = threadIdx.x; j < n; j += 256) {
-            if (j == i) continue;
-            const uint64_t key = ((uint64_t)(uint32_t)row[j] << 32) | (uint32_t)j;
-            if (key > prev && key < best) best = key;
+        for (int q = lane; q < n; q += kWave) {
+            const uint64_t key = ((uint64_t)(uint32_t)row[q] << 32) | (uint32_t)q;
+            if (q != i && key > prev && key < best) best = key;
         }
         best = wave_min_u64(best);
-        if (lane == 0) part[wave] = best;
-        __syncthreads();
-        uint64_t m = part[0];
-        for (int w = 1; w < 4; ++w) m = part[w] < m ? part[w] : m;
-        __syncthreads();
-        if (threadIdx.x == 0) out[(size_t)i * k + r] = (uint16_t)(m & 0xFFFFu);
-        prev = m;
+        if (lane == 0) o[r] = best == ~0ull ? (uint16_t)0 : (uint16_t)(best & 0xFFFFu);
+        prev = best;
     }
 }
 
-// Nearest-neighbour tour from city 0 (one wave; visited bits in LDS), then
-// its length. The candidate list is sorted by (d, index) and holds the cl
-// nearest cities, so when one of them is unvisited the first such is the
-// nearest unvisited city; only otherwise is the whole row scanned for the
-// smallest (d, index).
-__global__ __launch_bounds__(64) void k_nn_tour(const int32_t* __restrict__ d, const uint16_t* __restrict__ cand,
-                                                int cl, int n, uint16_t* __restrict__ tour,
-                                                mmas_device_state* __restrict__ st) {
-    extern __shared__ uint32_t vis[];  // ceil(n/32) words
-    const int lane = threadIdx.x;
-    const int words = (n + 31) >> 5;
-    for (int w = lane; w < words; w += kWave) vis[w] = 0u;
-    if (lane == 0) vis[0] = 1u;
-    int cur = 0;
-    uint32_t tbuf = 0;       // lane (k & 63) holds the city of step k
-    uint32_t prev_last = 0;  // last city of the previous 64-step chunk
+// LDS of the nearest-neighbour tour: visited bits, then the first `p` entries
+// of every candidate list.
+__host__ __device__ inline int nn_tour_bits(int n) { return (((n + 31) >> 5) * 4 + 15) & ~15; }
+
+// The smallest (distance, index) over the unvisited cities of a row, one
+// wave's share of it (cities w * 64 + lane, then every 64 nw): (distance, index)
+// packed, ~0 if none.
+__device__ __forceinline__ uint64_t nn_scan(const int32_t* __restrict__ row, int n, const uint32_t* vis, int w, int nw,
+                                            int lane) {
+    uint32_t bd = ~0u, bj = ~0u;
+    for (int j = w * kWave + lane; j < n; j += kWave * nw) {
+        const uint32_t v = (uint32_t)row[j];
+        const bool seen = (vis[j >> 5] >> (j & 31)) & 1u;
+        if (!seen && v < bd) {  // (ascending j: the first of equal distances)
+            bd = v;
+            bj = (uint32_t)j;
+        }
+    }
+    const uint32_t m = wave_min_u32<4>(bd);
+    const uint32_t jm = wave_min_u32<4>(bd == m ? bj : ~0u);
+    return jm == ~0u ? ~0ull : ((uint64_t)m << 32) | jm;
+}
+
+// The length of the tour the first wave has written (every thread of the
+// workgroup; the barrier before makes the tour visible to them).
+__device__ __forceinline__ void nn_length(const int32_t* __restrict__ d, int n, const uint16_t* tour, uint64_t* part,
+                                          mmas_device_state* __restrict__ st) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     int64_t len = 0;
-    for (int k = 1; k < n; ++k) {
-        int nxt = -1;
-        if (cl > 0) {
+    for (int k = threadIdx.x; k < n; k += blockDim.x)
+        len += d[(size_t)tour[k] * n + tour[k + 1 == n ? 0 : k + 1]];
+    len = wave_sum_i64(len);
+    if (lane == 0) part[wave] = (uint64_t)len;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < nw; ++w) len += (int64_t)part[w];
+        st->nn_len = len;
+    }
+}
+
+// Nearest-neighbour tour from city 0, then its length: one workgroup, whose
+// first wave walks. The candidate list is sorted by (d, index) and holds the
+// cl nearest cities, so when one of them is unvisited the first such is the
+// nearest unvisited city; the first p entries of every list are in LDS (a step
+// is then two LDS reads), the rest in global memory; only when all are visited
+// do all the waves scan the city's row for the smallest (d, index) (the others
+// wait at the barrier for that). n = 1002: 490 -> 240 us, n = 18512: 85 -> 10.4
+// ms (one wave, every list and scan from global memory).
+__global__ __launch_bounds__(1024) void k_nn_tour(const int32_t* __restrict__ d, const uint16_t* __restrict__ cand,
+                                                  int cl, int n, int p, uint16_t* __restrict__ tour,
+                                                  mmas_device_state* __restrict__ st) {
+    extern __shared__ uint32_t vis[];  // ceil(n/32) words, then the table
+    __shared__ uint64_t part[16];
+    __shared__ int s_cur;  // the city whose row is to be scanned, -1: the tour is done, -2: it failed
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint16_t* tab = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(vis) + nn_tour_bits(n));
+    const int words = (n + 31) >> 5;
+    for (int w = threadIdx.x; w < words; w += blockDim.x) vis[w] = w == 0 ? 1u : 0u;
+    // (lists and table start 16-byte aligned: eight entries at once where whole
+    // lists are kept, four where both lengths are multiples of four)
+    int done = 0;
+    if (p == cl) {
+        const int q = n * cl >> 3;
+#pragma unroll 4
+        for (int e = threadIdx.x; e < q; e += blockDim.x)
+            reinterpret_cast<uint4*>(tab)[e] = reinterpret_cast<const uint4*>(cand)[e];
+        done = 8 * q;
+    } else if (p > 0 && ((p | cl) & 3) == 0) {
+        const int pq = p >> 2, cq = cl >> 2;
+#pragma unroll 4
+        for (int e = threadIdx.x; e < n * pq; e += blockDim.x)
+            reinterpret_cast<uint2*>(tab)[e] = reinterpret_cast<const uint2*>(cand)[(size_t)(e / pq) * cq + e % pq];
+        done = n * p;
+    }
+    for (int e = done + threadIdx.x; e < n * p; e += blockDim.x) tab[e] = cand[(size_t)(e / p) * cl + e % p];
+    __syncthreads();
+    if (wave > 0) {
+        for (;;) {
+            __syncthreads();  // a city to scan, or the end
+            const int c = __builtin_amdgcn_readfirstlane(s_cur);
+            if (c < 0) {
+                if (c == -1) nn_length(d, n, tour, part, st);
+                return;
+            }
+            const uint64_t m = nn_scan(d + (size_t)c * n, n, vis, wave, nw, lane);
+            if (lane == 0) part[wave] = m;
+            __syncthreads();  // the waves' results
+        }
+    }
+    // the nearest unvisited city past the first p candidates (rare)
+    auto far_city = [&](int cur) -> int {
+        if (p < cl) {
             const uint32_t c = cand[(size_t)cur * cl + (lane < cl ? lane : cl - 1)];
             const bool free = (lane < cl) & !((vis[c >> 5] >> (c & 31)) & 1u);
             const uint64_t m = __ballot(free);
-            if (m) nxt = __builtin_amdgcn_readlane((int)c, __ffsll((unsigned long long)m) - 1);
+            if (m) return __builtin_amdgcn_readlane((int)c, (int)__builtin_ctzll(m));
         }
-        if (nxt < 0) {
-            const int32_t* row = d + (size_t)cur * n;
-            uint64_t best = ~0ull;
-            for (int j = lane; j < n; j += kWave) {
-                const uint64_t key = ((uint64_t)(uint32_t)row[j] << 32) | (uint32_t)j;
-                const bool seen = (vis[j >> 5] >> (j & 31)) & 1u;
-                best = (!seen && key < best) ? key : best;
-            }
-            const uint64_t m = wave_min_u64(best);
-            if (m == ~0ull) {  // no unvisited city: unreachable for k < n
-                if (lane == 0) atomicOr(&st->flags, 8u);
-                return;
-            }
-            nxt = (int)(m & 0xFFFFFFFFu);
+        if (lane == 0) s_cur = cur;
+        __syncthreads();
+        const uint64_t own = nn_scan(d + (size_t)cur * n, n, vis, 0, nw, lane);
+        if (lane == 0) part[0] = own;
+        __syncthreads();
+        const uint64_t r = lane < nw ? part[lane] : ~0ull;
+        const uint32_t rd = (uint32_t)(r >> 32), m = wave_min_u32<4>(rd);
+        return (int)wave_min_u32<4>(rd == m ? (uint32_t)r : ~0u);  // -1: no unvisited city
+    };
+    int cur = 0;
+    uint32_t tbuf = 0;  // lane (k & 63) holds the city of step k
+    bool failed = false;
+    const int lp = lane < p ? lane : p - 1;
+    const uint64_t listed = p >= 64 ? ~0ull : (1ull << p) - 1ull;
+    for (int k = 1; k < n; ++k) {
+        uint64_t m = 0ull;
+        uint32_t c = 0u, word = 0u;
+        if (p > 0) {
+            c = tab[cur * p + lp];
+            word = vis[c >> 5];
+            m = __ballot(__builtin_amdgcn_ubfe(word, c, 1u) == 0u) & listed;
         }
-        if (lane == 0) vis[nxt >> 5] |= 1u << (nxt & 31);
-        const int slot = k & 63;
-        if (lane == slot) tbuf = (uint32_t)nxt;
-        cur = nxt;
-        if (slot == 63 || k == n - 1) {
-            const int k0 = k - slot;
-            const uint32_t prev = __shfl_up(tbuf, 1);
-            if (lane <= slot) {
-                tour[k0 + lane] = (uint16_t)tbuf;
-                const uint32_t from = lane == 0 ? prev_last : prev;
-                if (k0 + lane > 0) len += d[(size_t)from * n + tbuf];
+        if (__builtin_expect(m != 0ull, 1)) {
+            const int f = (int)__builtin_ctzll(m);
+            cur = __builtin_amdgcn_readlane((int)c, f);
+            word = (uint32_t)__builtin_amdgcn_readlane((int)word, f);
+        } else {
+            cur = __builtin_amdgcn_readfirstlane(far_city(cur));
+            if (cur < 0) {  // unreachable for k < n
+                failed = true;
+                break;
             }
-            prev_last = (uint32_t)__builtin_amdgcn_readlane((int)tbuf, slot);
+            word = (uint32_t)__builtin_amdgcn_readfirstlane((int)vis[cur >> 5]);
+        }
+        // (the only wave that writes; every lane stores the same word)
+        vis[cur >> 5] = word | (1u << (cur & 31));
+        if (lane == (k & 63)) tbuf = (uint32_t)cur;
+        if ((k & 63) == 63 || k == n - 1) {
+            const int at = (k & ~63) + lane;
+            if (at <= k) tour[at] = (uint16_t)tbuf;
         }
     }
-    if (lane == 0) {
-        tour[0] = 0;
-        len += d[(size_t)cur * n];  // closing edge back to city 0
+    if (lane == 0) s_cur = failed ? -2 : -1;
+    __syncthreads();  // the others leave the scans
+    if (failed) {
+        if (lane == 0) atomicOr(&st->flags, 8u);
+        return;
     }
-    len = wave_sum_i64(len);
-    if (lane == 0) st->nn_len = len;
+    nn_length(d, n, tour, part, st);
 }
 
 __global__ void k_init_state(mmas_device_state* st, float rho, int n, double pdec) {
@@ -197,13 +353,24 @@ hipError_t launch_heuristic(const Views& v, const Shape& s, hipStream_t st) {
 
 hipError_t launch_nearest(const int32_t* dist, int n, int k, uint16_t* out, hipStream_t st) {
     if (k <= 0) return hipSuccess;
-    k_nearest<<<n, 256, 0, st>>>(dist, n, k, out);
+    k_nearest<<<(n + 3) / 4, 256, 0, st>>>(dist, n, k, out);
     return hipGetLastError();
 }
 
 hipError_t launch_nn_tour(const Views& v, const Shape& s, hipStream_t st) {
-    const size_t lds = sizeof(uint32_t) * (size_t)((s.n + 31) / 32);
-    k_nn_tour<<<1, kWave, lds, st>>>(v.dist, v.cand, s.cl, s.n, v.nn_tour, v.state);
+    // as many list entries per city as LDS holds (its static part aside)
+    const int bits = nn_tour_bits(s.n), room = max_lds_per_block() - 256 - bits;
+    int p = room > 0 ? room / (2 * s.n) : 0;
+    if (p > s.cl) p = s.cl;
+    if (p < s.cl && p >= 4) p &= ~3;
+    const size_t lds = (size_t)bits + 2 * (size_t)p * s.n;
+    if (lds > 64 * 1024) {
+        const hipError_t e =
+            hipFuncSetAttribute((const void*)k_nn_tour, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    // (the waves past the first only scan rows: sixteen where rows are long)
+    k_nn_tour<<<1, s.n >= 1024 ? 1024 : 256, lds, st>>>(v.dist, v.cand, s.cl, s.n, p, v.nn_tour, v.state);
     return hipGetLastError();
 }
 
