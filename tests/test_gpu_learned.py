@@ -195,3 +195,32 @@ def test_learned_heuristic_reaches_plain_quality_sooner(gpu):
     recs = L.time_to_gap(params, d, xy, seeds=[1, 2], budget=150, ants=200, log=say)
     for r in recs:
         assert r["learned_iters"] is not None and r["learned_iters"] < 75, r
+
+
+@pytest.mark.parametrize("E,groups", [(1, 1), (15, 2), (16, 1), (17, 3), (127, 1), (128, 2), (129, 300), (1000, 3)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_mlp_edge_counts(gpu, E, groups, shift):
+    """Edge counts around a wave's 16 and a workgroup's 128, fewer tiles than
+    workgroups, and inputs aligned to one value only: scores and gradients
+    against the float64 network with the same bfloat16 rounding points (within
+    the rounding of one bfloat16 step, 2^-8, of the largest sum)."""
+    from oracle import oracle as O
+    from paper_2003_11902_amd import mmas as M
+    P = rand_params(O, 11)
+    rng = np.random.default_rng(E)
+    X = O.bf16(O.pad_inputs(rng.normal(0, 1, (E, 8)).astype(np.float32)))
+    f = rng.uniform(0, 1, E).astype(np.float32)
+    say(f"mlp edges E={E} groups={groups} shift={shift}")
+    bits = np.zeros(16 * E + shift, np.int16)
+    bits[shift:] = (X.view(np.uint32) >> 16).astype(np.uint16).view(np.int16).reshape(-1)
+    gX = gpu.from_numpy(bits).cuda()[shift:].view(E, 16)
+    params = gpu.from_numpy(flat_params(P)).cuda()
+    packed = M.mmas_mlp_pack(params)
+    s = M.mmas_mlp_forward(gX, params, packed).cpu().numpy()
+    ref = O.mlp_forward(X, P, quantize=True)
+    assert np.max(np.abs(s - ref)) <= 2.0 ** -8 * np.max(np.abs(ref))
+    grad = M.mmas_mlp_grad(gX, gpu.from_numpy(f).cuda(), params, packed, groups=groups).cpu().numpy()
+    _, gref = O.mlp_backward(X, f, P, quantize=True)
+    refs = [gref.W1.ravel(), gref.b1, gref.W2.ravel(), gref.b2, gref.w3, np.array([gref.b3])]
+    for a, b in zip(split(grad[:-1]), refs):
+        assert rel_fro(a, b) < 1e-2
