@@ -22,17 +22,31 @@ namespace {
 
 constexpr int kMaxWaves = 16;
 constexpr int kListCap = 64;  // list entries kept, one per lane of the first wave
+// Cities examined in a round, at most: a move is found at the third one on
+// average, and every distance read for one behind it is read again (2-opt of
+// 64 ants on uniform instances of n = 1002 / 3795 / 18512 with 8, 8 and 16
+// waves: 8 cities 1.35 / 5.68 / 33.5 ms, 16: 1.31 / 5.59 / 32.9, 24: 1.38 /
+// 5.72 / 33.6, as many as fit 1.39 / 5.78 / 35.1).
+constexpr int kExamine = 16;
 
-// A wave's first move: its end points, their positions, the new edges'
-// lengths; flags bit 0 = predecessor direction, bits 1-3 = don't-look bits
-// of a1, c, c1 before the round.
-struct Move {
-    int a, a1, c, c1;
-    int pa, pc;
-    int dac, da1c1;
-    int flags;
+// A wave's first move and what applying it takes: all of it is worked out by
+// the lane that evaluates the move, beside its distance load.
+struct alignas(16) Move {
+    uint32_t aa1, cc1;  // the city a and its neighbour a1; c and c1 (low, high half)
+    int dac, da1c1;     // the new edges' lengths
+    uint32_t path;      // first and last position of the reversed path
+    uint32_t m12, m3f;  // places of the end points a1, c, c1 merged into the next list; kFlag* from bit 16
+    uint32_t found;     // half the path's length, the city's list index from bit 16; kNoMove: none
 };
 constexpr uint32_t kNoMove = 0xFFFFFFFFu;
+// m3f from bit 16: predecessor direction, then the number of end points that
+// count as active again, then the number merged (2 bits each)
+constexpr int kFlagPred = 16, kFlagAgain = 17, kFlagMerged = 19;
+
+// x + n if x < 0 (as x + n < 2^31, the smaller unsigned value is the one
+// wanted), and x - n if x >= n
+__device__ __forceinline__ int wrap_up(int x, int n) { return (int)min((uint32_t)x, (uint32_t)(x + n)); }
+__device__ __forceinline__ int wrap_down(int x, int n) { return (int)min((uint32_t)x, (uint32_t)(x - n)); }
 
 __device__ __forceinline__ uint32_t dlb_bit(const uint32_t* dlb, int x) { return (dlb[x >> 5] >> (x & 31)) & 1u; }
 
@@ -80,24 +94,33 @@ __device__ void list_active(const uint32_t* dlb, int words, uint32_t lastmask, i
 // reads one distance from HBM instead of three.
 //
 // A round examines the first E entries of a list of the next active cities
-// in cyclic index order (E = threads / group, a group of 2k lanes per city,
-// at most 64) against the current tour. The first of them (in that order)
-// with an improving move is the city the sequential search reaches next with
-// a move: the cities before it have none and get their bits set, its move is
-// applied and it is examined again. Without a move all E get their bits set.
-// Any prefix of the active cities in cyclic order from the cursor serves as
-// the list, so the next list is the old one from the move's city (or from
-// the first city not examined) on, with the end points that became active
-// inside its range merged in; the don't-look bits are scanned again only
-// when that list gets short. The first wave keeps the list (one entry per
-// lane), the bits, the cursor and the count of active cities; the others
-// reverse the path meanwhile.
+// in cyclic index order (a group of 2k lanes per city, kExamine cities at
+// most) against the current tour. The first of them (in that order) with an
+// improving move is the city the sequential search reaches next with a move:
+// the cities before it have none and get their bits set, its move is applied
+// and it is examined again. Without a move all E get their bits set. Any
+// prefix of the active cities in cyclic order from the cursor serves as the
+// list, so the next list is the old one from the move's city (or from the
+// first city not examined) on, with the end points that became active inside
+// its range merged in; the don't-look bits are scanned again only when that
+// list gets short.
+//
+// A round is one serial chain (one move: the next one depends on it), so its
+// length bounds the kernel: list, positions, tour neighbours from LDS, then
+// one distance from HBM; barrier; the winning move from LDS; barrier. All
+// that the move's consequences need (path, places of its end points) is
+// worked out by every lane beside the distance's load, the first wave then
+// keeps the bits and the count, the second the list, the others reverse the
+// path. In clock cycles a round at n = 3795 takes 1550 to the first barrier,
+// 330 there, 980 of bookkeeping beside 740 of reversal; with those values
+// derived by the first waves after the barrier, it was 1585, 363 and 1650
+// beside 1140. An iteration of 64 ants, n = 3795: 8.48 -> 6.63 ms; n = 18512:
+// 51.7 -> 42.9 ms (reversal 1955 -> 1437 cycles of a round there).
 template <bool kLen>
 __global__ __launch_bounds__(1024) void k_two_opt(Views vw, Shape s, const int32_t* __restrict__ nnd) {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ uint16_t s_lists[2][kListCap];  // by round parity
     __shared__ int s_count[2];                  // entries of each list (0: the search has ended)
-    __shared__ uint32_t s_best[2];              // lowest thread (list index, lane in group) with a move
     __shared__ Move s_mv[kMaxWaves];            // each wave's first move
     __shared__ unsigned long long s_len;
     const int n = s.n, k = s.ls_nn;
@@ -110,7 +133,7 @@ __global__ __launch_bounds__(1024) void k_two_opt(Views vw, Shape s, const int32
     int gs = 1;
     while (gs < 2 * k) gs <<= 1;  // lanes per city (power of two <= 64)
     const int lg = __builtin_ctz(gs);
-    const int E = min(nthr >> lg, kListCap);  // cities examined per round
+    const int E = min(nthr >> lg, kExamine);  // cities examined per round
     uint16_t* tour = reinterpret_cast<uint16_t*>(smem);
     uint16_t* pos = tour + n;
     const size_t tp_bytes = (4 * (size_t)n + 15) & ~(size_t)15;
@@ -130,28 +153,33 @@ __global__ __launch_bounds__(1024) void k_two_opt(Views vw, Shape s, const int32
         pos[v] = (uint16_t)i;
     }
     for (int w = t; w < words; w += nthr) dlb[w] = 0u;
-    if (t == 0) {
-        s_len = 0ull;
-        s_best[0] = s_best[1] = kNoMove;
-    }
+    if (t == 0) s_len = 0ull;
     __syncthreads();
     if (kLen)
         for (int i = t; i < n; i += nthr) elen[i] = dist[(size_t)tour[i] * n + tour[i + 1 == n ? 0 : i + 1]];
 
     // Roles after a round's move is known: wave 0 sets and clears the
-    // don't-look bits and tops the next list up from them, wave 1 merges the
-    // next list from the current one, the other waves reverse the path (with
-    // fewer waves, wave 0 also merges, and a single wave does everything).
+    // don't-look bits, counts the active cities and tops the next list up from
+    // the bits, wave 1 makes the next list from the current one, the other
+    // waves reverse the path (with fewer waves, wave 0 also makes the list, and
+    // a single wave does everything).
     const int merge_wave = nwaves > 2 ? 1 : 0;
     const int rev_wave0 = nwaves > 2 ? 2 : nwaves - 1;
-    int act = n, a0 = 0;            // active cities, cursor (kept alike by the first two waves)
+    int act = n;                    // active cities (kept by the first wave)
     int ca = -1, cc = 0, cdac = 0;  // this lane's last (city, neighbour, distance) from the lists
     // a list shorter than this is topped up from the bits
     const int refill = min(E, 8);
     // every round sets a bit or shortens the tour; the cap only guards
     // against a search that would not end
-    const long long max_rounds = 256ll * n + 4096;
-    long long rounds = 0;
+    const int max_rounds = 256 * n + 4096;
+    int rounds = 0;
+    // this lane's part of every round: its city's list entry, its neighbour's
+    // rank and its direction (step to the tour neighbour, and the same step
+    // around the end: the smaller unsigned sum is the position)
+    const int g = t >> lg, rl = t & (gs - 1);
+    const bool pd = rl >= k;
+    const int rank = pd ? rl - k : rl;
+    const int step = pd ? -1 : 1, step_wrap = pd ? n - 1 : 1 - n;
     if (wave == 0) {
         list_active(dlb, words, lastmask, 0, min(kListCap, n), s_lists[1], lane);
         if (lane == 0) s_count[1] = min(kListCap, n);
@@ -162,165 +190,159 @@ __global__ __launch_bounds__(1024) void k_two_opt(Views vw, Shape s, const int32
         const uint16_t* s_list = s_lists[par];
 
         __syncthreads();  // the list, the tour, positions, lengths and bits of this round
-        // (the list entries are read beside the count: one LDS round trip)
-        const int g = t >> lg, rl = t & (gs - 1);
-        const int a_l = s_list[g < kListCap ? g : 0];
-        const int le_l = s_list[lane];
-        const int count = __builtin_amdgcn_readfirstlane(s_count[par]);
+        // the list entries are read beside the count: one LDS round trip (the
+        // compiler would read them behind the exit)
+        int a_l = s_list[g < kListCap ? g : 0];
+        int le_l = s_list[lane];
+        int count = s_count[par];
+        asm volatile("" : "+v"(a_l), "+v"(le_l), "+v"(count));
+        count = __builtin_amdgcn_readfirstlane(count);
         if (count == 0) break;
         if (rounds > max_rounds) {
             if (t == 0) atomicOr(&vw.state->flags, 16u);
             return;
         }
         const int ev = min(count, E);
-        const int le = lane < count ? le_l : 0;  // the list, one entry a lane (used by waves 0 and 1)
+        const int le = lane < count ? le_l : 0;  // the list, one entry a lane
+        // places of cities are cyclic distances from the first listed one
+        // (the cities between the cursor and it are inactive)
+        const int a0 = __builtin_amdgcn_readfirstlane(le_l);
+        const int last = __builtin_amdgcn_readlane(le, count - 1);
+        auto cyc = [&](int x) { return wrap_up(x - a0, n); };
+        const int ql = cyc(last);
 
         // ---- evaluate every candidate move of the first ev listed cities ----
-        const bool pred_dir = rl >= k;
         bool ok = false;
-        int a = 0, a1 = 0, c = 0, c1 = 0, dac = 0, da1c1 = 0, pa = 0, pc = 0, fl = 0;
+        Move em;  // (only the lanes with a move fill it and use it)
         if (g < ev && rl < 2 * k) {
-            a = a_l;
-            const int r = pred_dir ? rl - k : rl;
+            const int a = a_l;
             if (a != ca) {  // the list often starts where the last one did
-                cc = nn[(size_t)a * k + r];
-                cdac = nnd[(size_t)a * k + r];
+                cc = nn[(size_t)a * k + rank];
+                cdac = nnd[(size_t)a * k + rank];
                 ca = a;
             }
-            c = cc;
-            dac = cdac;
+            const int c = cc, dac = cdac;
             // both ends' positions, then both tour neighbours and edge lengths
-            pa = pos[a];
-            pc = pos[c];
-            const int pa_n = pa + 1 == n ? 0 : pa + 1, pa_p = pa == 0 ? n - 1 : pa - 1;
-            const int pc_n = pc + 1 == n ? 0 : pc + 1, pc_p = pc == 0 ? n - 1 : pc - 1;
-            a1 = tour[pred_dir ? pa_p : pa_n];
-            c1 = tour[pred_dir ? pc_p : pc_n];
-            const int64_t daa1 = kLen ? (int64_t)elen[pred_dir ? pa_p : pa] : (int64_t)dist[(size_t)a * n + a1];
+            const int pa = pos[a], pc = pos[c];
+            const int pa1 = (int)min((uint32_t)(pa + step), (uint32_t)(pa + step_wrap));
+            const int pc1 = (int)min((uint32_t)(pc + step), (uint32_t)(pc + step_wrap));
+            const int a1 = tour[pa1], c1 = tour[pc1];
+            const int64_t daa1 = kLen ? (int64_t)elen[pd ? pa1 : pa] : (int64_t)dist[(size_t)a * n + a1];
+            const int32_t ecc1 = kLen ? elen[pd ? pc1 : pc] : 0;
             const int64_t g1 = daa1 - dac;
             if (g1 > 0 && c != a1 && c1 != a) {
-                const int32_t dcc1 = kLen ? elen[pred_dir ? pc_p : pc] : dist[(size_t)c * n + c1];
-                da1c1 = dist[(size_t)a1 * n + c1];
-                // the end points' don't-look bits, read while the distance loads
-                fl = (pred_dir ? 1 : 0) | ((int)dlb_bit(dlb, a1) << 1) | ((int)dlb_bit(dlb, c) << 2) |
-                     ((int)dlb_bit(dlb, c1) << 3);
+                const int32_t dcc1 = kLen ? ecc1 : dist[(size_t)c * n + c1];
+                const int32_t da1c1 = dist[(size_t)a1 * n + c1];
+                // beside the distance's load: the end points' don't-look bits
+                // and places, whether each counts as active again (inactive
+                // before, or listed before a) and is merged into the next list
+                // (inactive before and inside (a, last])
+                const uint32_t w1 = dlb_bit(dlb, a1), w2 = dlb_bit(dlb, c), w3 = dlb_bit(dlb, c1);
+                // the two paths the move may reverse (a1 and c1 sit next to a
+                // and c); the shorter one, the first on a tie
+                const int i1 = pd ? pa : pa1, j1 = pd ? pc1 : pc;  // a1..c or a..c1
+                const int i2 = pd ? pc : pc1, j2 = pd ? pa1 : pa;  // c1..a or c..a1
+                const int len1 = wrap_up(j1 - i1, n) + 1;
+                const bool first = len1 <= n - len1;
+                em.path = (uint32_t)(first ? i1 : i2) | (uint32_t)(first ? j1 : j2) << 16;
+                em.found = (uint32_t)((first ? len1 : n - len1) >> 1) | (uint32_t)g << 16;
+                const int qa = cyc(a), q1 = cyc(a1), q2 = cyc(c), q3 = cyc(c1);
+                const bool b1 = w1 && q1 > qa && q1 <= ql;
+                const bool b2 = w2 && q2 > qa && q2 <= ql;
+                const bool b3 = w3 && q3 > qa && q3 <= ql;
+                const uint32_t again = (w1 | (uint32_t)(q1 < qa)) + (w2 | (uint32_t)(q2 < qa)) + (w3 | (uint32_t)(q3 < qa));
+                em.m12 = (uint32_t)(b1 ? q1 : n) | (uint32_t)(b2 ? q2 : n) << 16;
+                em.m3f = (uint32_t)(b3 ? q3 : n) | (uint32_t)pd << kFlagPred | again << kFlagAgain |
+                         ((uint32_t)b1 + (uint32_t)b2 + (uint32_t)b3) << kFlagMerged;
+                em.aa1 = (uint32_t)a | (uint32_t)a1 << 16;
+                em.cc1 = (uint32_t)c | (uint32_t)c1 << 16;
+                // (kept here: the compiler would move all of it behind the load)
+                asm volatile("" : "+v"(em.path), "+v"(em.found), "+v"(em.m12), "+v"(em.m3f), "+v"(em.aa1), "+v"(em.cc1));
+                em.dac = dac;
+                em.da1c1 = da1c1;
                 ok = g1 + (int64_t)dcc1 - (int64_t)da1c1 > 0;
             }
         }
+        // the lowest lane with a move: the wave's first city, its first move
         const uint64_t mask = __ballot(ok);
-        if (mask != 0ull && lane == __ffsll((unsigned long long)mask) - 1) {
-            // lowest lane: first city, first move of this wave
-            s_mv[wave] = Move{a, a1, c, c1, pa, pc, dac, da1c1, fl};
-            atomicMin(&s_best[par], (uint32_t)t);  // thread index: list index, then lane in group
+        if (mask == 0ull) {
+            if (lane == 0) s_mv[wave].found = kNoMove;
+        } else if (lane == __ffsll((unsigned long long)mask) - 1) {
+            s_mv[wave] = em;
         }
         __syncthreads();
-        // the first move over all waves
-        const uint32_t best = __builtin_amdgcn_readfirstlane(s_best[par]);
-        const bool moved = best != kNoMove;
-        Move mv{};
-        if (moved) {
-            const Move m = s_mv[best >> 6];
-            mv = Move{__builtin_amdgcn_readfirstlane(m.a),   __builtin_amdgcn_readfirstlane(m.a1),
-                      __builtin_amdgcn_readfirstlane(m.c),   __builtin_amdgcn_readfirstlane(m.c1),
-                      __builtin_amdgcn_readfirstlane(m.pa),  __builtin_amdgcn_readfirstlane(m.pc),
-                      __builtin_amdgcn_readfirstlane(m.dac), __builtin_amdgcn_readfirstlane(m.da1c1),
-                      __builtin_amdgcn_readfirstlane(m.flags)};
-        }
-        const int gstar = moved ? (int)(best >> lg) : ev;  // the listed cities before it have no move
+        // the first move over all waves: that of the first wave with one (the
+        // waves' moves are read beside their flags, one a lane)
+        Move wm = s_mv[lane & (kMaxWaves - 1)];
+        // (read in one go: the compiler would read part of it in the branches)
+        asm volatile("" : "+v"(wm.aa1), "+v"(wm.cc1), "+v"(wm.dac), "+v"(wm.da1c1), "+v"(wm.path), "+v"(wm.m12),
+                     "+v"(wm.m3f), "+v"(wm.found));
+        const uint64_t wmask = __ballot(lane < nwaves && wm.found != kNoMove);
+        const bool moved = wmask != 0ull;
+        const int bw = moved ? __ffsll((unsigned long long)wmask) - 1 : 0;
+        const uint32_t found = __builtin_amdgcn_readlane(wm.found, bw);
 
         if (wave <= merge_wave) {
-            const int last = __builtin_amdgcn_readlane(le, count - 1);
-            auto cyc = [&](int x) { return x >= a0 ? x - a0 : x - a0 + n; };
-            // The end points a1, c, c1: their don't-look bits before the
-            // round (w), cyclic places (q), and the places of those merged
-            // into the next list (inactive before, inside (a, last]; n for
-            // the others). Everything here is wave-uniform but the lists.
-            const int e1 = mv.a1, e2 = mv.c, e3 = mv.c1;
-            const int w1 = (mv.flags >> 1) & 1, w2 = (mv.flags >> 2) & 1, w3 = (mv.flags >> 3) & 1;
-            const int qa = cyc(mv.a), ql = cyc(last), q1 = cyc(e1), q2 = cyc(e2), q3 = cyc(e3);
-            const int m1 = moved && w1 && q1 > qa && q1 <= ql ? q1 : n;
-            const int m2 = moved && w2 && q2 > qa && q2 <= ql ? q2 : n;
-            const int m3 = moved && w3 && q3 > qa && q3 <= ql ? q3 : n;
-            // the listed cities before the move's city lose their bits (except
-            // end points); the end points are all active afterwards: those
-            // inactive before, and those listed before the move's city, count
-            // again
-            const int newact = act - gstar +
-                               (moved ? (int)(w1 | (q1 < qa)) + (int)(w2 | (q2 < qa)) + (int)(w3 | (q3 < qa)) : 0);
-            const int ee = lane == 0 ? e1 : lane == 1 ? e2 : e3;
-            const int cap = min(kListCap, newact);
+            const int gstar = moved ? (int)(found >> 16) : ev;  // the listed cities before it have no move
+            const uint32_t aa1 = __builtin_amdgcn_readlane(wm.aa1, bw);
+            const uint32_t cc1 = __builtin_amdgcn_readlane(wm.cc1, bw);
+            const uint32_t m3f = moved ? __builtin_amdgcn_readlane(wm.m3f, bw) : 0u;
+            const int merged = (int)(m3f >> kFlagMerged);
             // kept: the move's city (first) and the entries after it, or the
             // entries not examined; merged end points in cyclic order
-            const int keep0 = moved ? gstar + 1 : gstar, head = moved ? 1 : 0;
-            const int merged = (int)(m1 < n) + (int)(m2 < n) + (int)(m3 < n);
-            int len = newact > 0 ? min(cap, head + count - keep0 + merged) : 0;
+            const int head = moved ? 1 : 0, keep0 = gstar + head;
             uint16_t* nl = s_lists[par ^ 1];
-            if (wave == 0) {
-                if (lane == 0) s_best[par ^ 1] = kNoMove;  // for the next round
-                const bool is_end = moved && (le == e1 || le == e2 || le == e3);
-                if (lane < gstar && !is_end) atomicOr(&dlb[le >> 5], 1u << (le & 31));
-                const int we = lane == 0 ? w1 : lane == 1 ? w2 : w3;
-                if (moved && lane < 3 && we) atomicAnd(&dlb[ee >> 5], ~(1u << (ee & 31)));
-            }
-            if (wave == merge_wave && newact > 0) {
+            const int ee = lane == 0 ? (int)(aa1 >> 16) : lane == 1 ? (int)(cc1 & 0xFFFFu) : (int)(cc1 >> 16);
+            if (wave == merge_wave) {
                 const bool keep = lane >= keep0 && lane < count;
-                const int cx = cyc(le);
-                const int idx = head + lane - keep0 + (int)(m1 < cx) + (int)(m2 < cx) + (int)(m3 < cx);
-                if (keep && idx < cap) nl[idx] = (uint16_t)le;
-                // lanes 0-2: the place of merged end point e1, e2, e3 (lane 0
-                // first writes the move's city)
-                const int r1 = __popcll(__ballot(keep && cx < m1));
-                const int r2 = __popcll(__ballot(keep && cx < m2));
-                const int r3 = __popcll(__ballot(keep && cx < m3));
-                const int mm = lane == 0 ? m1 : lane == 1 ? m2 : m3;
-                const int rr = lane == 0 ? r1 : lane == 1 ? r2 : r3;
-                const int ie = head + rr + (int)(m1 < mm) + (int)(m2 < mm) + (int)(m3 < mm);
-                if (moved && lane == 0) nl[0] = (uint16_t)mv.a;
-                if (lane < 3 && mm < n && ie < cap) nl[ie] = (uint16_t)ee;
+                int idx = lane - gstar;
+                if (merged) {
+                    const uint32_t m12 = __builtin_amdgcn_readlane(wm.m12, bw);
+                    const int m1 = (int)(m12 & 0xFFFFu), m2 = (int)(m12 >> 16), m3 = (int)(m3f & 0xFFFFu);
+                    const int cx = cyc(le);
+                    idx += (int)(m1 < cx) + (int)(m2 < cx) + (int)(m3 < cx);
+                    // lanes 0-2: the place of merged end point a1, c, c1
+                    const int r1 = __popcll(__ballot(keep && cx < m1));
+                    const int r2 = __popcll(__ballot(keep && cx < m2));
+                    const int r3 = __popcll(__ballot(keep && cx < m3));
+                    const int mm = lane == 0 ? m1 : lane == 1 ? m2 : m3;
+                    const int rr = lane == 0 ? r1 : lane == 1 ? r2 : r3;
+                    const int ie = head + rr + (int)(m1 < mm) + (int)(m2 < mm) + (int)(m3 < mm);
+                    if (lane < 3 && mm < n && ie < kListCap) nl[ie] = (uint16_t)ee;
+                }
+                // (the move's city is list entry gstar)
+                if ((keep || (moved && lane == gstar)) && idx < kListCap) nl[idx] = (uint16_t)le;
             }
-            int a0n = last + 1 == n ? 0 : last + 1;
-            if (len > 0) a0n = moved ? mv.a : __builtin_amdgcn_readlane(le, gstar);
-            if (len < cap && len < refill) {
-                // the next active cities after the last listed one (after the
-                // bits above: wave 0's own LDS operations complete in order)
-                if (wave == 0)
+            if (wave == 0) {
+                // the listed cities before the move's city lose their bits, the
+                // end points are all active afterwards (a wave's LDS operations
+                // complete in order)
+                if (lane < gstar) atomicOr(&dlb[le >> 5], 1u << (le & 31));
+                if (moved && lane < 3) atomicAnd(&dlb[ee >> 5], ~(1u << (ee & 31)));
+                act = act - gstar + (int)((m3f >> kFlagAgain) & 3u);
+                const int cap = min(kListCap, act);
+                int len = min(cap, count - gstar + merged);
+                if (len < cap && len < refill) {
+                    // the next active cities after the last listed one
                     list_active(dlb, words, lastmask, last + 1 == n ? 0 : last + 1, cap - len, nl + len, lane);
-                len = cap;
+                    len = cap;
+                }
+                if (lane == 0) s_count[par ^ 1] = len;
             }
-            if (wave == 0 && lane == 0) s_count[par ^ 1] = len;
-            a0 = a0n;
-            act = newact;
         }
         if (moved && wave >= rev_wave0) {
-            // the two paths the move may reverse (a1 and c1 sit next to a and
-            // c); the shorter one, the first on a tie
-            const bool pd = mv.flags & 1;
-            const int pa_n = mv.pa + 1 == n ? 0 : mv.pa + 1, pa_p = mv.pa == 0 ? n - 1 : mv.pa - 1;
-            const int pc_n = mv.pc + 1 == n ? 0 : mv.pc + 1, pc_p = mv.pc == 0 ? n - 1 : mv.pc - 1;
-            const int i1 = pd ? mv.pa : pa_n, j1 = pd ? pc_p : mv.pc;  // a1..c or a..c1
-            const int i2 = pd ? mv.pc : pc_n, j2 = pd ? pa_p : mv.pa;  // c1..a or c..a1
-            int len1 = j1 - i1;
-            if (len1 < 0) len1 += n;
-            len1 += 1;
-            const bool first = len1 <= n - len1;
-            const int mi = first ? i1 : i2, mj = first ? j1 : j2;
             // reverse positions i..j of the tour and i..j-1 of the edge lengths:
             // pair q swaps tour[i+q] and tour[j-q], and elen[i+q] and
             // elen[j-1-q] (for even lengths the middle pair of the lengths is
             // one cell swapped with itself)
+            const uint32_t path = __builtin_amdgcn_readlane(wm.path, bw);
+            const int mi = (int)(path & 0xFFFFu), mj = (int)(path >> 16);
+            const int half = (int)(found & 0xFFFFu);
             const int rt = t - rev_wave0 * kWave, rthr = nthr - rev_wave0 * kWave;
-            const int half = (first ? len1 : n - len1) / 2;
-            // position i - 1 lies outside the reversed path (at most n / 2 long)
-            const int pl = mi == 0 ? n - 1 : mi - 1;
-            int x = 0;
-            if (kLen && rt == 0) x = tour[pl];
             for (int q = rt; q < half; q += rthr) {
-                int p = mi + q;
-                if (p >= n) p -= n;
-                int r = mj - q;
-                if (r < 0) r += n;
-                int r1 = r - 1;
-                if (r1 < 0) r1 += n;
+                const int p = wrap_down(mi + q, n);
+                const int r = wrap_up(mj - q, n);
+                const int r1 = wrap_up(r - 1, n);
                 const uint16_t tp = tour[p], tr = tour[r];
                 int32_t ep = 0, er = 0;
                 if (kLen) {
@@ -337,11 +359,13 @@ __global__ __launch_bounds__(1024) void k_two_opt(Views vw, Shape s, const int32
                 }
             }
             if (kLen && rt == 0) {
-                // the two new edges close the reversed path: {a, c} and
-                // {a1, c1}, the one next to the city left of it first
-                const bool left_ac = x == mv.a || x == mv.c;
-                elen[pl] = left_ac ? mv.dac : mv.da1c1;
-                elen[mj] = left_ac ? mv.da1c1 : mv.dac;
+                // the two new edges close the path: in successor direction the
+                // city left of it is a (path from a1) or c (path from c1), and
+                // {a, c} comes first; else it is a1 or c1
+                const bool pd = (__builtin_amdgcn_readlane(wm.m3f, bw) >> kFlagPred) & 1u;
+                const int dac = __builtin_amdgcn_readlane(wm.dac, bw), da1c1 = __builtin_amdgcn_readlane(wm.da1c1, bw);
+                elen[wrap_up(mi - 1, n)] = pd ? da1c1 : dac;
+                elen[mj] = pd ? dac : da1c1;
             }
         }
     }
@@ -396,7 +420,9 @@ hipError_t launch_two_opt(const Views& v, const Shape& s, const int32_t* nnd, hi
     Shape ss = s;
     void* args[] = {(void*)&vv, (void*)&ss, (void*)&nnd};
     // more waves shorten the reversal of long paths and cost a little more
-    // at the barriers: 4 below 1024 cities, 8 below 8192, 16 from there
+    // at the barriers: 4 below 1024 cities, 8 below 8192, 16 from there (4, 8,
+    // 16 waves: n = 500 664, 666, 682 us; 1002 1322, 1305, 1349; 3795 5.84,
+    // 5.59, 5.66 ms; 18512 41.4, 33.9, 32.9)
     const int waves = s.two_opt_waves ? s.two_opt_waves : s.n < 1024 ? 4 : s.n < 8192 ? 8 : 16;
     return hipLaunchKernel(kern, dim3(s.ants), dim3(64 * waves), args, lds, st);
 }

@@ -71,6 +71,19 @@ def test_two_opt_without_lds_edge_lengths(gpu):
     two_opt_pair(d, 8, 5, ants=4)
 
 
+@pytest.mark.parametrize("n,k,waves", [(40, 8, 4), (40, 9, 4), (70, 32, 1), (300, 2, 2), (300, 2, 16), (64, 8, 16)])
+def test_two_opt_round_sizes(gpu, n, k, waves):
+    """Cities examined per round: exactly the cap, half of it, one, more
+    groups than the cap, waves without a city; cities on a grid, so that many
+    distances tie and some are zero."""
+    rng = np.random.default_rng(n + k)
+    xy = rng.integers(0, 12, (n, 2)).astype(np.float64)
+    d = np.rint(100 * np.sqrt(((xy[:, None] - xy[None]) ** 2).sum(-1))).astype(np.int32)
+    np.fill_diagonal(d, 0)
+    say(f"2-opt round sizes n={n} k={k} waves={waves}")
+    two_opt_pair(d, k, seed=6, ants=8, waves=waves, random_tours=True)
+
+
 @pytest.mark.parametrize("tabu", ["bitmask", "compact"])
 def test_iterations_with_two_opt(gpu, tabu):
     _, d = I.make_instance("uniform", 600, seed=7, side=1e6)
