@@ -75,10 +75,10 @@ def test_two_opt_without_lds_edge_lengths(gpu):
 def test_two_opt_round_sizes(gpu, n, k, waves):
     """Cities examined per round: exactly the cap, half of it, one, more
     groups than the cap, waves without a city; cities on a grid, so that many
-    distances tie and some are zero."""
+    distances tie (1 between cities at one place, the least a matrix takes)."""
     rng = np.random.default_rng(n + k)
     xy = rng.integers(0, 12, (n, 2)).astype(np.float64)
-    d = np.rint(100 * np.sqrt(((xy[:, None] - xy[None]) ** 2).sum(-1))).astype(np.int32)
+    d = np.maximum(np.rint(100 * np.sqrt(((xy[:, None] - xy[None]) ** 2).sum(-1))), 1).astype(np.int32)
     np.fill_diagonal(d, 0)
     say(f"2-opt round sizes n={n} k={k} waves={waves}")
     two_opt_pair(d, k, seed=6, ants=8, waves=waves, random_tours=True)
