@@ -215,7 +215,7 @@ mmas_status mmas_two_opt(mmas_ctx* ctx);
 /* Launch shape of the 2-opt kernel; results never depend on it.
  * `waves_per_ant`: wave64s of the workgroup that runs one ant's search, 1, 2,
  * 4, 8 or 16 (0 = by the instance: 4 below 1024 cities, 8 below 8192, 16
- * from there); each round examines min(64, threads / (2*ls_nn rounded up to
+ * from there); each round examines min(16, threads / (2*ls_nn rounded up to
  * a power of two)) cities. EINVAL for other values. */
 mmas_status mmas_set_two_opt_launch(mmas_ctx* ctx, int32_t waves_per_ant);
 
