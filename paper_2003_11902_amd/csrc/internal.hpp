@@ -77,7 +77,8 @@ mmas_status hip_fail(hipError_t e, const char* where);
 // ---- set-up (prep.hip) ----
 hipError_t launch_validate(const Views& v, const Shape& s, hipStream_t st);
 hipError_t launch_heuristic(const Views& v, const Shape& s, hipStream_t st);
-hipError_t launch_nearest(const int32_t* dist, int n, int k, uint16_t* out, hipStream_t st);
+// (`clear`, if given: n counters set to 0 beside it)
+hipError_t launch_nearest(const int32_t* dist, int n, int k, uint16_t* out, hipStream_t st, int* clear = nullptr);
 hipError_t launch_nn_tour(const Views& v, const Shape& s, hipStream_t st);
 hipError_t launch_init_trails(const Views& v, const Shape& s, hipStream_t st);
 
@@ -116,7 +117,8 @@ int compute_units();
 // ---- learned heuristic (learned.hip) ----
 int mlp_param_count();
 int mlp_packed_count();
-hipError_t launch_features(const int32_t* dist, const float* xy, const uint16_t* knn, int n, float* dbar, int* indeg,
+// (the nearest cities, then the features)
+hipError_t launch_features(const int32_t* dist, const float* xy, uint16_t* knn, int n, float* dbar, int* indeg,
                            float* feat, uint16_t* X, hipStream_t st);
 hipError_t launch_pack(const float* p, uint16_t* pk, hipStream_t st);
 hipError_t launch_mlp_forward(const uint16_t* X, const float* p, const uint16_t* pk, int64_t E, float* s,

@@ -98,13 +98,6 @@ __device__ __forceinline__ float gelu_d_of(float z, const Normal& n) {
 
 // ---- features ----------------------------------------------------------------
 
-// in-degree counters cleared by a kernel rather than a memset node, so that
-// the feature pass can be captured into a graph and replayed
-__global__ __launch_bounds__(256) void k_zero_i32(int* __restrict__ a, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) a[i] = 0;
-}
-
 // one thread per edge e = 16 i + r: the mean distance of i's neighbours, summed
 // left to right by every lane of the row of 16 that holds them, and the
 // in-degrees
@@ -659,10 +652,11 @@ int grid_of(size_t total) {
 int mlp_param_count() { return kParams; }
 int mlp_packed_count() { return kPacked; }
 
-hipError_t launch_features(const int32_t* dist, const float* xy, const uint16_t* knn, int n, float* dbar, int* indeg,
+hipError_t launch_features(const int32_t* dist, const float* xy, uint16_t* knn, int n, float* dbar, int* indeg,
                            float* feat, uint16_t* X, hipStream_t st) {
-    k_zero_i32<<<(n + 255) / 256, 256, 0, st>>>(indeg, n);
-    hipError_t e = hipGetLastError();
+    // the in-degrees are cleared by the kernel that finds the neighbours (a
+    // launch of its own took 4.5 us, a memset node would not replay safely)
+    hipError_t e = launch_nearest(dist, n, kK, knn, st, indeg);
     if (e != hipSuccess) return e;
     k_feat_city<<<(n * kK + 255) / 256, 256, 0, st>>>(dist, knn, n, dbar, indeg);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -771,8 +765,6 @@ mmas_status mmas_mlp_features(const int32_t* dist_dev, const float* xy_dev, int3
                               uint16_t* knn_dev, float* feat_dev, uint16_t* x_dev, void* hip_stream) {
     if (!dist_dev || !xy_dev || !scratch_dev || !knn_dev || !x_dev || n < 17 || n > 65535) return MMAS_EINVAL;
     hipStream_t st = as_stream(hip_stream);
-    hipError_t e = mmas::launch_nearest(dist_dev, n, 16, knn_dev, st);
-    if (e != hipSuccess) return st_of(e);
     float* dbar = reinterpret_cast<float*>(scratch_dev);
     int* indeg = reinterpret_cast<int*>(dbar + n);
     return st_of(mmas::launch_features(dist_dev, xy_dev, knn_dev, n, dbar, indeg, feat_dev, x_dev, st));
@@ -786,8 +778,6 @@ mmas_status mmas_mlp_features_noalloc(const int32_t* dist_dev, const float* xy_d
     const mmas_status got = scratch_of_current_device(&ws);
     if (got != MMAS_OK) return got;
     hipStream_t st = as_stream(hip_stream);
-    hipError_t e = mmas::launch_nearest(dist_dev, n, 16, knn_dev, st);
-    if (e != hipSuccess) return st_of(e);
     // the in-degree counters are cleared by a kernel inside launch_features
     float* dbar = reinterpret_cast<float*>(ws);
     int* indeg = reinterpret_cast<int*>(dbar + n);

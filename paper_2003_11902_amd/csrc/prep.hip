@@ -65,39 +65,54 @@ constexpr int kNearCap = 256;
 // smallest group minimum, or a little more, bounds the k-th smallest entry, so
 // a second pass gathers the few entries up to that bound (37 of 3795 on
 // average for k = 32) and their ranks among each other are their places.
-// Reads the row twice where taking the next smallest entry k times read it k
-// times: n = 3795, k = 16: 184 -> 34 us, n = 1002, k = 32: 43 -> 8 us.
+// A wave's time is its reads' latency (the whole grid is resident at once), so
+// a row of up to 64 kRegs cities is read once, all loads in flight, and kept
+// in registers; a longer one (kRegs = 0) twice, eight loads in flight (sixteen
+// change nothing). k = 16, n = 3795 / 18512: 17.7 / 460 us; 35.0 / 661 with
+// four loads and then one in flight, 184 / 4470 by taking the next smallest
+// entry k times. (n = 3795: 57.6 MB, 12 us at a copy's rate.)
 // Rows with more than kNearCap entries up to the bound (long runs of equal
 // distances) take the smallest remaining entry k times.
+// `clear` (or null): cleared at i, for the kernel that counts in-degrees next.
+template <int kRegs>
 __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, int n, int k,
-                                                 uint16_t* __restrict__ out) {
+                                                 uint16_t* __restrict__ out, int* __restrict__ clear) {
+    constexpr int kBatch = kRegs ? kRegs : 8;
     __shared__ uint64_t s_key[4][kNearCap];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int i = (int)blockIdx.x * 4 + wave;
     if (i >= n) return;
+    if (clear && lane == 0) clear[i] = 0;
     const int32_t* row = d + (size_t)i * n;
     uint16_t* o = out + (size_t)i * k;
-    uint32_t m0 = ~0u, m1 = ~0u;
-    int j = lane;
-    for (; j + 3 * kWave < n; j += 4 * kWave) {
-        uint32_t x[4];
+    // the entries of kBatch 64-city pieces from city j0 on (all ones past the
+    // row's end and for i itself); the last, partial piece is read once, and
+    // pieces past the end read the last full one instead (the first cities
+    // again where there is none): scalar bases and one lane offset
+    const int full = n >> 6, lc = min(lane, n - 1), self = i >> 6;
+    const bool own = lane == (i & 63);
+    const uint32_t tail = full * kWave + lane < n ? (uint32_t)row[full * kWave + lane] : ~0u;
+    uint32_t x[kBatch];
+    auto fetch = [&](int j0) {
+        const int p0 = j0 >> 6;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = (uint32_t)row[j + u * kWave];
+        for (int u = 0; u < kBatch; ++u) x[u] = (uint32_t)(row + max(min(p0 + u, full - 1), 0) * kWave)[lc];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t v = j + u * kWave == i ? ~0u : x[u];
-            if (u & 1)
-                m1 = min(m1, v);
-            else
-                m0 = min(m0, v);
+        for (int u = 0; u < kBatch; ++u) {
+            uint32_t v = p0 + u < full ? x[u] : p0 + u == full ? tail : ~0u;
+            x[u] = p0 + u == self && own ? ~0u : v;
         }
-    }
-    for (int u = 0; j < n; j += kWave, ++u) {
-        const uint32_t v = j == i ? ~0u : (uint32_t)row[j];
-        if (u & 1)
-            m1 = min(m1, v);
-        else
-            m0 = min(m0, v);
+    };
+    uint32_t m0 = ~0u, m1 = ~0u;
+    for (int j0 = 0; j0 < n; j0 += kBatch * kWave) {
+        fetch(j0);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (u & 1)
+                m1 = min(m1, x[u]);
+            else
+                m0 = min(m0, x[u]);
+        }
     }
     // the least bound under which at least k group minima lie, or one with up
     // to eight more (bisection; every group but that of i alone has a minimum,
@@ -118,14 +133,17 @@ __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, 
     }
     // the entries up to the bound
     int m = 0;
-    for (int j0 = 0; j0 < n; j0 += kWave) {
-        const int q = j0 + lane;
-        const uint32_t v = q < n && q != i ? (uint32_t)row[q] : ~0u;
-        const uint64_t in = __ballot(v <= hi);
-        if (in) {
-            const int at = m + __popcll(in & ((1ull << lane) - 1ull));
-            if (v <= hi && at < kNearCap) s_key[wave][at] = ((uint64_t)v << 32) | (uint32_t)q;
-            m += __popcll(in);
+    for (int j0 = 0; j0 < n; j0 += kBatch * kWave) {
+        if (!kRegs) fetch(j0);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint64_t in = __ballot(x[u] <= hi);
+            if (in) {
+                const int at = m + __popcll(in & ((1ull << lane) - 1ull));
+                if (x[u] <= hi && at < kNearCap)
+                    s_key[wave][at] = ((uint64_t)x[u] << 32) | (uint32_t)(j0 + u * kWave + lane);
+                m += __popcll(in);
+            }
         }
     }
     if (__builtin_expect(m <= kNearCap, 1)) {
@@ -133,6 +151,7 @@ __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, 
         for (int e = lane; e < ((m + kWave - 1) & ~(kWave - 1)); e += kWave) {
             const uint64_t key = e < m ? s_key[wave][e] : ~0ull;
             int rank = 0;
+#pragma unroll 8
             for (int q = 0; q < m; ++q) rank += s_key[wave][q] < key ? 1 : 0;
             if (e < m && rank < k) o[rank] = (uint16_t)key;
         }
@@ -351,9 +370,17 @@ hipError_t launch_heuristic(const Views& v, const Shape& s, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_nearest(const int32_t* dist, int n, int k, uint16_t* out, hipStream_t st) {
+hipError_t launch_nearest(const int32_t* dist, int n, int k, uint16_t* out, hipStream_t st, int* clear) {
     if (k <= 0) return hipSuccess;
-    k_nearest<<<(n + 3) / 4, 256, 0, st>>>(dist, n, k, out);
+    const int grid = (n + 3) / 4;
+    if (n <= 16 * kWave)
+        k_nearest<16><<<grid, 256, 0, st>>>(dist, n, k, out, clear);
+    else if (n <= 32 * kWave)
+        k_nearest<32><<<grid, 256, 0, st>>>(dist, n, k, out, clear);
+    else if (n <= 64 * kWave)
+        k_nearest<64><<<grid, 256, 0, st>>>(dist, n, k, out, clear);
+    else
+        k_nearest<0><<<grid, 256, 0, st>>>(dist, n, k, out, clear);
     return hipGetLastError();
 }
 

@@ -40,6 +40,15 @@ def test_lists_and_tour(gpu, n, cl, ls_nn):
     check(d, cl, min(ls_nn, n - 1))
 
 
+@pytest.mark.parametrize("n", [1025, 1088, 2048, 2049, 4032, 4096, 4097])
+def test_lists_at_register_limits(gpu, n):
+    """Rows that fill a wave's registers, one city less than a piece of 64 or
+    one more than fits."""
+    _, d = I.make_instance("uniform", n, seed=n, side=1e6)
+    say(f"register limits n={n}")
+    check(d, 16, 8, pher="candidates")
+
+
 @pytest.mark.parametrize("n", [300, 1500])
 def test_equal_distances(gpu, n):
     """Runs of equal distances: more entries up to the k-th smallest than are
