@@ -38,11 +38,14 @@ typedef int32_t i32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr size_t kDrawBytes = 4 * kWave * sizeof(float);  // candidate draws of the next steps
 constexpr size_t kScratchBytes = 16;                       // per-ant counter of the fallback list
 
-// x with lane kLane's value replaced by the wave-uniform v.
+// x with lane kLane's value replaced by the wave-uniform v. (The compiler's own
+// operation, by its name as there is no builtin for it: a vector instruction
+// may read a scalar register two wait states after a lane read wrote it at the
+// earliest, and the compiler cannot see to that inside inline assembly.)
+extern "C" __device__ __attribute__((const)) int lane_write(int v, int lane, int x) __asm__("llvm.amdgcn.writelane.i32");
 template <int kLane>
 __device__ __forceinline__ int write_lane(int v, int x) {
-    asm("v_writelane_b32 %0, %1, %2" : "+v"(x) : "s"(__builtin_amdgcn_readfirstlane(v)), "n"(kLane));
-    return x;
+    return lane_write(__builtin_amdgcn_readfirstlane(v), kLane, x);
 }
 
 // ---- tabu variants ---------------------------------------------------------
