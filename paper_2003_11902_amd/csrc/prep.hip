@@ -224,12 +224,13 @@ __device__ __forceinline__ void nn_length(const int32_t* __restrict__ d, int n, 
 __global__ __launch_bounds__(1024) void k_nn_tour(const int32_t* __restrict__ d, const uint16_t* __restrict__ cand,
                                                   int cl, int n, int p, uint16_t* __restrict__ tour,
                                                   mmas_device_state* __restrict__ st) {
-    extern __shared__ uint32_t vis[];  // ceil(n/32) words, then the table
+    extern __shared__ __align__(16) uint8_t smem[];  // ceil(n/32) words, then the table
     __shared__ uint64_t part[16];
     __shared__ int s_cur;  // the city whose row is to be scanned, -1: the tour is done, -2: it failed
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    uint16_t* tab = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(vis) + nn_tour_bits(n));
+    uint32_t* vis = reinterpret_cast<uint32_t*>(smem);
+    uint16_t* tab = reinterpret_cast<uint16_t*>(smem + nn_tour_bits(n));
     const int words = (n + 31) >> 5;
     for (int w = threadIdx.x; w < words; w += blockDim.x) vis[w] = w == 0 ? 1u : 0u;
     // (lists and table start 16-byte aligned: eight entries at once where whole

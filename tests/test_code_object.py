@@ -80,3 +80,27 @@ def test_lane_reads_settle_before_vector_reads(code_objects):
     for path in code_objects:
         found += close_scalar_reads(_run(os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", path))
     assert not found, f"{len(found)} reads too early, the first: {found[:3]}"
+
+
+def kernel_lds(notes):
+    """{kernel: bytes of static LDS, where its dynamic LDS starts}."""
+    out = {}
+    for block in notes.split(".agpr_count:")[1:]:
+        size = re.search(r"\.group_segment_fixed_size:\s*(\d+)", block)
+        name = re.search(r"\.name:\s*(_Z\S+)", block)
+        out[name.group(1)] = int(size.group(1))
+    return out
+
+
+def test_dynamic_lds_starts_at_16_bytes(code_objects):
+    """The nearest-neighbour tour stores 16 bytes at a time into its dynamic LDS,
+    and so do the constructions and the 2-opt: it has to start at a multiple
+    of 16, behind whatever static LDS the kernel has."""
+    lds = {}
+    for path in code_objects:
+        lds.update(kernel_lds(_run(os.path.join(LLVM, "llvm-readelf"), "--notes", path)))
+    wide = {k: v for k, v in lds.items()
+            if any(s in k for s in ("k_nn_tour", "11k_construct", "k_batch_construct", "k_two_opt", "k_mlp_train"))
+            and "k_construct_team" not in k}  # (the team has no dynamic LDS)
+    assert any("k_nn_tour" in k for k in wide) and len(wide) > 20
+    assert not {k: v for k, v in wide.items() if v % 16}
