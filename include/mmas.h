@@ -315,8 +315,9 @@ mmas_status mmas_batch_set_launch(mmas_batch* b, int32_t ants_per_block, int32_t
                                   int32_t lanes_per_ant);
 
 /* Tabu of the batch's constructions, MMAS_TABU_BITMASK, _COMPACT or _LIST
- * (tours never depend on it); keeps the launch shape, EUNSUPPORTED if that
- * shape's LDS no longer fits. Drops a captured graph. */
+ * (tours never depend on it); keeps a launch shape that was asked for or tuned
+ * (EUNSUPPORTED if its LDS no longer fits), and takes the default one for the
+ * new tabu otherwise. Drops a captured graph. */
 mmas_status mmas_batch_set_tabu(mmas_batch* b, int32_t tabu);
 
 /* Autotuner: times one construction launch for each ants_per_block in

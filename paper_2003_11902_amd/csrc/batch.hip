@@ -39,6 +39,7 @@ struct mmas_batch {
     int table_request;  // table_bytes as last asked for (-1: all that fits)
     int ants_per_block;
     int lanes_per_ant;
+    bool asked;         // the launch shape was asked for or tuned (else default_launch's)
     bool pair_ok;       // every instance has 1 <= cl <= 32
     int table_bytes;
     int ntiles;
@@ -137,6 +138,25 @@ void apply_tabu(mmas_batch* b, int tabu) {
     b->tabu = tabu;
     b->per_ant = b->per_ant_tabu[tabu];
     for (auto& it : b->items) it.s.tabu = tabu;
+}
+
+// The launch shape of a batch without one asked for, by the current tabu: two
+// ants per wave, eight per workgroup (four where eight do not fit) and no LDS
+// table (rows from L2; a table leaves fewer waves per SIMD to hide the steps'
+// chains), the fastest or within 3 % of it from 512 to 20 thousand ants: 160
+// colonies of 64 ants, n 200-1000: 1.21 ms a step against 3.62 with one ant
+// per wave, four per workgroup and a full table, and 1.41 without the table;
+// 20 instances with ants = n: 1.59, 9.49 and 2.51 ms. Lists longer than 32
+// take one ant per wave, with the table only while every workgroup has a CU
+// of its own.
+void default_launch(mmas_batch* b) {
+    int64_t ants = 0;
+    for (const auto& it : b->items) ants += it.s.ants;
+    const int lds = mmas::max_lds_per_block() - kStaticLds;
+    b->lanes_per_ant = b->pair_ok ? 32 : 64;
+    b->ants_per_block = b->pair_ok && 8 * b->per_ant <= lds ? 8 : 4;
+    b->table_request = b->pair_ok || ants > 4 * (int64_t)mmas::compute_units() ? 0 : -1;
+    b->table_bytes = b->table_request < 0 ? std::max(0, (lds - b->ants_per_block * b->per_ant) & ~15) : 0;
 }
 
 // Adds up the timed launches that have finished (waits for them).
@@ -264,19 +284,8 @@ mmas_status mmas_batch_create(int32_t count, const int32_t* const* dists_host, c
     }
     b->pair_ok = true;
     for (int i = 0; i < count; ++i) b->pair_ok = b->pair_ok && b->items[i].s.cl >= 1 && b->items[i].s.cl <= 32;
-    // Without a launch asked for: two ants per wave, eight per workgroup and no
-    // LDS table (rows from L2; a table leaves fewer waves per SIMD to hide the
-    // steps' chains), the fastest or within 3 % of it from 512 to 20 thousand
-    // ants: 160 colonies of 64 ants, n 200-1000: 1.21 ms a step against 3.62
-    // with one ant per wave, four per workgroup and a full table, and 1.41
-    // without the table; 20 instances with ants = n: 1.59, 9.49 and 2.51 ms.
-    // Lists longer than 32 take one ant per wave, with the table only while
-    // every workgroup has a CU of its own.
-    const int lds = mmas::max_lds_per_block() - kStaticLds;
-    b->lanes_per_ant = b->pair_ok ? 32 : 64;
-    b->ants_per_block = b->pair_ok && 8 * b->per_ant <= lds ? 8 : 4;
-    b->table_request = b->pair_ok || (int64_t)total_ants > 4 * (int64_t)mmas::compute_units() ? 0 : -1;
-    b->table_bytes = b->table_request < 0 ? std::max(0, (lds - b->ants_per_block * b->per_ant) & ~15) : 0;
+    b->asked = false;
+    default_launch(b);
     r = rebuild_tiles(b);
     if (r != MMAS_OK) {
         for (mmas_ctx* c : b->ctx) mmas_destroy(c);
@@ -299,6 +308,7 @@ mmas_status mmas_batch_set_launch(mmas_batch* b, int32_t ants_per_block, int32_t
     const int budget = (mmas::max_lds_per_block() - kStaticLds - ants_per_block * b->per_ant) & ~15;
     if (budget < 0) return MMAS_EUNSUPPORTED;
     drop_graph(b);
+    b->asked = true;
     b->ants_per_block = ants_per_block;
     b->lanes_per_ant = lanes;
     b->table_request = table_bytes;
@@ -309,9 +319,18 @@ mmas_status mmas_batch_set_launch(mmas_batch* b, int32_t ants_per_block, int32_t
 mmas_status mmas_batch_set_tabu(mmas_batch* b, int32_t tabu) {
     if (!b || (tabu != MMAS_TABU_BITMASK && tabu != MMAS_TABU_COMPACT && tabu != MMAS_TABU_LIST)) return MMAS_EINVAL;
     const int keep = b->tabu;
+    const bool asked = b->asked;
     apply_tabu(b, tabu);
+    if (!asked) default_launch(b);  // (a shape that nobody asked for follows the tabu's LDS)
     mmas_status r = mmas_batch_set_launch(b, b->ants_per_block, b->table_request, b->lanes_per_ant);
-    if (r != MMAS_OK) apply_tabu(b, keep);
+    b->asked = asked;
+    if (r != MMAS_OK) {
+        apply_tabu(b, keep);
+        if (!asked) {
+            default_launch(b);
+            (void)rebuild_tiles(b);
+        }
+    }
     return r;
 }
 

@@ -177,3 +177,28 @@ def test_default_launch(gpu, cl, ants):
             assert np.array_equal(v.tours(), ref[k][it][0])
             assert np.array_equal(v.lengths(), ref[k][it][2])
             assert np.array_equal(v.pheromone(), ref[k][it][1])
+
+
+@pytest.mark.parametrize("tabu,n,pher", [("list", 5000, "dense"), ("compact", 10000, "candidates")])
+def test_default_launch_follows_the_tabu(gpu, tabu, n, pher):
+    """A batch whose launch nobody set takes every tabu of which four ants fit a
+    workgroup's LDS (lists 4n bytes an ant, compact entries 2n), and tours are
+    those of a single colony; a shape that was asked for is kept, and refused
+    where it does not fit."""
+    from paper_2003_11902_amd import mmas as M
+    _, d = I.make_instance("uniform", n, seed=31)
+    p = M.make_params(n, 5, cand_len=16, rho=0.05, seed=11, pher=pher)
+    say(f"set_tabu {tabu} n={n} {pher}")
+    b = M.Batch([d], [p])
+    b.set_tabu(tabu)
+    b.step()
+    c = M.Colony(d, 5, cand_len=16, rho=0.05, seed=11, pher=pher)
+    c.iterate(0)
+    assert np.array_equal(b.instance(0).tours(), c.tours())
+    b.set_tabu("bitmask")
+    b.set_launch(8, 0, 32)
+    with pytest.raises(M.MmasError):
+        b.set_tabu(tabu)
+    b.step()  # (as before the refused call)
+    c.iterate(1)
+    assert np.array_equal(b.instance(0).tours(), c.tours())
