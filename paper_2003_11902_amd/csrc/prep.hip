@@ -72,7 +72,8 @@ constexpr int kNearCap = 256;
 // four loads and then one in flight, 184 / 4470 by taking the next smallest
 // entry k times. (n = 3795: 57.6 MB, 12 us at a copy's rate.)
 // Rows with more than kNearCap entries up to the bound (long runs of equal
-// distances) take the smallest remaining entry k times.
+// distances) look for the least bound that holds k, by bisection over all
+// entries, and take of the cities at it the first ones.
 // `clear` (or null): cleared at i, for the kernel that counts in-degrees next.
 template <int kRegs>
 __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, int n, int k,
@@ -146,31 +147,58 @@ __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, 
             }
         }
     }
-    if (__builtin_expect(m <= kNearCap, 1)) {
-        // (one wave's LDS operations complete in order)
-        for (int e = lane; e < ((m + kWave - 1) & ~(kWave - 1)); e += kWave) {
-            const uint64_t key = e < m ? s_key[wave][e] : ~0ull;
-            int rank = 0;
+    if (__builtin_expect(m > kNearCap, 0)) {
+        // the least bound with k entries up to it (or with few enough to sort);
+        // `below`: entries up to the bound before it
+        uint32_t least = wave_min_u32<4>(min(m0, m1));
+        int below = 0;
+        while (least < hi) {
+            const uint32_t mid = least + (hi - least) / 2;
+            int c = 0;
+            for (int j0 = 0; j0 < n; j0 += kBatch * kWave) {
+                if (!kRegs) fetch(j0);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) c += __popcll(__ballot(x[u] <= mid));
+            }
+            if (c < k) {
+                least = mid + 1;
+                below = c;
+            } else {
+                hi = mid;
+                if (c <= kNearCap) break;
+            }
+        }
+        // every entry before the bound, and those at it in index order while
+        // there is room (at least k in all)
+        const int room = least < hi ? kNearCap : k - below;
+        int at_bound = 0;
+        m = 0;
+        for (int j0 = 0; j0 < n; j0 += kBatch * kWave) {
+            if (!kRegs) fetch(j0);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const uint64_t equal = __ballot(x[u] == hi), before = (1ull << lane) - 1ull;
+                const bool mine = x[u] < hi || (x[u] == hi && at_bound + __popcll(equal & before) < room);
+                const uint64_t in = __ballot(mine);
+                if (mine)
+                    s_key[wave][m + __popcll(in & before)] =
+                        ((uint64_t)x[u] << 32) | (uint32_t)(j0 + u * kWave + lane);
+                at_bound += __popcll(equal);
+                m += __popcll(in);
+            }
+        }
+    }
+    // (one wave's LDS operations complete in order)
+    for (int e = lane; e < ((m + kWave - 1) & ~(kWave - 1)); e += kWave) {
+        const uint64_t key = e < m ? s_key[wave][e] : ~0ull;
+        int rank = 0;
 #pragma unroll 8
-            for (int q = 0; q < m; ++q) rank += s_key[wave][q] < key ? 1 : 0;
-            if (e < m && rank < k) o[rank] = (uint16_t)key;
-        }
-        // (a matrix that is refused may leave too few: any city keeps the
-        // later set-up steps in bounds)
-        for (int r = m + lane; r < k; r += kWave) o[r] = 0;
-        return;
+        for (int q = 0; q < m; ++q) rank += s_key[wave][q] < key ? 1 : 0;
+        if (e < m && rank < k) o[rank] = (uint16_t)key;
     }
-    uint64_t prev = 0;  // keys are (d << 32 | j) with d >= 1 for j != i
-    for (int r = 0; r < k; ++r) {
-        uint64_t best = ~0ull;
-        for (int q = lane; q < n; q += kWave) {
-            const uint64_t key = ((uint64_t)(uint32_t)row[q] << 32) | (uint32_t)q;
-            if (q != i && key > prev && key < best) best = key;
-        }
-        best = wave_min_u64(best);
-        if (lane == 0) o[r] = best == ~0ull ? (uint16_t)0 : (uint16_t)(best & 0xFFFFu);
-        prev = best;
-    }
+    // (a matrix that is refused may leave too few: any city keeps the later
+    // set-up steps in bounds)
+    for (int r = m + lane; r < k; r += kWave) o[r] = 0;
 }
 
 // LDS of the nearest-neighbour tour: visited bits, then the first `p` entries

@@ -63,6 +63,22 @@ def test_equal_distances(gpu, n):
         check(d, 64, 0, pher="candidates")
 
 
+@pytest.mark.parametrize("n", [1024, 1025, 2049, 4097])
+def test_bounds_among_equal_distances(gpu, n):
+    """Runs of equal distances with rows in registers and read again: a run at
+    the k-th smallest with entries before it, distances far apart, and runs
+    short enough to be sorted whole."""
+    rng = np.random.default_rng(n)
+    for values, p in (([5, 2000000000], None), ([1, 2, 3000, 2147483647], [0.004, 0.004, 0.5, 0.492]),
+                      (np.arange(1, 2 + n // 290) * 123457, None)):
+        d = rng.choice(np.asarray(values, np.int32), (n, n), p=p)
+        d = np.triu(d, 1)
+        d = d + d.T
+        say(f"bounds among equal distances n={n} {len(values)} values")
+        check(d, 16, 0, pher="candidates")
+        check(d, 64, 32, pher="candidates")
+
+
 def test_refused_matrices_stay_refused(gpu):
     """Matrices with negative or zero distances are refused (and leave the
     lists of later set-up steps in bounds)."""
