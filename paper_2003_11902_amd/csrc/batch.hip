@@ -140,22 +140,33 @@ void apply_tabu(mmas_batch* b, int tabu) {
     for (auto& it : b->items) it.s.tabu = tabu;
 }
 
-// The launch shape of a batch without one asked for, by the current tabu: two
-// ants per wave, eight per workgroup (four where eight do not fit) and no LDS
-// table (rows from L2; a table leaves fewer waves per SIMD to hide the steps'
-// chains), the fastest or within 3 % of it from 512 to 20 thousand ants: 160
-// colonies of 64 ants, n 200-1000: 1.21 ms a step against 3.62 with one ant
-// per wave, four per workgroup and a full table, and 1.41 without the table;
-// 20 instances with ants = n: 1.59, 9.49 and 2.51 ms. Lists longer than 32
-// take one ant per wave, with the table only while every workgroup has a CU
-// of its own.
+// The launch shape of a batch without one asked for, by the current tabu.
+// While every workgroup of four ants has a CU of its own, a lone wave's step is
+// a chain of latencies: lists up to 16 entries and those longer than 32 take
+// one ant per wave and the LDS table (4 to 1024 ants, n 200-3000, against the
+// shape below: 8 entries 5 to 33 % less time, 16 entries 6 % more to 13 % less,
+// 32 entries 4 % less to 11 % more; n = 3000, 128 ants: 2.21 and 3.28 ms with 8
+// entries, 1.96 and 2.26 with 16, 1.86 and 1.83 with 32).
+// Otherwise two ants per wave where the lists fit, eight per workgroup (four
+// where eight do not fit), and no table (rows from L2; a table leaves fewer
+// waves per SIMD to hide the steps' chains): 160 colonies of 64 ants, n
+// 200-1000: 1.21 ms a step against 3.62 with one ant per wave, four per
+// workgroup and a full table, and 1.41 without the table; 20 instances with
+// ants = n: 1.59, 9.49 and 2.51 ms; 2048 ants, n = 1000, lists of 8 entries:
+// 0.78, 1.15 and 0.74 ms.
 void default_launch(mmas_batch* b) {
     int64_t ants = 0;
-    for (const auto& it : b->items) ants += it.s.ants;
+    int cl = 0;
+    for (const auto& it : b->items) {
+        ants += it.s.ants;
+        cl = std::max(cl, it.s.cl);
+    }
     const int lds = mmas::max_lds_per_block() - kStaticLds;
-    b->lanes_per_ant = b->pair_ok ? 32 : 64;
-    b->ants_per_block = b->pair_ok && 8 * b->per_ant <= lds ? 8 : 4;
-    b->table_request = b->pair_ok || ants > 4 * (int64_t)mmas::compute_units() ? 0 : -1;
+    const bool few = ants <= 4 * (int64_t)mmas::compute_units();
+    const bool pair = b->pair_ok && !(few && cl <= 16);
+    b->lanes_per_ant = pair ? 32 : 64;
+    b->ants_per_block = pair && 8 * b->per_ant <= lds ? 8 : 4;
+    b->table_request = few && !pair ? -1 : 0;
     b->table_bytes = b->table_request < 0 ? std::max(0, (lds - b->ants_per_block * b->per_ant) & ~15) : 0;
 }
 

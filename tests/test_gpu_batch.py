@@ -202,3 +202,25 @@ def test_default_launch_follows_the_tabu(gpu, tabu, n, pher):
     b.step()  # (as before the refused call)
     c.iterate(1)
     assert np.array_equal(b.instance(0).tours(), c.tours())
+
+
+@pytest.mark.parametrize("cl,ants", [(16, 5), (17, 5), (16, 400), (1, 3)])
+def test_default_launch_by_list_length(gpu, cl, ants):
+    """The default launch on both sides of its rule: lists up to 16 entries with
+    few ants (one ant per wave, the table in LDS) and with more than the GPU
+    takes four a CU, and longer lists."""
+    from paper_2003_11902_amd import mmas as M
+    dists, params = [], []
+    for k, n in enumerate((300, 258, 60)):
+        _, d = I.make_instance("uniform", n, seed=90 + k)
+        dists.append(d)
+        params.append(M.make_params(n, ants, cand_len=cl, rho=0.05, seed=17 + k))
+    say(f"default launch by list length cl={cl} ants={ants}")
+    ref = singles(dists, params, 2)
+    b = M.Batch(dists, params)
+    for it in range(2):
+        b.step()
+        b.synchronize()
+        for i in range(len(dists)):
+            assert np.array_equal(b.instance(i).tours(), ref[i][it][0]), (it, i)
+            assert np.array_equal(b.instance(i).pheromone(), ref[i][it][1]), (it, i)
