@@ -348,8 +348,11 @@ __global__ __launch_bounds__(256) void k_update_cand(Views vw, Shape s) {
     }
 }
 
-// Sizes up to which the update is one launch (k_update_small).
-constexpr int kFusedRows = 1024, kFusedAnts = 2048;
+// Sizes up to which the update is one launch (k_update_small): with more ants
+// every workgroup's reading of the lengths costs as much as the launch it saves
+// (two launches -> one, 1536 ants: n = 50 10.2 -> 10.2 us, n = 200 10.4 -> 9.4,
+// n = 1000 16.5 -> 16.5; 2048 ants: 10.3 -> 10.8, 10.7 -> 9.8, 16.7 -> 17.1).
+constexpr int kFusedRows = 1024, kFusedAnts = 1536;
 
 int grid_for(size_t total, int block) {
     size_t g = (total + block - 1) / block;

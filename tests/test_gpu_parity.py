@@ -334,3 +334,11 @@ def test_update_sizes(gpu, n, ants, deposit, problem):
     say(f"update n={n} ants={ants} {deposit} {problem}")
     g, o, _ = run_parity(d, 3, ants=ants, cand_len=8, rho=0.2, seed=3, deposit=deposit, problem=problem)
     assert np.array_equal(g.best()[0], o.best()[0])
+
+
+@pytest.mark.parametrize("ants", [1536, 1537])
+def test_update_ant_limit(gpu, ants):
+    """The update on both sides of the ant count up to which it is one launch."""
+    _, d = I.make_instance("uniform", 70, seed=5)
+    say(f"update n=70 ants={ants}")
+    run_parity(d, 3, ants=ants, cand_len=8, rho=0.2, seed=3)
