@@ -88,8 +88,10 @@ __device__ __forceinline__ Normal normal_tail(float z) {
     p = __builtin_fmaf(p, t, 0.116584545f);
     return Normal{p * t * e, e};
 }
+// (h is 0 long before z = 64: the bound keeps infinity times 0 out of the sum)
 __device__ __forceinline__ float gelu_of(float z, const Normal& n) {
-    return __builtin_fmaf(-__builtin_fabsf(z), n.h, z > 0.0f ? z : 0.0f);
+    const float u = __builtin_amdgcn_fmed3f(z, -__builtin_inff(), 64.0f);
+    return __builtin_fmaf(-__builtin_fabsf(u), n.h, z > 0.0f ? z : 0.0f);
 }
 // the derivative Phi(z) + z phi(z)
 __device__ __forceinline__ float gelu_d_of(float z, const Normal& n) {

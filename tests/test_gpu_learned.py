@@ -224,3 +224,33 @@ def test_mlp_edge_counts(gpu, E, groups, shift):
     refs = [gref.W1.ravel(), gref.b1, gref.W2.ravel(), gref.b2, gref.w3, np.array([gref.b3])]
     for a, b in zip(split(grad[:-1]), refs):
         assert rel_fro(a, b) < 1e-2
+
+
+@pytest.mark.parametrize("x,w1,w2,w3", [(3e38, 2.0, 0.01, 0.1), (1e38, 1.0, 0.5, 0.1), (1e18, 1.0, 0.5, 0.25),
+                                        (1e38, 1.0, -0.5, 0.1)])
+def test_mlp_overflow(gpu, x, w1, w2, w3):
+    """Pre-activations that overflow FP32 in the first and in the second layer:
+    GELU of +infinity is +infinity (a score far above the others stays that),
+    of a large finite value the value; that of -infinity is not defined by the
+    product z Phi(z) and gives NaN."""
+    from paper_2003_11902_amd import mmas as M
+    W1 = np.zeros((16, 128), np.float32)
+    W1[0] = w1
+    zero = np.zeros(128, np.float32)
+    p = np.concatenate([W1.ravel(), zero, np.full(128 * 128, w2, np.float32), zero, np.full(128, w3, np.float32),
+                        [0.0]]).astype(np.float32)
+    X = np.zeros((20, 16), np.float32)
+    X[3, 0] = x
+    say(f"mlp overflow x={x} w1={w1} w2={w2} w3={w3}")
+    params = gpu.from_numpy(p).cuda()
+    gX = gpu.from_numpy(X).to(gpu.bfloat16).view(gpu.int16).cuda()
+    s = M.mmas_mlp_forward(gX, params, M.mmas_mlp_pack(params)).cpu().numpy().astype(np.float64)
+    assert (s[:3] == 0).all() and (s[4:] == 0).all()
+    bf = gpu.tensor([x, w1, w2, w3], dtype=gpu.bfloat16).double().numpy()
+    z2 = 128 * bf[0] * bf[1] * bf[2]
+    if z2 < -3.4e38:
+        assert np.isnan(s[3])
+    elif z2 > 3.4e38 or bf[0] * bf[1] > 3.4e38:
+        assert s[3] == np.inf
+    else:  # two roundings to bfloat16, 2^-9 each, and FP32 sums
+        assert abs(s[3] / (z2 * 128 * bf[3]) - 1) < 2 ** -8 + 1e-5
