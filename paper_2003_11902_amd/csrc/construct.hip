@@ -287,6 +287,25 @@ struct Fallback {
     uint32_t it, ant, step;
 };
 
+// The fallback's arguments read back into scalar registers (an outlined
+// function gets them in vector registers).
+__device__ __forceinline__ Fallback uni(const Fallback& v) {
+    Fallback q;
+    q.tabu = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)v.tabu);
+    q.L = uni(v.L);
+    q.n = uni(v.n);
+    q.cl = uni(v.cl);
+    q.beta = uni(v.beta);
+    q.irow = (GlbPtr<const float>)uni((uint64_t)(uintptr_t)v.irow);
+    q.drow = (GlbPtr<const int32_t>)uni((uint64_t)(uintptr_t)v.drow);
+    q.tmin_a = uni(v.tmin_a);
+    q.seed = uni(v.seed);
+    q.it = uni(v.it);
+    q.ant = uni(v.ant);
+    q.step = uni(v.step);
+    return q;
+}
+
 template <int kTabu>
 __device__ __forceinline__ bool fallback_seen(const Fallback& q, uint32_t v) {
     if constexpr (kTabu == MMAS_TABU_BITMASK)
@@ -306,9 +325,12 @@ __device__ __forceinline__ float exact_factor(const Fallback& q, uint32_t v) {
 }
 
 // The exact fallback, for the near ties: city v draws slot cl + v, and the
-// largest key (the lowest city among equal ones) wins.
+// largest key (the lowest city among equal ones) wins. (Its registers count for
+// every kernel that may call it: with the arguments in vector registers the
+// candidate-only batches took 65 and lost the eighth wave of a SIMD.)
 template <int kTabu, int kPher>
-__device__ __attribute__((noinline)) uint32_t fallback_exact(Fallback q, int lane) {
+__device__ __attribute__((noinline)) uint32_t fallback_exact(Fallback qv, int lane) {
+    const Fallback q = uni(qv);
     uint32_t bcode = 0u, bnode = kNone;
     for (int v0 = 0; v0 < q.n; v0 += kWave) {
         const uint32_t v = (uint32_t)(v0 + lane);
@@ -471,25 +493,6 @@ __device__ __forceinline__ unsigned long long near_part(const Fallback& q, int p
     else
         near_list<kPher>(q, q.tabu, part, parts, lane, nb);
     return near_share<kPher>(q, nb);
-}
-
-// The fallback's arguments read back into scalar registers (an outlined
-// function gets them in vector registers).
-__device__ __forceinline__ Fallback uni(const Fallback& v) {
-    Fallback q;
-    q.tabu = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)v.tabu);
-    q.L = uni(v.L);
-    q.n = uni(v.n);
-    q.cl = uni(v.cl);
-    q.beta = uni(v.beta);
-    q.irow = (GlbPtr<const float>)uni((uint64_t)(uintptr_t)v.irow);
-    q.drow = (GlbPtr<const int32_t>)uni((uint64_t)(uintptr_t)v.drow);
-    q.tmin_a = uni(v.tmin_a);
-    q.seed = uni(v.seed);
-    q.it = uni(v.it);
-    q.ant = uni(v.ant);
-    q.step = uni(v.step);
-    return q;
 }
 
 // The all-city fallback of one wave: by draw blocks or by list, the cheaper by

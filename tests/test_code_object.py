@@ -104,3 +104,16 @@ def test_dynamic_lds_starts_at_16_bytes(code_objects):
             and "k_construct_team" not in k}  # (the team has no dynamic LDS)
     assert any("k_nn_tour" in k for k in wide) and len(wide) > 20
     assert not {k: v for k, v in wide.items() if v % 16}
+
+
+def test_batched_construction_fits_eight_waves(code_objects):
+    """Eight waves share a SIMD's 512 vector registers: 64 each (the functions a
+    kernel calls count)."""
+    regs = {}
+    for path in code_objects:
+        for block in _run(os.path.join(LLVM, "llvm-readelf"), "--notes", path).split(".agpr_count:")[1:]:
+            name = re.search(r"\.name:\s*(_Z\S+)", block).group(1)
+            if "k_batch_construct" in name:
+                regs[name] = int(re.search(r"\.vgpr_count:\s*(\d+)", block).group(1))
+    assert len(regs) == 24
+    assert not {k: v for k, v in regs.items() if v > 64}
