@@ -1715,8 +1715,9 @@ __global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, ui
         const uint32_t best = wave_max_bcast(m1);
         const uint32_t near = near_code(best);
         const uint64_t tied = __ballot(m1 >= near);
-        const int first = (int)__builtin_ctzll(tied);
-        // (none is near when the wave has no city left: best is 0)
+        // (none is near when the wave has no city left: best is 0, and its city,
+        // which no wave takes then, that of the last lane)
+        const int first = (int)__builtin_ctzll(tied | (1ull << 63));
         bool clear = (__popcll(tied) == 1) & (__ballot(m2 >= near) == 0ull);
         const uint32_t id = best & kId;
         uint32_t next = 4u * (uint32_t)(kWave * (W * (int)(id >> 2) + wave) + first) + (id & 3u);
@@ -1735,7 +1736,7 @@ __global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, ui
             if (W > 8) mx = max(mx, dpp<0x140>(mx));
             const uint32_t top = near_code((uint32_t)__builtin_amdgcn_readfirstlane((int)mx));
             const uint64_t held = __ballot(hi >= top) & ((1ull << W) - 1ull);
-            const uint32_t pick = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)__builtin_ctzll(held));
+            const uint32_t pick = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)__builtin_ctzll(held | (1ull << 63)));
             next = pick >> 1;
             clear = (__popcll(held) == 1) & ((pick & 1u) == 0u);
         }
