@@ -31,6 +31,11 @@ template <class T>
 using LdsPtr = __attribute__((address_space(3))) T*;
 template <class T>
 using GlbPtr = __attribute__((address_space(1))) T*;
+// the LDS address `byte` as a pointer
+template <class T>
+__device__ __forceinline__ LdsPtr<T> lds_at(uint32_t byte) {
+    return (LdsPtr<T>)(uintptr_t)byte;
+}
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 // four consecutive row entries, aligned to one
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
@@ -291,7 +296,7 @@ struct Fallback {
 // function gets them in vector registers).
 __device__ __forceinline__ Fallback uni(const Fallback& v) {
     Fallback q;
-    q.tabu = (LdsPtr<const uint16_t>)uni((uint32_t)(uintptr_t)v.tabu);
+    q.tabu = lds_at<const uint16_t>(uni((uint32_t)(uintptr_t)v.tabu));
     q.L = uni(v.L);
     q.n = uni(v.n);
     q.cl = uni(v.cl);
@@ -547,7 +552,7 @@ __device__ __forceinline__ uint32_t fallback_wave(Fallback q, LdsPtr<uint16_t> l
 // unrolled step loop).
 template <int kTabu, int kPher>
 __device__ __attribute__((noinline)) uint32_t fallback_lone(Fallback qv, LdsPtr<uint16_t> list_v, int cap_v, int lane) {
-    return fallback_wave<kTabu, kPher>(uni(qv), (LdsPtr<uint16_t>)uni((uint32_t)(uintptr_t)list_v), uni(cap_v), lane);
+    return fallback_wave<kTabu, kPher>(uni(qv), lds_at<uint16_t>(uni((uint32_t)(uintptr_t)list_v)), uni(cap_v), lane);
 }
 
 // The exact choice of a candidate step whose approximate keys nearly tie:
@@ -1075,7 +1080,7 @@ __device__ __forceinline__ void construct_lone(ItemPtr item, uint32_t it, int an
             // it: lane 0 into the city's word, the others a 0 into their own
             // word of the draw buffer (no change)
             const uint32_t addr = mark_base + (((next >> 5) << 2) & mark_mask);
-            __hip_atomic_fetch_or((LdsPtr<uint32_t>)(uintptr_t)addr, (1u << (next & 31u)) & mark_mask,
+            __hip_atomic_fetch_or(lds_at<uint32_t>(addr), (1u << (next & 31u)) & mark_mask,
                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
             tabu.mark_at(next, at);
@@ -1095,8 +1100,8 @@ __device__ __forceinline__ void construct_lone(ItemPtr item, uint32_t it, int an
     asm volatile("" : "+v"(lds_cand_l), "+v"(lds_chc_l));
     auto load_row_near = [&](int c) {
         const uint32_t e = (uint32_t)(c * cl);
-        node_next = *(LdsPtr<const _Float16>)(lds_cand_l + 2u * e);
-        w_next = *(LdsPtr<const float>)(lds_chc_l + 4u * e);
+        node_next = *lds_at<const _Float16>(lds_cand_l + 2u * e);
+        w_next = *lds_at<const float>(lds_chc_l + 4u * e);
     };
     auto load_row_far = [&](int c) {
         const uint32_t e = (uint32_t)(c * cl);
@@ -1128,7 +1133,7 @@ __device__ __forceinline__ void construct_lone(ItemPtr item, uint32_t it, int an
         const float lnu = lds_ln[4 * j * G + ln_lane];
         uint32_t seen = 0u, cell = 0u;
         if constexpr (kTabu == MMAS_TABU_BITMASK)
-            seen = (uint32_t)__builtin_amdgcn_sbfe((int)*(LdsPtr<const uint32_t>)(cells + 4u * node_word), node_raw, 1u);
+            seen = (uint32_t)__builtin_amdgcn_sbfe((int)*lds_at<const uint32_t>(cells + 4u * node_word), node_raw, 1u);
         else
             cell = tabu.cell(node_raw);
         if constexpr (kTabu != MMAS_TABU_BITMASK) {
@@ -1341,7 +1346,7 @@ __device__ __attribute__((noinline)) uint32_t fallback_item(ItemPtr item_v, LdsP
     const int k = uni(k_v), n = item->s.n;
     const size_t row = (size_t)uni(cur_v) * n;
     Fallback q;
-    q.tabu = (LdsPtr<const uint16_t>)(region + (uint32_t)(kDrawBytes + kScratchBytes));
+    q.tabu = lds_at<const uint16_t>(region + (uint32_t)(kDrawBytes + kScratchBytes));
     q.L = n - k;
     q.n = n;
     q.cl = item->s.cl;
@@ -1356,7 +1361,7 @@ __device__ __attribute__((noinline)) uint32_t fallback_item(ItemPtr item_v, LdsP
     q.step = (uint32_t)k;
     const int cap = list_cap(n, item->s.list_cap);
     return fallback_wave<kTabu, kPher>(
-        q, (LdsPtr<uint16_t>)(region + (uint32_t)(kDrawBytes + kScratchBytes) + (uint32_t)align16(4 * ((n + 31) / 32))),
+        q, lds_at<uint16_t>(region + (uint32_t)(kDrawBytes + kScratchBytes) + (uint32_t)align16(4 * ((n + 31) / 32))),
         cap, lane);
 }
 
@@ -1366,12 +1371,12 @@ __device__ __attribute__((noinline)) uint32_t fallback_item(ItemPtr item_v, LdsP
 template <int kTabu>
 __device__ __forceinline__ uint32_t seen_pair(uint32_t cells, int n, int L, uint32_t v) {
     if constexpr (kTabu == MMAS_TABU_BITMASK) {
-        const uint32_t word = *(LdsPtr<const uint32_t>)(cells + 4u * __builtin_amdgcn_ubfe(v, 5u, 11u));
+        const uint32_t word = *lds_at<const uint32_t>(cells + 4u * __builtin_amdgcn_ubfe(v, 5u, 11u));
         return (uint32_t)__builtin_amdgcn_sbfe((int)word, v, 1u);
     } else if constexpr (kTabu == MMAS_TABU_COMPACT) {
-        return *(LdsPtr<const uint16_t>)(cells + 2u * v) > v ? ~0u : 0u;
+        return *lds_at<const uint16_t>(cells + 2u * v) > v ? ~0u : 0u;
     } else {
-        return (int)*(LdsPtr<const uint16_t>)(cells + 2u * ((uint32_t)n + v)) >= L ? ~0u : 0u;
+        return (int)*lds_at<const uint16_t>(cells + 2u * ((uint32_t)n + v)) >= L ? ~0u : 0u;
     }
 }
 __device__ __forceinline__ int pair_left(const BitmaskTabu&, const BitmaskTabu&, int) { return 0; }
@@ -1487,7 +1492,7 @@ __device__ __forceinline__ void construct_pair(ItemPtr item, uint32_t it, int an
                 node = *(GlbPtr<const uint16_t>)(glb_cand + 2u * e);
                 w = *(GlbPtr<const float>)(glb_chc + 4u * e);
             }
-            const float lnu = *(LdsPtr<const float>)(ln_lane + (uint32_t)(16 * (k - k0) * G));
+            const float lnu = *lds_at<const float>(ln_lane + (uint32_t)(16 * (k - k0) * G));
             const uint32_t seen = seen_pair<kTabu>(cells, n, pair_left(tabA, tabB, h), node);
             float key = lnu * w;  // (w holds 1 / choice_info)
             asm volatile("" : "+v"(key));
@@ -1524,7 +1529,7 @@ __device__ __forceinline__ void construct_pair(ItemPtr item, uint32_t it, int an
             const uint32_t nx = h ? nextB : nextA;
             if constexpr (kTabu == MMAS_TABU_BITMASK) {
                 const uint32_t addr = mark_base + 4u * __builtin_amdgcn_ubfe(nx, 5u, mark_bits);
-                __hip_atomic_fetch_or((LdsPtr<uint32_t>)(uintptr_t)addr, mark_one << (nx & 31u), __ATOMIC_RELAXED,
+                __hip_atomic_fetch_or(lds_at<uint32_t>(addr), mark_one << (nx & 31u), __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_WORKGROUP);
             } else {
                 tabA.mark(nextA, lane);
@@ -1718,7 +1723,8 @@ __global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, ui
         // (none is near when the wave has no city left: best is 0, and its city,
         // which no wave takes then, that of the last lane)
         const int first = (int)__builtin_ctzll(tied | (1ull << 63));
-        bool clear = (__popcll(tied) == 1) & (__ballot(m2 >= near) == 0ull);
+        const bool one = __popcll(tied) == 1, alone = __ballot(m2 >= near) == 0ull;
+        bool clear = one & alone;
         const uint32_t id = best & kId;
         uint32_t next = 4u * (uint32_t)(kWave * (W * (int)(id >> 2) + wave) + first) + (id & 3u);
         if constexpr (W > 1) {
@@ -1738,7 +1744,8 @@ __global__ __launch_bounds__(64 * W) void k_construct_team(Views vw, Shape s, ui
             const uint64_t held = __ballot(hi >= top) & ((1ull << W) - 1ull);
             const uint32_t pick = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)__builtin_ctzll(held | (1ull << 63)));
             next = pick >> 1;
-            clear = (__popcll(held) == 1) & ((pick & 1u) == 0u);
+            const bool one_wave = __popcll(held) == 1, sure = (pick & 1u) == 0u;
+            clear = one_wave & sure;
         }
         if (__builtin_expect(!clear, 0)) {
             // the exact keys (every wave of the team comes here)

@@ -117,3 +117,14 @@ def test_batched_construction_fits_eight_waves(code_objects):
                 regs[name] = int(re.search(r"\.vgpr_count:\s*(\d+)", block).group(1))
     assert len(regs) == 24
     assert not {k: v for k, v in regs.items() if v > 64}
+
+
+@pytest.mark.parametrize("name", ["mmas.hip", "prep.hip", "construct.hip", "update.hip", "two_opt.hip", "batch.hip",
+                                  "learned.hip", "diag.hip"])
+def test_sources_compile_without_a_warning(name):
+    """Neither the device's nor the host's pass of the compiler warns."""
+    from paper_2003_11902_amd import build
+    assert name in build.SOURCES
+    r = subprocess.run([build._hipcc(), *build.FLAGS, "-fsyntax-only", os.path.join(build.CSRC, name)],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "warning" not in r.stderr, r.stderr[:2000]
