@@ -436,6 +436,11 @@ mmas_status mmas_set_learned_heuristic(mmas_ctx* ctx, const uint16_t* knn_dev, c
  * (seed, it[i], ant[i], step[i], slot[i]) (device arrays of `count`). Both
  * enqueue on `hip_stream` and return without waiting. */
 mmas_status mmas_eval_log(const float* dev_u, float* dev_out, size_t count, void* hip_stream);
+/* The approximate base-2 logarithm of the u of `count` draw words (device
+ * arrays): within a relative 2^-23 of log2 u for every draw, which the
+ * construction relies on where it compares approximate keys. EINVAL for null
+ * pointers. */
+mmas_status mmas_eval_near_log(const uint32_t* dev_draws, float* dev_out, size_t count, void* hip_stream);
 mmas_status mmas_eval_draws(uint64_t seed, const uint32_t* dev_it, const uint32_t* dev_ant,
                             const uint32_t* dev_step, const uint32_t* dev_slot, uint32_t* dev_out,
                             size_t count, void* hip_stream);

@@ -1,4 +1,4 @@
-// Diagnostic entry points: the device logarithm and Philox draws on arrays,
+// Diagnostic entry points: the device logarithms and Philox draws on arrays,
 // so that they can be compared with an independent implementation.
 #include "device.hpp"
 #include "internal.hpp"
@@ -9,6 +9,12 @@ namespace {
 __global__ __launch_bounds__(256) void k_eval_log(const float* __restrict__ u, float* __restrict__ out, size_t count) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
         out[i] = log_u01(u[i]);
+}
+
+__global__ __launch_bounds__(256) void k_eval_near_log(const uint32_t* __restrict__ x, float* __restrict__ out,
+                                                       size_t count) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
+        out[i] = log2_draw(x[i]);
 }
 
 __global__ __launch_bounds__(256) void k_eval_draws(uint64_t seed, const uint32_t* __restrict__ it,
@@ -34,6 +40,14 @@ extern "C" mmas_status mmas_eval_log(const float* dev_u, float* dev_out, size_t 
     if (count == 0) return MMAS_OK;
     if (!dev_u || !dev_out) return MMAS_EINVAL;
     mmas::k_eval_log<<<mmas::grid_for(count), 256, 0, reinterpret_cast<hipStream_t>(hip_stream)>>>(dev_u, dev_out, count);
+    return hipGetLastError() == hipSuccess ? MMAS_OK : MMAS_EHIP;
+}
+
+extern "C" mmas_status mmas_eval_near_log(const uint32_t* dev_draws, float* dev_out, size_t count, void* hip_stream) {
+    if (count == 0) return MMAS_OK;
+    if (!dev_draws || !dev_out) return MMAS_EINVAL;
+    mmas::k_eval_near_log<<<mmas::grid_for(count), 256, 0, reinterpret_cast<hipStream_t>(hip_stream)>>>(dev_draws,
+                                                                                                       dev_out, count);
     return hipGetLastError() == hipSuccess ? MMAS_OK : MMAS_EHIP;
 }
 

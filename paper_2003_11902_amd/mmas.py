@@ -54,7 +54,7 @@ EXPORTED = (
     "mmas_workspace_bytes", "mmas_create", "mmas_prepare_choice_info", "mmas_construct",
     "mmas_two_opt", "mmas_update_pheromone", "mmas_best", "mmas_buffer", "mmas_read",
     "mmas_set_pheromone", "mmas_synchronize", "mmas_destroy", "mmas_status_str",
-    "mmas_eval_log", "mmas_eval_draws", "mmas_eval_tabu", "mmas_set_selection", "mmas_set_launch",
+    "mmas_eval_log", "mmas_eval_near_log", "mmas_eval_draws", "mmas_eval_tabu", "mmas_set_selection", "mmas_set_launch",
     "mmas_batch_workspace_bytes", "mmas_batch_create", "mmas_batch_set_launch", "mmas_batch_tune",
     "mmas_batch_capture", "mmas_batch_step", "mmas_batch_iteration", "mmas_batch_context",
     "mmas_batch_destroy", "mmas_mlp_param_count", "mmas_mlp_packed_count", "mmas_mlp_features",
@@ -134,6 +134,8 @@ def _load():
     L.mmas_destroy.restype = None
     L.mmas_eval_log.argtypes = [p, p, C.c_size_t, p]
     L.mmas_eval_log.restype = C.c_int
+    L.mmas_eval_near_log.argtypes = [p, p, C.c_size_t, p]
+    L.mmas_eval_near_log.restype = C.c_int
     L.mmas_eval_draws.argtypes = [C.c_uint64, p, p, p, p, p, C.c_size_t, p]
     L.mmas_eval_draws.restype = C.c_int
     L.mmas_eval_tabu.argtypes = [C.c_int32, C.c_int32, p, C.c_int32, p, p, p, p]
@@ -210,6 +212,16 @@ def mmas_eval_log(u):
     out = torch.empty_like(u)
     _check(lib.mmas_eval_log(C.c_void_p(u.data_ptr()), C.c_void_p(out.data_ptr()), u.numel(),
                              C.c_void_p(torch.cuda.current_stream().cuda_stream)), "mmas_eval_log")
+    return out
+
+
+def mmas_eval_near_log(draws):
+    """Approximate base-2 logarithms of the u of an int32 CUDA tensor of draw
+    words (new float32 tensor)."""
+    import torch
+
+    out = torch.empty(draws.shape, dtype=torch.float32, device=draws.device)
+    _check(lib.mmas_eval_near_log(_dptr(draws), _dptr(out), draws.numel(), _cur_stream()), "mmas_eval_near_log")
     return out
 
 

@@ -342,3 +342,69 @@ def test_update_ant_limit(gpu, ants):
     _, d = I.make_instance("uniform", 70, seed=5)
     say(f"update n=70 ants={ants}")
     run_parity(d, 3, ants=ants, cand_len=8, rho=0.2, seed=3)
+
+
+def test_near_log_bound(gpu):
+    """The approximate logarithm of the keys lies within a relative 2^-23 of
+    log2 u on all 2^23 values of u, whatever the draw's low nine bits: the
+    width of a near tie (32 codes, 27 needed) rests on this bound."""
+    from paper_2003_11902_amd import mmas as M
+    k = np.arange(1 << 23, dtype=np.uint32)
+    low = np.random.default_rng(1).integers(0, 512, k.size).astype(np.uint32)
+    draws = gpu.from_numpy(((k << 9) | low).view(np.int32)).cuda()
+    out = M.mmas_eval_near_log(draws).cpu().numpy()
+    exact = np.log2((2 * k.astype(np.float64) + 1) * 2.0 ** -24)
+    err = np.abs(out.astype(np.float64) - exact) / np.abs(exact)
+    say(f"near log: relative error up to {err.max():.4g}, bound {2.0 ** -23:.4g}")
+    assert (out < 0).all() and err.max() <= 2.0 ** -23
+
+
+@pytest.mark.parametrize("n,alpha,beta,side,tau_min", [
+    (300, 8, 8, 1e5, None),      # tau_min^alpha 0: every factor infinite
+    (300, 2, 8, 3e7, None),      # d^beta overflows for most cities
+    (260, 1, 8, 6e4, None),      # eta^beta denormal or 0 beside normal weights
+    (300, 8, 8, 6e4, 8.0),       # tau_min^alpha 2^24: normal weights of denormal eta^beta
+    (300, 4, 0, 1e4, 3.1e-10),   # tau_min^alpha denormal, its reciprocal finite
+    (1000, 0, 0, 1e4, None),     # every weight 1: draws that nearly tie
+    (400, 1, 2, 2e1, None),      # coarse distances
+])
+def test_near_ties_along_lists(gpu, n, alpha, beta, side, tau_min):
+    """Candidate-only trails, whose fallback factors are approximate too: at the
+    ends of the range in which they are bounded, with every tabu, one and two
+    ants per wave, several waves per ant, and both steps of a batch."""
+    from paper_2003_11902_amd import mmas as M
+    _, d = I.make_instance("uniform", n, seed=n + 2, side=side)
+    kw = dict(cand_len=4, alpha=alpha, beta=beta, rho=0.1, seed=6, pher="candidates")
+    for tabu, launch in (("bitmask", None), ("compact", (0, -1, 64, 1)), ("list", (0, -1, 64, 4)),
+                         ("bitmask", (0, -1, 64, 4)), ("bitmask", (4, -1, 32, 0)), ("list", (4, -1, 32, 0))):
+        say(f"near ties along lists n={n} alpha={alpha} beta={beta} tau_min={tau_min} {tabu} {launch}")
+        g, o = make_pair(d, 24, tabu=tabu, **kw)
+        if launch is not None:
+            g.set_launch(*launch)
+        if tau_min is not None:
+            tau = np.full((n, 4), 2 * tau_min, np.float32)
+            ck = o.checkpoint()
+            ck.update(pheromone=tau, limits=(np.float32(tau_min), np.float32(4 * tau_min)))
+            o.restore(ck)
+            gk = g.checkpoint()
+            gk["pheromone"] = tau
+            gk["state"].tau_min, gk["state"].tau_max = tau_min, 4 * tau_min
+            g.restore(gk)
+        g.construct(0)
+        o.prepare_choice()
+        o.construct(0, 8)
+        compare_iteration(g, o, 0, check_tau=False)
+        assert g.state().flags == 0
+    if tau_min is not None:
+        return
+    for pher in ("candidates", "dense"):
+        _, o = make_pair(d, 24, **dict(kw, pher=pher))
+        o.prepare_choice()
+        o.construct(0, 8)
+        for tabu, lanes in (("bitmask", 32), ("bitmask", 64), ("compact", 32), ("list", 64)):
+            say(f"near ties along lists, batch {pher} {tabu} {lanes}")
+            b = M.Batch([d], [M.make_params(n, 24, tabu=tabu, **dict(kw, pher=pher))])
+            b.set_launch(4, 0, lanes)
+            b.step()
+            b.synchronize()
+            assert np.array_equal(b.instance(0).tours(), o.tours())
