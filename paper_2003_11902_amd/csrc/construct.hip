@@ -169,25 +169,6 @@ struct ListTabu {
 
 // ---- fallback weights --------------------------------------------------------
 
-// A fallback key is ln(u) times the reciprocal of the weight (Sec. 4.2.2).
-// The factor functors give that reciprocal: read from the dense matrix of
-// reciprocals the update writes, or computed from the distance (trails kept
-// along the candidate lists only: every other weight is tau_min^alpha *
-// eta^beta).
-struct DenseFactor {
-    const float* row_inv;
-    __device__ __forceinline__ float operator()(uint32_t v) const { return row_inv[v]; }
-};
-
-struct CandFactor {
-    const int32_t* drow;
-    float tmin_a;
-    int beta;
-    __device__ __forceinline__ float operator()(uint32_t v) const {
-        return 1.0f / (tmin_a * heur_from_dist(drow[v], beta));
-    }
-};
-
 // The weights themselves (the roulette wheel sums them).
 struct DenseWeight {
     const float* row;
@@ -256,10 +237,6 @@ __device__ __forceinline__ float uni(float x) { return __int_as_float(__builtin_
 __device__ __forceinline__ uint64_t uni(uint64_t x) {
     return ((uint64_t)uni((uint32_t)(x >> 32)) << 32) | uni((uint32_t)x);
 }
-template <class T>
-__device__ __forceinline__ T* uni_ptr(T* p) {
-    return reinterpret_cast<T*>(uni((uint64_t)reinterpret_cast<uintptr_t>(p)));
-}
 
 
 // A kernel's instance, read through the constant address space (scalar loads):
@@ -321,6 +298,10 @@ __device__ __forceinline__ bool fallback_seen(const Fallback& q, uint32_t v) {
         return (int)q.tabu[q.n + v] >= q.L;
 }
 
+// A fallback key is ln(u) times the reciprocal of the weight (Sec. 4.2.2): read
+// from the dense matrix of reciprocals the update writes, or computed from the
+// distance (trails kept along the candidate lists only: every other weight is
+// tau_min^alpha * eta^beta).
 template <int kPher>
 __device__ __forceinline__ float exact_factor(const Fallback& q, uint32_t v) {
     if constexpr (kPher == MMAS_PHER_DENSE)
@@ -910,8 +891,7 @@ __device__ __forceinline__ void construct_ant(ItemPtr item, uint32_t it, int ant
             // branch-free: every lane of the list computes its key; visited
             // cities and lanes past the list contribute no key
             const float lnu = lnbuf[4 * j * G + (lane & (4 * G - 1))];
-            // the visited-bit load is issued first, then every lane divides (no
-            // exec mask), so that the division overlaps the load
+            // the visited-bit load is issued first, so that the product overlaps it
             const bool seen = tabu.visited(node);
             float key = lnu * w;  // (w holds 1 / choice_info)
             asm volatile("" : "+v"(key));
