@@ -1373,9 +1373,10 @@ __device__ __forceinline__ int pair_left(const T& a, const T& b, int h) { return
 // instruction issue, so what is wave-uniform (ant0, both cities, the
 // selection) stays in scalar registers and instructions, rows are addressed
 // by 32-bit offsets, and whatever only the rare paths need (a near tie, a
-// fallback) is read again there: about 47 vector instructions a step (75 with
-// the instance held in spilled scalar registers), 16 more for a quarter of the
-// draws' Philox block and logarithms. kTable: some rows are in LDS.
+// fallback) is read again there: about 38 vector instructions a step (75 with
+// the instance held in spilled scalar registers), 14 more for a quarter of the
+// draws' Philox block and logarithms, and no spilled register inside the loop.
+// kTable: some rows are in LDS.
 template <int kTabu, int kPher, bool kTable>
 __device__ __forceinline__ void construct_pair(ItemPtr item, uint32_t it, int ant0, int lane, uint8_t* regA, uint8_t* regB,
                                const uint16_t* tcand, const float* tchc, int R) {
@@ -1794,7 +1795,7 @@ static_assert(offsetof(BatchItem, v) == 0 && offsetof(BatchItem, s) == sizeof(Vi
 template <int kTabu, int kPher, bool kPair, bool kTable>
 // (limited to 64 VGPRs, which lets eight waves share a SIMD: the persistent
 // batch is bound by instruction issue, and the extra waves hide more latency
-// than the few spilled registers cost)
+// than the few registers cost that are spilled around the steps)
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_batch_construct(const BatchItem* __restrict__ items,
                                                           const BatchTile* __restrict__ tiles, int ntiles,
                                                           uint32_t* __restrict__ queue, const uint32_t* __restrict__ it_dev,

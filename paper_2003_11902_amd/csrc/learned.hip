@@ -70,9 +70,9 @@ __device__ __forceinline__ float sigmoid_f32(float s) { return 1.0f / (1.0f + ex
 // 1 - Phi(|z|) = h = E (c1 t + .. + c6 t^6) / 2, a form of Abramowitz and
 // Stegun 7.1.26 with a degree-6 fit made for this project (reweighted least
 // squares of z times the error: 1.5e-8 over the range), E and t by
-// v_exp_f32 and v_rcp_f32. 12 instructions and the two transcendentals, where
-// the degree-5 form with an IEEE division and a Taylor exponential took about
-// 65; against 64 bits over [-8, 8] GELU is off by at most 2.4e-7 and its
+// v_exp_f32 and v_rcp_f32. 13 instructions and the two transcendentals (the
+// derivative 5 more), where the degree-5 form with an IEEE division and a
+// Taylor exponential took about 65; against 64 bits over [-8, 8] GELU is off by at most 2.4e-7 and its
 // derivative by 2.5e-7 (4.7e-7 and 3.0e-7 before).
 struct Normal {
     float h, e;  // 1 - Phi(|z|), exp(-z^2/2)

@@ -73,7 +73,9 @@ constexpr int kNearCap = 256;
 // entry k times. (n = 3795: 57.6 MB, 12 us at a copy's rate.)
 // Rows with more than kNearCap entries up to the bound (long runs of equal
 // distances) look for the least bound that holds k, by bisection over all
-// entries, and take of the cities at it the first ones.
+// entries, and take of the cities at it the first ones (n = 3795, distances
+// 1 to 10: 81 us for the three kernels of the features; 520 by taking the next
+// smallest entry k times in the wave, 216 in four waves).
 // `clear` (or null): cleared at i, for the kernel that counts in-degrees next.
 template <int kRegs>
 __global__ __launch_bounds__(256) void k_nearest(const int32_t* __restrict__ d, int n, int k,
