@@ -150,10 +150,10 @@ void apply_tabu(mmas_batch* b, int tabu) {
 // Otherwise two ants per wave where the lists fit, eight per workgroup (four
 // where eight do not fit), and no table (rows from L2; a table leaves fewer
 // waves per SIMD to hide the steps' chains): 160 colonies of 64 ants, n
-// 200-1000: 1.21 ms a step against 3.62 with one ant per wave, four per
-// workgroup and a full table, and 1.41 without the table; 20 instances with
-// ants = n: 1.59, 9.49 and 2.51 ms; 2048 ants, n = 1000, lists of 8 entries:
-// 0.78, 1.15 and 0.74 ms.
+// 200-1000: 0.99 ms a step against 3.47 with one ant per wave, four per
+// workgroup and a full table, and 1.16 without the table; 20 instances, n
+// 100-2000, ants = n: 2.15, 15.1 and 3.62 ms; 2048 ants, n = 1000, lists of 8
+// entries: 0.78, 1.15 and 0.74 ms.
 void default_launch(mmas_batch* b) {
     int64_t ants = 0;
     int cl = 0;

@@ -350,9 +350,10 @@ __device__ __forceinline__ uint2 transpose(uint2 v, uint2 identity) {
 // The weight gradients sum over edges, so the waves turn their tiles of H1,
 // dZ2, dZ1 and X (an MFMA with the identity each) and exchange them through
 // LDS; wave w then owns output columns 16w .. + 15: 64 products for dW2, 4 for
-// dW1, and the column sums for the biases with a row of ones. Each GELU and
-// its derivative come from one evaluation. Bound by their vector instructions
-// at two waves a SIMD. 65536 edges, 256 workgroups: 209 -> 41 us (operands
+// dW1, and the column sums for the biases with a row of ones. Each GELU of
+// the second layer and its derivative come from one evaluation. Bound by the
+// chains of vector instructions (2600 per wave and 16 edges) at two waves a
+// SIMD, which the LDS leaves: one every 7 clocks of a SIMD. 65536 edges, 256 workgroups: 209 -> 41 us (operands
 // gathered from LDS two bytes at a time, three GELU evaluations per unit).
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_train(const uint16_t* __restrict__ X, const float* __restrict__ f,
                                                            const float* __restrict__ p,
